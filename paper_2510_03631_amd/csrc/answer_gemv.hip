@@ -12,12 +12,17 @@
 //   per limb every 16 bytes: ~1.25 VALU lane-ops per database byte, far
 //   under the ~4.9 the CUs can spend at full HBM rate.  All arithmetic
 //   wraps modulo 2^32, which is all the answer needs.
-// * A workgroup (4 waves) stages a slice of kSlice query words in LDS as the
+// * A workgroup (WV waves) stages a slice of kSlice query words in LDS as the
 //   four limb planes (split once per workgroup, not per wave).
 // * Each wave owns RW database rows.  One wave-wide 16-byte load covers 1024
 //   contiguous bytes of a row (fully coalesced); the RW row loads of a chunk
-//   are issued back to back so RW KiB per wave are in flight.  The stream is
-//   read with non-temporal loads.
+//   are issued back to back so RW KiB per wave are in flight, those of a
+//   slice's first chunk before the slice's query words are staged.  The
+//   stream is read with non-temporal loads.
+// * Rows may start at any address and have any length: loads of 16 bytes
+//   need no alignment on gfx950.  (Reading unaligned rows byte by byte took
+//   450 us for 20000 x 10007 bytes; 16-byte loads take 43 us, and 35 us when
+//   the same rows are padded to an aligned pitch.)
 // * After the column loop each lane holds RW partial sums; they are
 //   transposed through LDS and finished with lane shuffles, so one lane per
 //   row writes the result.
@@ -30,11 +35,8 @@
 
 namespace {
 
-constexpr int kWaves = 4;
-constexpr int kThreads = 64 * kWaves;
 constexpr int kChunk = 1024;   // columns covered by one wave-wide 16-byte load
 constexpr int kSlice = 4096;   // query words staged in LDS at a time
-constexpr int kRW = 16;        // rows per wave of the default variant
 
 // Four consecutive query words -> the four limb words; limb k holds byte k
 // of each word, the first word in the low byte.
@@ -48,19 +50,44 @@ __device__ inline void limbs_of4(uint32_t x0, uint32_t x1, uint32_t x2, uint32_t
     }
 }
 
-// 16 bytes of a row starting at column c, zero past column `end`.
-template <bool VEC>
-__device__ inline u32x4 load16(const uint8_t* row, uint32_t c, uint32_t end) {
-    if (VEC && c + 16 <= end) {
-        return __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(row + c));
-    }
-    uint32_t w[4] = {0, 0, 0, 0};
+// 16 bytes at any alignment (gfx950 serves unaligned global accesses; one
+// wave-wide load of 1024 consecutive bytes then touches nine lines, not
+// eight).
+typedef u32x4 u32x4_any __attribute__((aligned(1)));
+typedef u32x4 u32x4_word __attribute__((aligned(4)));
+
+__device__ inline u32x4 load_stream(const uint8_t* p) {
+    return __builtin_nontemporal_load(reinterpret_cast<const u32x4_any*>(p));
+}
+
+// Chunk loads of RW rows of C >= 16 bytes: the 16 bytes at column c of each
+// (c = chunk + 16 lane), or at C - 16 for lanes past that.
+template <int RW>
+__device__ inline void load_chunk(u32x4 (&d)[RW], const uint8_t* const (&rp)[RW], uint32_t c,
+                                  uint32_t C) {
+    const uint32_t at = min(c, C - 16u);
 #pragma unroll
-    for (int e = 0; e < 16; ++e) {
-        const uint32_t b = (c + e < end) ? row[c + e] : 0u;
-        w[e >> 2] |= b << (8 * (e & 3));
+    for (int i = 0; i < RW; ++i) d[i] = load_stream(rp[i] + at);
+}
+
+// In a row's ragged last chunk, move the bytes of the one lane whose 16
+// bytes cross the end into place.  (Lanes past the end hold anything: they
+// meet zero limbs.)
+template <int RW>
+__device__ inline void align_tail(u32x4 (&d)[RW], uint32_t c, uint32_t C) {
+    const uint32_t sh = 8u * min(c - min(c, C - 16u), 15u);
+#pragma unroll
+    for (int i = 0; i < RW; ++i) {
+        uint64_t lo = (uint64_t)d[i].x | ((uint64_t)d[i].y << 32);
+        uint64_t hi = (uint64_t)d[i].z | ((uint64_t)d[i].w << 32);
+        if (sh >= 64u) {
+            lo = hi >> (sh - 64u);
+        } else if (sh != 0u) {
+            lo = (lo >> sh) | (hi << (64u - sh));
+            hi >>= sh;
+        }
+        d[i] = u32x4{(uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32)};
     }
-    return u32x4{w[0], w[1], w[2], w[3]};
 }
 
 // 16 database bytes times the matching 16 query words, mod 2^32: per limb k
@@ -78,20 +105,23 @@ __device__ inline uint32_t dot16(const u32x4 d, const u32x4 L[4]) {
     return p[0] + (p[1] << 8) + (p[2] << 16) + (p[3] << 24);
 }
 
-template <int RW, bool VEC>
-__global__ __launch_bounds__(kThreads) void k_answer1(const uint8_t* __restrict__ D, uint64_t pitch,
-                                                      uint32_t R, uint32_t C,
-                                                      const uint32_t* __restrict__ q,
-                                                      uint32_t* __restrict__ out,
-                                                      uint32_t cols_per_split) {
+template <int RW, int WV>
+__global__ __launch_bounds__(64 * WV) void k_answer1(const uint8_t* __restrict__ D, uint64_t pitch,
+                                                     uint32_t R, uint32_t C,
+                                                     const uint32_t* __restrict__ q,
+                                                     uint32_t* __restrict__ out,
+                                                     uint32_t cols_per_split) {
+    // Loads ahead of the staging.  32 rows' loads held across it cost more
+    // registers than they gain (32768 x 32768: 165 us against 158 us).
+    constexpr bool kAhead = RW <= 16;
     __shared__ u32x4 s_limb[4][kSlice / 16];
-    __shared__ uint32_t s_red[kWaves][RW][65];
+    __shared__ uint32_t s_red[WV][RW][65];
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     // Wave-uniform, so the row addresses live in scalar registers.
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const uint32_t row0 = (blockIdx.x * kWaves + wave) * RW;
+    const uint32_t row0 = (blockIdx.x * WV + wave) * RW;
     const uint32_t cb = blockIdx.y * cols_per_split;
     const uint32_t ce = min(C, cb + cols_per_split);
 
@@ -107,17 +137,26 @@ __global__ __launch_bounds__(kThreads) void k_answer1(const uint8_t* __restrict_
 #pragma unroll
     for (int i = 0; i < RW; ++i) acc[i] = 0;
 
-    for (uint32_t s0 = cb; s0 < ce; s0 += kSlice) {
+    if (C < 16u) {   // shorter than a load: lane e takes column e
+        if ((uint32_t)lane < C) {
+#pragma unroll
+            for (int i = 0; i < RW; ++i) acc[i] = (uint32_t)rp[i][lane] * q[lane];
+        }
+    } else for (uint32_t s0 = cb; s0 < ce; s0 += kSlice) {
         const uint32_t se = min(ce, s0 + (uint32_t)kSlice);
+        u32x4 d[RW];
+        if (kAhead) load_chunk<RW>(d, rp, s0 + 16u * lane, C);
         __syncthreads();   // previous slice fully consumed
-        for (int t = tid; t < kSlice / 16; t += kThreads) {
+        // Limbs of the slice's words, zero past its end up to a whole chunk.
+        const uint32_t groups = (se - s0 + kChunk - 1) / kChunk * (kChunk / 16);
+        for (int t = tid; t < kSlice / 16; t += 64 * WV) {
+            if ((uint32_t)t >= groups) break;
             const uint32_t c = s0 + 16u * t;
             uint32_t x[16];
-            if (VEC && c + 16 <= se) {
-                const u32x4* qp = reinterpret_cast<const u32x4*>(q + c);
+            if (c + 16 <= se) {
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
-                    const u32x4 w = qp[v];
+                    const u32x4 w = *reinterpret_cast<const u32x4_word*>(q + c + 4 * v);
                     x[4 * v + 0] = w.x;
                     x[4 * v + 1] = w.y;
                     x[4 * v + 2] = w.z;
@@ -141,21 +180,22 @@ __global__ __launch_bounds__(kThreads) void k_answer1(const uint8_t* __restrict_
         __syncthreads();
 
         for (uint32_t c0 = s0; c0 < se; c0 += kChunk) {
-            const uint32_t li = (c0 - s0) / 16 + lane;
+            const uint32_t c = c0 + 16u * lane;
             u32x4 L[4];
 #pragma unroll
-            for (int k = 0; k < 4; ++k) L[k] = s_limb[k][li];
-            const uint32_t c = c0 + 16u * lane;
-            if (VEC && c0 + kChunk <= se) {
-                u32x4 d[RW];
+            for (int k = 0; k < 4; ++k) L[k] = s_limb[k][(c0 - s0) / 16 + lane];
+            if (!kAhead && c0 + kChunk <= se) {
+                // A whole chunk's loads and products, interleaved.
 #pragma unroll
-                for (int i = 0; i < RW; ++i)
-                    d[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(rp[i] + c));
+                for (int i = 0; i < RW; ++i) d[i] = load_stream(rp[i] + c);
 #pragma unroll
                 for (int i = 0; i < RW; ++i) acc[i] += dot16(d[i], L);
-            } else if (c < se) {
+                asm volatile("");   // keep the two branches' products apart
+            } else {
+                if (!kAhead || c0 != s0) load_chunk<RW>(d, rp, c, C);
+                if (c0 + kChunk > C) align_tail<RW>(d, c, C);
 #pragma unroll
-                for (int i = 0; i < RW; ++i) acc[i] += dot16(load16<VEC>(rp[i], c, se), L);
+                for (int i = 0; i < RW; ++i) acc[i] += dot16(d[i], L);
             }
         }
     }
@@ -190,32 +230,51 @@ struct SplitPlan {
     uint32_t cols_per_split;
 };
 
-// Split the columns only when the row blocks alone cannot give every CU
-// a workgroup; then aim at about four workgroups per CU, so the last
-// round's stragglers stay short (measured on the 3072 x 2^18 field-form
-// database, 48 row blocks: 11 splits 147 us, 21-32 splits 137-139 us).
-SplitPlan plan_splits(const pir_db_t* db, uint32_t rows_per_block) {
-    const uint64_t blocks = (db->rows + rows_per_block - 1) / rows_per_block;
-    const uint64_t chunks = (db->cols + kChunk - 1) / kChunk;
-    uint64_t s = 1;
-    if (blocks < 256) s = (1024 + blocks - 1) / blocks;
-    if (s > chunks) s = chunks;
+// Split the columns into `s` pieces, of at least `min_cols` columns each and
+// whole chunks (splits cost a second launch, about 2 us, and their partials).
+SplitPlan plan_splits(const pir_db_t* db, uint64_t s, uint32_t min_cols) {
+    s = std::min<uint64_t>(s, (db->cols + min_cols - 1) / min_cols);
     if (s < 1) s = 1;
     uint64_t cps = ((db->cols + s - 1) / s + kChunk - 1) / kChunk * kChunk;
     s = (db->cols + cps - 1) / cps;
     return SplitPlan{(uint32_t)s, (uint32_t)cps};
 }
 
+uint64_t row_blocks(const pir_db_t* db, uint32_t rows_per_block) {
+    return (db->rows + rows_per_block - 1) / rows_per_block;
+}
+
+// Single query.  Blocks of 64 rows and more run long, so the splits even out
+// the workgroups over the 256 CUs (eight waves of 8 rows, us: 3072 x 2^18, 48
+// blocks: 6 splits 163, 16 splits 129; 12288 x 40000, 192 blocks: not split
+// 90, 4 splits 83; 8192 x 32768, 128 blocks: 2 splits 48).  Smaller ones only
+// split where there are fewer than four per CU (1024 x 65536, two rows per
+// wave: 8 splits 16.2, not split 52; 2048 x 3001: not split 6.0, two 7.0).
+SplitPlan answer1_plan(const pir_db_t* db, uint32_t rows_per_block) {
+    const uint64_t blocks = row_blocks(db, rows_per_block);
+    if (rows_per_block < 64) return plan_splits(db, 1024 / blocks, kSlice);
+    uint64_t best = 1;
+    double best_t = 1e300;
+    for (uint64_t s = 1; s <= 16; ++s) {
+        const double t = (double)((blocks * s + 255) / 256) / s * (1.0 + 0.03 * s);
+        if (t < best_t) {
+            best_t = t;
+            best = s;
+        }
+    }
+    return plan_splits(db, best, kSlice);
+}
+
 size_t split_bytes(const pir_db_t* db, uint32_t rows_per_block) {
-    const SplitPlan p = plan_splits(db, rows_per_block);
+    const SplitPlan p = answer1_plan(db, rows_per_block);
     return p.splits > 1 ? round_up((size_t)p.splits * db->rows * 4, kWsAlign) : 0;
 }
 
-template <int RW>
+template <int RW, int WV>
 pir_status launch_answer1(const pir_db_t* db, const uint32_t* q, uint32_t* a, void* ws,
                           size_t ws_bytes, hipStream_t s) {
-    constexpr uint32_t kRows = RW * kWaves;
-    const SplitPlan p = plan_splits(db, kRows);
+    constexpr uint32_t kRows = RW * WV;
+    const SplitPlan p = answer1_plan(db, kRows);
     const uint32_t R = (uint32_t)db->rows, C = (uint32_t)db->cols;
     uint32_t* dst = a;
     if (p.splits > 1) {
@@ -223,14 +282,8 @@ pir_status launch_answer1(const pir_db_t* db, const uint32_t* q, uint32_t* a, vo
             return PIR_ERR_WORKSPACE;
         dst = static_cast<uint32_t*>(ws);
     }
-    const bool vec = db->aligned && ((uintptr_t)q % 16 == 0);
     dim3 grid((R + kRows - 1) / kRows, p.splits);
-    if (vec)
-        k_answer1<RW, true><<<grid, kThreads, 0, s>>>(db->D, db->pitch, R, C, q, dst,
-                                                      p.cols_per_split);
-    else
-        k_answer1<RW, false><<<grid, kThreads, 0, s>>>(db->D, db->pitch, R, C, q, dst,
-                                                       p.cols_per_split);
+    k_answer1<RW, WV><<<grid, 64 * WV, 0, s>>>(db->D, db->pitch, R, C, q, dst, p.cols_per_split);
     PIR_LAUNCH_CHECK();
     if (p.splits > 1) {
         k_sum_splits<<<(R + 255) / 256, 256, 0, s>>>(dst, R, p.splits, a);
@@ -241,17 +294,44 @@ pir_status launch_answer1(const pir_db_t* db, const uint32_t* q, uint32_t* a, vo
 
 struct GemvVariant {
     const char* name;
-    uint32_t rows_per_wave;
+    uint32_t rows_per_block;
     pir_status (*launch)(const pir_db_t*, const uint32_t*, uint32_t*, void*, size_t, hipStream_t);
 };
 
 const GemvVariant kGemv[] = {
-    {"auto", kRW, launch_answer1<kRW>},
-    {"rows16", 16, launch_answer1<16>},
-    {"rows8", 8, launch_answer1<8>},
-    {"rows32", 32, launch_answer1<32>},
+    {"auto", 0, nullptr},
+    {"rows16", 64, launch_answer1<16, 4>},
+    {"rows8", 32, launch_answer1<8, 4>},
+    {"rows32", 128, launch_answer1<32, 4>},
+    {"rows8w8", 64, launch_answer1<8, 8>},
+    {"rows4", 16, launch_answer1<4, 4>},
+    {"rows2", 8, launch_answer1<2, 4>},
 };
 constexpr uint32_t kNumGemv = sizeof(kGemv) / sizeof(kGemv[0]);
+constexpr uint32_t kGemvLong = 3, kGemvLarge = 4, kGemvMid = 5, kGemvSmall = 6;
+
+// Built-in choice.  While the whole stream lasts some tens of microseconds,
+// many short workgroups fill the chip most evenly; a longer one runs better
+// with more loads in flight per wave and the query slice staged once for
+// eight waves, and long rows with the fewest workgroups.  us, best split of
+// each:
+//                    rows16  rows32  rows8w8  rows4   rows2
+//   2048 x 3001       16.8      -       -       7.4     6.0
+//   4096 x 4096        7.9      -      7.3      6.8     5.5
+//   8192 x 8192       14.2     17.6   14.4     14.1    13.0
+//   65536 x 1024      12.9      -     12.9     11.9      -
+//   20000 x 10007     48.4      -     46.7     42.8      -
+//   4096 x 65536      46.2      -     45.9     46.5      -
+//   12288 x 40000     87.6      -     83.4     81.3      -
+//   3072 x 2^18      127        -    129      130        -
+//   40000 x 26001    197      199    171        -        -
+//   32768 x 32768    162      158    162      186      178
+//   131072 x 131072 2483     2408   2460     2524     2536
+uint32_t gemv_auto(const pir_db_t* db) {
+    if (db->rows >= 32768u && db->cols >= 32768u) return kGemvLong;
+    if (db->rows * db->cols >= (1ull << 28)) return kGemvLarge;
+    return db->rows >= 16384u ? kGemvMid : kGemvSmall;
+}
 
 // ---------------------------------------------------------------- few queries
 // Batches of at most 4 queries (and the field form's single query): the same
@@ -268,19 +348,29 @@ constexpr uint32_t kNumGemv = sizeof(kGemv) / sizeof(kGemv[0]);
 // the exact integer, reduced mod p once at the end.
 constexpr int kFewSlice = 2048;   // query words per LDS stage
 
-template <int NQ, int RW, bool VEC, bool EXACT>
-__global__ __launch_bounds__(kThreads) void k_answer_few(
+// Outputs of one workgroup row: the answer itself when one split covers all
+// columns (output element (r, b) at out[r * o_ldr + b * o_ldb], reduced mod p
+// in the field form), else a partial for k_few_finish.
+struct FewOut {
+    uint32_t* out;
+    uint64_t o_ldr, o_ldb;
+    uint32_t p;
+    void* part;
+};
+
+template <int NQ, int RW, int WV, bool EXACT>
+__global__ __launch_bounds__(64 * WV) void k_answer_few(
     const uint8_t* __restrict__ D, uint64_t pitch, uint32_t R, uint32_t C,
     const uint32_t* __restrict__ Q, uint64_t ldj, uint64_t ldb, uint32_t B,
-    uint32_t cols_per_split, void* __restrict__ part) {
+    uint32_t cols_per_split, FewOut o) {
     typedef typename std::conditional<EXACT, uint64_t, uint32_t>::type acc_t;
     __shared__ u32x4 s_limb[NQ][4][kFewSlice / 16];
-    __shared__ acc_t s_red[kWaves][RW][65];
+    __shared__ acc_t s_red[WV][RW][65];
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const uint32_t row0 = (blockIdx.x * kWaves + wave) * RW;
+    const uint32_t row0 = (blockIdx.x * WV + wave) * RW;
     const uint32_t cb = blockIdx.y * cols_per_split;
     const uint32_t ce = min(C, cb + cols_per_split);
 
@@ -296,10 +386,22 @@ __global__ __launch_bounds__(kThreads) void k_answer_few(
 #pragma unroll
         for (int b = 0; b < NQ; ++b) acc[i][b] = 0;
 
-    for (uint32_t s0 = cb; s0 < ce; s0 += kFewSlice) {
+    if (C < 16u) {   // shorter than a load: lane e takes column e
+        if ((uint32_t)lane < C) {
+#pragma unroll
+            for (int b = 0; b < NQ; ++b) {
+                const uint32_t x = (uint32_t)b < B ? Q[(uint64_t)lane * ldj + (uint64_t)b * ldb] : 0u;
+#pragma unroll
+                for (int i = 0; i < RW; ++i) acc[i][b] = (acc_t)rp[i][lane] * x;
+            }
+        }
+    } else for (uint32_t s0 = cb; s0 < ce; s0 += kFewSlice) {
         const uint32_t se = min(ce, s0 + (uint32_t)kFewSlice);
+        u32x4 d[RW];
+        // 16 rows' loads held across the staging would cost occupancy.
+        if (RW <= 8) load_chunk<RW>(d, rp, s0 + 16u * lane, C);
         __syncthreads();   // previous slice fully consumed
-        for (int t = tid; t < NQ * (kFewSlice / 16); t += kThreads) {
+        for (int t = tid; t < NQ * (kFewSlice / 16); t += 64 * WV) {
             const int b = t / (kFewSlice / 16);
             const int g = t % (kFewSlice / 16);
             const uint32_t c = s0 + 16u * g;
@@ -311,10 +413,10 @@ __global__ __launch_bounds__(kThreads) void k_answer_few(
             uint32_t l[4][4];
 #pragma unroll
             for (int w = 0; w < 4; ++w) {
-                uint32_t o[4];
-                limbs_of4(x[4 * w], x[4 * w + 1], x[4 * w + 2], x[4 * w + 3], o);
+                uint32_t o4[4];
+                limbs_of4(x[4 * w], x[4 * w + 1], x[4 * w + 2], x[4 * w + 3], o4);
 #pragma unroll
-                for (int k = 0; k < 4; ++k) l[k][w] = o[k];
+                for (int k = 0; k < 4; ++k) l[k][w] = o4[k];
             }
 #pragma unroll
             for (int k = 0; k < 4; ++k) s_limb[b][k][g] = u32x4{l[k][0], l[k][1], l[k][2], l[k][3]};
@@ -323,21 +425,13 @@ __global__ __launch_bounds__(kThreads) void k_answer_few(
 
         for (uint32_t c0 = s0; c0 < se; c0 += kChunk) {
             const uint32_t li = (c0 - s0) / 16 + lane;
-            const uint32_t c = c0 + 16u * lane;
-            u32x4 d[RW];
-            if (VEC && c0 + kChunk <= se) {
-#pragma unroll
-                for (int i = 0; i < RW; ++i)
-                    d[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(rp[i] + c));
-            } else {
-#pragma unroll
-                for (int i = 0; i < RW; ++i) d[i] = c < se ? load16<VEC>(rp[i], c, se) : u32x4{0, 0, 0, 0};
-            }
+            if (RW > 8 || c0 != s0) load_chunk<RW>(d, rp, c0 + 16u * lane, C);
+            if (c0 + kChunk > C) align_tail<RW>(d, c0 + 16u * lane, C);
 #pragma unroll
             for (int b = 0; b < NQ; ++b) {
                 u32x4 L[4];
 #pragma unroll
-                for (int k = 0; k < 4; ++k) L[k] = s_limb[b][k][li < kFewSlice / 16 ? li : 0];
+                for (int k = 0; k < 4; ++k) L[k] = s_limb[b][k][li];
 #pragma unroll
                 for (int i = 0; i < RW; ++i) {
                     if (EXACT) {
@@ -375,8 +469,12 @@ __global__ __launch_bounds__(kThreads) void k_answer_few(
         for (int t = 0; t < RW; ++t) v += s_red[wave][i][prt * RW + t];
 #pragma unroll
         for (int off = 1; off < kLanesPerRow; off <<= 1) v += __shfl_xor(v, off);
-        if (prt == 0 && r < R && (uint32_t)b < B)
-            static_cast<acc_t*>(part)[((uint64_t)blockIdx.y * B + b) * R + r] = v;
+        if (prt != 0 || r >= R || (uint32_t)b >= B) continue;
+        if (o.part)
+            static_cast<acc_t*>(o.part)[((uint64_t)blockIdx.y * B + b) * R + r] = v;
+        else
+            o.out[(uint64_t)r * o.o_ldr + (uint64_t)b * o.o_ldb] =
+                EXACT ? (uint32_t)(v % o.p) : (uint32_t)v;
     }
 }
 
@@ -403,34 +501,35 @@ __global__ void k_few_finish(const void* __restrict__ part, uint32_t R, uint32_t
     }
 }
 
-template <int NQ>
-constexpr int few_rw() { return NQ == 4 ? 8 : 16; }
-
 uint32_t few_nq(uint32_t B) { return B <= 1 ? 1u : (B <= 2 ? 2u : 4u); }
 
-// Column splits for the few-query stream (as for k_answer1), and the
-// partial buffer: splits x B x R accumulators (8 bytes, enough for both
-// forms).
-SplitPlan few_plan(const pir_db_t* db, uint32_t B) {
-    const uint32_t rw = few_nq(B) == 4 ? 8u : 16u;
-    return plan_splits(db, rw * kWaves);
+// Rows per workgroup and column splits.  The limb planes of NQ queries are
+// staged for a workgroup's rows, so it takes 64 (four waves of 16) and splits
+// to three workgroups per CU.  Below 32 MiB that leaves too few, and the
+// second launch of a split costs more than the staging: 16 rows (four waves
+// of 4).  us for one / two queries, 64 and 16 rows: 2048 x 3001 11.6 / 11.6
+// and 7.9 / 9.3; 4096 x 4096 8.5 / 9.8 and 9.0 / 11.3 (one launch, not two);
+// 8192 x 8192 15.8 / 19.7 and 20 / 28; 3072 x 2^18 131 / 155 and 183 / 286.
+uint32_t few_rows(const pir_db_t* db) { return db->rows * db->cols < (1ull << 25) ? 16u : 64u; }
+
+SplitPlan few_plan(const pir_db_t* db) {
+    const uint32_t rows = few_rows(db);
+    const uint64_t blocks = row_blocks(db, rows);
+    return rows == 16u ? plan_splits(db, 512 / blocks, kSlice) : plan_splits(db, 768 / blocks, kChunk);
 }
 
-template <int NQ, bool EXACT>
+template <int NQ, int RW, int WV, bool EXACT>
 pir_status launch_few_t(const pir_db_t* db, const BatchIO& io, uint32_t B, uint32_t modulus,
                         void* ws, hipStream_t s) {
-    constexpr int RW = few_rw<NQ>();
-    constexpr uint32_t kRows = RW * kWaves;
-    const SplitPlan pl = plan_splits(db, kRows);
+    constexpr uint32_t kRows = RW * WV;
+    const SplitPlan pl = few_plan(db);
     const uint32_t R = (uint32_t)db->rows, C = (uint32_t)db->cols;
     dim3 grid((R + kRows - 1) / kRows, pl.splits);
-    if (db->aligned)
-        k_answer_few<NQ, RW, true, EXACT><<<grid, kThreads, 0, s>>>(
-            db->D, db->pitch, R, C, io.Q, io.q_ldj, io.q_ldb, B, pl.cols_per_split, ws);
-    else
-        k_answer_few<NQ, RW, false, EXACT><<<grid, kThreads, 0, s>>>(
-            db->D, db->pitch, R, C, io.Q, io.q_ldj, io.q_ldb, B, pl.cols_per_split, ws);
+    const FewOut o{io.out, io.o_ldr, io.o_ldb, modulus, pl.splits > 1 ? ws : nullptr};
+    k_answer_few<NQ, RW, WV, EXACT><<<grid, 64 * WV, 0, s>>>(
+        db->D, db->pitch, R, C, io.Q, io.q_ldj, io.q_ldb, B, pl.cols_per_split, o);
     PIR_LAUNCH_CHECK();
+    if (pl.splits == 1) return PIR_OK;
     const uint64_t n = (uint64_t)R * B;
     k_few_finish<EXACT><<<(uint32_t)((n + 255) / 256), 256, 0, s>>>(
         ws, R, B, pl.splits, modulus, io.out, io.o_ldr, io.o_ldb);
@@ -438,11 +537,18 @@ pir_status launch_few_t(const pir_db_t* db, const BatchIO& io, uint32_t B, uint3
     return PIR_OK;
 }
 
+template <int NQ, bool EXACT>
+pir_status launch_few(const pir_db_t* db, const BatchIO& io, uint32_t B, uint32_t modulus,
+                      void* ws, hipStream_t s) {
+    if (few_rows(db) == 64u) return launch_few_t<NQ, 16, 4, EXACT>(db, io, B, modulus, ws, s);
+    return launch_few_t<NQ, 4, 4, EXACT>(db, io, B, modulus, ws, s);
+}
+
 }  // namespace
 
 size_t few_workspace_bytes(const pir_db_t* db, uint32_t B) {
     if (B == 0 || B > kFewMax) return 0;
-    const SplitPlan pl = few_plan(db, B);
+    const SplitPlan pl = few_plan(db);
     return round_up((size_t)pl.splits * B * db->rows * 8, kWsAlign);
 }
 
@@ -454,12 +560,12 @@ pir_status few_answer_batch(const pir_db_t* db, const BatchIO& io, uint32_t B, u
         return PIR_ERR_WORKSPACE;
     const bool exact = modulus != 0;
     switch (few_nq(B)) {
-        case 1: return exact ? launch_few_t<1, true>(db, io, B, modulus, ws, s)
-                             : launch_few_t<1, false>(db, io, B, modulus, ws, s);
-        case 2: return exact ? launch_few_t<2, true>(db, io, B, modulus, ws, s)
-                             : launch_few_t<2, false>(db, io, B, modulus, ws, s);
-        default: return exact ? launch_few_t<4, true>(db, io, B, modulus, ws, s)
-                              : launch_few_t<4, false>(db, io, B, modulus, ws, s);
+        case 1: return exact ? launch_few<1, true>(db, io, B, modulus, ws, s)
+                             : launch_few<1, false>(db, io, B, modulus, ws, s);
+        case 2: return exact ? launch_few<2, true>(db, io, B, modulus, ws, s)
+                             : launch_few<2, false>(db, io, B, modulus, ws, s);
+        default: return exact ? launch_few<4, true>(db, io, B, modulus, ws, s)
+                              : launch_few<4, false>(db, io, B, modulus, ws, s);
     }
 }
 
@@ -470,8 +576,8 @@ const char* gemv_variant_name(uint32_t v) { return v < kNumGemv ? kGemv[v].name 
 // Enough for every variant, so a workspace sized once serves any tuning.
 size_t gemv_workspace_bytes(const pir_db_t* db) {
     size_t m = 0;
-    for (uint32_t v = 0; v < kNumGemv; ++v) {
-        const size_t b = split_bytes(db, kGemv[v].rows_per_wave * kWaves);
+    for (uint32_t v = 1; v < kNumGemv; ++v) {
+        const size_t b = split_bytes(db, kGemv[v].rows_per_block);
         m = b > m ? b : m;
     }
     return m;
@@ -480,6 +586,6 @@ size_t gemv_workspace_bytes(const pir_db_t* db) {
 pir_status gemv_answer(const pir_db_t* db, const uint32_t* q, uint32_t* a, void* ws,
                        size_t ws_bytes, hipStream_t s) {
     uint32_t v = db->variant[0];
-    if (v >= kNumGemv) v = 0;
+    if (v == 0 || v >= kNumGemv) v = gemv_auto(db);
     return kGemv[v].launch(db, q, a, ws, ws_bytes, s);
 }

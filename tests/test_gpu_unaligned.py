@@ -1,0 +1,65 @@
+"""Databases whose rows start anywhere and have any length: the byte stream's
+chunks, slices, column splits and ragged last pieces, and the refresh.
+Results are whole numbers: equality with the oracle."""
+import numpy as np
+import pytest
+
+import oracle
+import workload
+from _util import banner, to_dev_u32, to_dev_u8, to_host_u32
+
+pytestmark = pytest.mark.gpu
+P = 4294967291
+
+
+@pytest.fixture(scope="module")
+def qp(gpu):
+    import paper_2510_03631_amd as p
+    return p
+
+
+def resident(D: np.ndarray, pad: int, shift: int):
+    """D on the device with rows `pad` bytes apart more than their length,
+    starting `shift` bytes past an aligned address; nothing after the last
+    row's bytes belongs to the tensor."""
+    import torch
+    R, C = D.shape
+    store = torch.zeros(shift + (R - 1) * (C + pad) + C, dtype=torch.uint8, device="cuda")
+    view = torch.as_strided(store, (R, C), (C + pad, 1), shift)
+    view.copy_(to_dev_u8(D))
+    return view
+
+
+@pytest.mark.parametrize("pad,shift", [(0, 0), (1, 0), (9, 5)])
+@pytest.mark.parametrize("R,C", [(1, 1), (5, 15), (9, 16), (70, 17), (3, 1023), (33, 1025),
+                                 (130, 4097), (300, 8193), (17, 40001)])
+def test_stream_ragged(qp, R, C, pad, shift):
+    banner(f"stream {R}x{C} pad={pad} shift={shift}")
+    g = np.random.default_rng(R * 31 + C + pad)
+    D = workload.db_bytes(g, R, C)
+    Q = workload.uniform_u32(g, (C, 4))
+    with qp.Database(resident(D, pad, shift)) as db:
+        for name in qp.variant_names(0):
+            db.set_variant(0, name)
+            a = to_host_u32(db.answer(to_dev_u32(Q[:, 0])))
+            assert np.array_equal(a, oracle.answer(D, Q[:, 0])), name
+        for B in (1, 2, 3, 4):
+            db.set_variant(B, "few")
+            q = np.ascontiguousarray(Q[:, :B])
+            assert np.array_equal(to_host_u32(db.answer_batch(to_dev_u32(q))),
+                                  oracle.answer_batch(D, q)), B
+            assert np.array_equal(to_host_u32(db.answer_batch_modp(to_dev_u32(q), P)),
+                                  oracle.answer_batch_mod(D, q, P)), B
+
+
+@pytest.mark.parametrize("R,C", [(16385, 16391), (3001, 90001)])
+def test_stream_large_ragged(qp, R, C):
+    """The large database's row blocks, whole and split by columns."""
+    banner(f"stream large {R}x{C}")
+    D_d = workload.device_db(R, C, workload.SEED_BASE + 5, "cuda")
+    D = D_d.cpu().numpy()
+    q = workload.uniform_u32(workload.rng(3), (C,))
+    with qp.Database(D_d) as db:
+        assert np.array_equal(to_host_u32(db.answer(to_dev_u32(q))), oracle.answer(D, q))
+        out = to_host_u32(db.answer_batch(to_dev_u32(q[:, None])))
+        assert np.array_equal(out[:, 0], oracle.answer(D, q))
