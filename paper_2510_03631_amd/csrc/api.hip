@@ -75,7 +75,7 @@ pir_status pir_db_open(uint8_t* d_D, uint64_t rows, uint64_t cols, uint64_t row_
     }
     db->magic = kDbMagic;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    pir_status st = launch_rowsum(db, nullptr, (uint32_t)rows, s);
+    pir_status st = launch_rowsum(db, s);
     if (st == PIR_OK && hipStreamSynchronize(s) != hipSuccess) st = PIR_ERR_DEVICE;
     if (st != PIR_OK) {
         db->magic = 0;
@@ -171,10 +171,7 @@ pir_status pir_update_rows(pir_db_t* db, const uint32_t* d_rows, uint32_t m,
     if (m == 0) return PIR_OK;
     if (!d_rows || !d_new || !on_db_device(db)) return PIR_ERR_INVALID_ARG;
     if (m > db->rows) return PIR_ERR_SHAPE;
-    hipStream_t s = static_cast<hipStream_t>(stream);
-    pir_status st = launch_scatter_rows(db, d_rows, m, d_new, s);
-    if (st != PIR_OK) return st;
-    return launch_rowsum(db, d_rows, m, s);
+    return launch_update_rows(db, d_rows, m, d_new, static_cast<hipStream_t>(stream));
 }
 
 pir_status pir_hint_update_rows(pir_db_t* db, const uint32_t* d_rows, uint32_t m,

@@ -87,9 +87,10 @@ pir_status few_answer_batch(const pir_db_t* db, const BatchIO& io, uint32_t B, u
                             void* ws, size_t ws_bytes, hipStream_t s);
 
 // ---- database metadata (db.hip)
-pir_status launch_rowsum(const pir_db_t* db, const uint32_t* rows, uint32_t m, hipStream_t s);
-pir_status launch_scatter_rows(const pir_db_t* db, const uint32_t* rows, uint32_t m,
-                               const uint8_t* src, hipStream_t s);
+pir_status launch_rowsum(const pir_db_t* db, hipStream_t s);
+// D[rows[i]] = src[i] and the rows' sums, i < m.
+pir_status launch_update_rows(const pir_db_t* db, const uint32_t* rows, uint32_t m,
+                              const uint8_t* src, hipStream_t s);
 
 // ---- batched / hint path (answer_mfma.hip)
 pir_status mfma_init();

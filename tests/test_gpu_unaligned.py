@@ -63,3 +63,27 @@ def test_stream_large_ragged(qp, R, C):
         assert np.array_equal(to_host_u32(db.answer(to_dev_u32(q))), oracle.answer(D, q))
         out = to_host_u32(db.answer_batch(to_dev_u32(q[:, None])))
         assert np.array_equal(out[:, 0], oracle.answer(D, q))
+
+
+@pytest.mark.parametrize("pad,shift", [(0, 0), (7, 3)])
+@pytest.mark.parametrize("R,C,m", [(3, 5, 3), (40, 16, 1), (300, 4111, 37), (50, 70003, 2)])
+def test_refresh_ragged(qp, R, C, m, pad, shift):
+    """A refresh writes the rows and their sums (which the batched product
+    reads), and nothing beside them."""
+    import torch
+    banner(f"refresh {R}x{C} m={m} pad={pad} shift={shift}")
+    g = np.random.default_rng(R + C + m)
+    D = workload.db_bytes(g, R, C)
+    rows = workload.distinct_rows(g, R, m)
+    new = workload.db_bytes(g, m, C)
+    Q = workload.uniform_u32(g, (C, 5))
+    view = resident(D, pad, shift)
+    with qp.Database(view) as db:
+        listed = to_dev_u32(np.concatenate([rows, [R]]).astype(np.uint32))   # one past the end
+        db.update_rows(listed[:m], to_dev_u8(new))
+        if m < R:
+            db.update_rows(listed[m:], torch.zeros((1, C), dtype=torch.uint8, device="cuda"))
+        D[rows] = new
+        assert np.array_equal(view.cpu().numpy(), D)
+        assert np.array_equal(to_host_u32(db.answer_batch(to_dev_u32(Q))),
+                              oracle.answer_batch(D, Q))
