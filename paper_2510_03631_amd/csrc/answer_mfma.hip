@@ -45,7 +45,7 @@
 //                 epilogue, optional row gather, optional split-K
 //   k_gemm_roles  the same with separate loader waves for D and QL
 //   k_gemm        register-staged LDS tiles, for databases the ring cannot
-//                 serve (unaligned rows or C not a multiple of 16)
+//                 serve (rows not 16-byte aligned)
 //   k_finish      sums split-K partials and adds the centring terms
 //
 // QL row index of (query b, limb k): n = (b / 32) * 128 + k * 32 + (b % 32),
@@ -408,136 +408,6 @@ __device__ inline TileId tile_of(uint32_t bid, uint32_t n_tiles, uint32_t m_tile
     return t;
 }
 
-// ---------------------------------------------------------------- GEMM, register-staged
-template <int WM_, int WN_, int TM_, int TN_, int BK_>
-struct Tile {
-    static constexpr int WM = WM_, WN = WN_, TM = TM_, TN = TN_, BK = BK_;
-    static constexpr int BM = WM * TM * 32;
-    static constexpr int BN = WN * TN * 32;
-    static constexpr int LDK = BK + 16;              // padded LDS row, bytes
-    static constexpr int A_LOADS = BM * BK / (256 * 16);
-    static constexpr int B_LOADS = BN * BK / (256 * 16);
-    static constexpr int SEGS = BK / 16;             // 16-byte pieces per row
-    static_assert(WM * WN == 4, "four waves");
-    static_assert(TN % 4 == 0, "a wave covers whole groups of four limbs");
-    static_assert(A_LOADS >= 1 && B_LOADS >= 1, "tile too small for 256 threads");
-};
-
-template <bool VEC>
-__device__ inline u32x4 load_row16(const uint8_t* row, uint32_t k, uint32_t C) {
-    if (VEC && k + 16 <= C) return *reinterpret_cast<const u32x4*>(row + k);
-    uint32_t w[4] = {0, 0, 0, 0};
-#pragma unroll
-    for (int e = 0; e < 16; ++e) {
-        const uint32_t b = (k + e < C) ? row[k + e] : 0u;
-        w[e >> 2] |= b << (8 * (e & 3));
-    }
-    return u32x4{w[0], w[1], w[2], w[3]};
-}
-
-// Block tile BM x BN of Out; 4 waves in a WM x WN grid, each computing
-// (TM*32) x (TN*32) with 32x32x32 int8 MFMAs; LDS tiles staged through
-// registers with one tile of prefetch.  LWE form, no split.
-template <class T, bool VEC, bool GATHER>
-__global__ __launch_bounds__(256) void k_gemm(const uint8_t* __restrict__ D, uint64_t pitch,
-                                              const int8_t* __restrict__ QL, uint32_t Cp,
-                                              uint32_t n_tiles, Epi e) {
-    __shared__ __attribute__((aligned(16))) uint8_t sA[T::BM * T::LDK];
-    __shared__ __attribute__((aligned(16))) uint8_t sB[T::BN * T::LDK];
-    const uint32_t R = e.R, C = e.C, M = e.M;
-
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = wave / T::WN;
-    const int wn = wave % T::WN;
-
-    const uint32_t bid = xcd_remap(blockIdx.x, gridDim.x);
-    const uint32_t m0 = (bid / n_tiles) * T::BM;
-    const uint32_t n0 = (bid % n_tiles) * T::BN;
-
-    // Global load assignment: thread -> (row, 16-byte segment).
-    const int seg = tid % T::SEGS;
-    const int rsub = tid / T::SEGS;
-    constexpr int ROWS_PER_PASS = 256 / T::SEGS;
-
-    const uint8_t* arow[T::A_LOADS];
-#pragma unroll
-    for (int p = 0; p < T::A_LOADS; ++p) {
-        uint32_t i = m0 + rsub + p * ROWS_PER_PASS;
-        i = i < M ? i : M - 1;
-        const uint32_t r = GATHER ? e.rows[i] : i;
-        arow[p] = D + (uint64_t)(r < R ? r : R - 1) * pitch;
-    }
-    const int8_t* brow[T::B_LOADS];
-#pragma unroll
-    for (int p = 0; p < T::B_LOADS; ++p)
-        brow[p] = QL + ql_row(n0 + rsub + p * ROWS_PER_PASS, Cp);
-
-    u32x4 ra[T::A_LOADS], rb[T::B_LOADS];
-    auto gload = [&](uint32_t k0) {
-        const uint32_t k = k0 + 16u * seg;
-#pragma unroll
-        for (int p = 0; p < T::A_LOADS; ++p) ra[p] = load_row16<VEC>(arow[p], k, C);
-#pragma unroll
-        for (int p = 0; p < T::B_LOADS; ++p)
-            rb[p] = *reinterpret_cast<const u32x4*>(brow[p] + ql_col(k));
-    };
-    auto lstore = [&]() {
-#pragma unroll
-        for (int p = 0; p < T::A_LOADS; ++p) {
-            const u32x4 v = ra[p] ^ u32x4{kCentreWord, kCentreWord, kCentreWord, kCentreWord};
-            *reinterpret_cast<u32x4*>(&sA[(rsub + p * ROWS_PER_PASS) * T::LDK + 16 * seg]) = v;
-        }
-#pragma unroll
-        for (int p = 0; p < T::B_LOADS; ++p)
-            *reinterpret_cast<u32x4*>(&sB[(rsub + p * ROWS_PER_PASS) * T::LDK + 16 * seg]) = rb[p];
-    };
-
-    i32x16 acc[T::TM][T::TN];
-#pragma unroll
-    for (int a = 0; a < T::TM; ++a)
-#pragma unroll
-        for (int b = 0; b < T::TN; ++b)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[a][b][v] = 0;
-
-    const int frag_row = lane & 31;
-    const int frag_k = 16 * (lane >> 5);
-
-    gload(0);
-    lstore();
-    __syncthreads();
-    for (uint32_t k0 = 0; k0 < C; k0 += T::BK) {
-        const bool more = k0 + T::BK < C;
-        if (more) gload(k0 + T::BK);
-#pragma unroll
-        for (int ks = 0; ks < T::BK / 32; ++ks) {
-            i32x4 fa[T::TM], fb[T::TN];
-#pragma unroll
-            for (int a = 0; a < T::TM; ++a)
-                fa[a] = *reinterpret_cast<const i32x4*>(
-                    &sA[(wm * T::TM * 32 + a * 32 + frag_row) * T::LDK + ks * 32 + frag_k]);
-#pragma unroll
-            for (int b = 0; b < T::TN; ++b)
-                fb[b] = *reinterpret_cast<const i32x4*>(
-                    &sB[(wn * T::TN * 32 + b * 32 + frag_row) * T::LDK + ks * 32 + frag_k]);
-#pragma unroll
-            for (int a = 0; a < T::TM; ++a)
-#pragma unroll
-                for (int b = 0; b < T::TN; ++b)
-                    acc[a][b] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[a], fb[b], acc[a][b], 0, 0, 0);
-        }
-        __syncthreads();
-        if (more) {
-            lstore();
-            __syncthreads();
-        }
-    }
-    epi_wave<kFinal32, GATHER, T::TM, T::TN>(e, 0, acc, m0 + wm * T::TM * 32,
-                                              n0 + wn * T::TN * 32, lane);
-}
-
 // ---------------------------------------------------------------- LDS ring helpers
 // 16-byte slot of (row, segment) in an LDS row.  A fragment read has 32
 // lanes on 32 consecutive rows at one segment; gfx950's LDS serves a
@@ -570,9 +440,195 @@ __device__ inline void ring_barrier() {
     asm volatile("" ::: "memory");
 }
 
+// ---------------------------------------------------------------- GEMM, register-staged
+// 16 bytes at any alignment.
+typedef u32x4 u32x4_any __attribute__((aligned(1)));
+
+template <int WM_, int WN_, int TM_, int TN_>
+struct Tile {
+    static constexpr int WM = WM_, WN = WN_, TM = TM_, TN = TN_, BK = 128;
+    static constexpr int NW = WM * WN;
+    static constexpr int THREADS = 64 * NW;
+    static constexpr int BM = WM * TM * 32;
+    static constexpr int BN = WN * TN * 32;
+    static constexpr int A_LOADS = BM / 8 / NW;      // 1 KiB blocks of 8 rows per wave
+    static constexpr int B_LOADS = BN / 8 / NW;
+    static constexpr int LOADS = A_LOADS + B_LOADS;
+    static constexpr int BUF_BYTES = (BM + BN) * BK;
+    static constexpr int LDS_BYTES = 2 * BUF_BYTES;
+    static_assert(NW == 4 || NW == 8, "four or eight waves");
+    static_assert(TN % 4 == 0, "a wave covers whole groups of four limbs");
+    static_assert(A_LOADS >= 1 && B_LOADS >= 1, "tile too small for the waves");
+    static_assert(LDS_BYTES <= 160 * 1024, "LDS");
+};
+
+// The product for databases the ring cannot serve: direct-to-LDS loads need
+// 16-byte aligned rows, so here the tiles pass through registers.  D rows are
+// read in 16-byte pieces at any address; in a row's ragged last tile the
+// piece that crosses the end is the row's last 16 bytes, shifted, and pieces
+// past it meet zero limbs.  LWE form.
+//
+// Two LDS buffers (the ring's swizzle) and one barrier per 128-byte tile: the
+// loads of tile u+1 are issued one after each of the first MFMAs of tile u
+// and written to the other buffer after its last.  Bound by that staging: the
+// loads have one tile's MFMAs to land, and every byte passes the register
+// file.  37 and 200 queries on 20000 rows of 10007 bytes, whole calls: byte
+// loads, no split-K 900 and 1885 us; 16-byte loads and split-K, one buffer and
+// two barriers 115 and 417 us; now 84 and 278 us.
+template <class T, bool GATHER, int MODE>
+__global__ __launch_bounds__(T::THREADS) void k_gemm(const uint8_t* __restrict__ D, uint64_t pitch,
+                                                     const int8_t* __restrict__ QL, uint32_t Cp,
+                                                     uint32_t n_tiles, uint32_t m_tiles,
+                                                     uint32_t kts, Epi e) {
+    extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
+    const uint32_t R = e.R, C = e.C, M = e.M;
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave / T::WN;
+    const int wn = wave % T::WN;
+
+    const TileId tl = tile_of(xcd_remap(blockIdx.x, gridDim.x), n_tiles, m_tiles,
+                              GATHER ? m_tiles : 8u);
+    const uint32_t m0 = tl.m * T::BM;
+    const uint32_t n0 = tl.n * T::BN;
+    const uint32_t ktiles_all = (C + T::BK - 1) / T::BK;
+    const uint32_t kt0 = tl.split * kts;
+    const uint32_t ktiles = kt0 < ktiles_all ? min(kts, ktiles_all - kt0) : 0u;
+
+    // Block i of this wave: rows 8 (wave + NW i) .. + 7, lane: row lane / 8,
+    // 16-byte segment lane % 8.
+    const int lrow = lane >> 3;
+    const uint32_t kseg = 16u * (lane & 7);
+    const uint8_t* arow[T::A_LOADS];
+    const int8_t* brow[T::B_LOADS];
+#pragma unroll
+    for (int i = 0; i < T::A_LOADS; ++i) {
+        uint32_t mi = m0 + 8 * (wave + T::NW * i) + lrow;
+        mi = mi < M ? mi : M - 1;
+        const uint32_t r = GATHER ? e.rows[mi] : mi;
+        arow[i] = D + (uint64_t)(r < R ? r : R - 1) * pitch;
+    }
+#pragma unroll
+    for (int i = 0; i < T::B_LOADS; ++i)
+        brow[i] = QL + ql_row(n0 + 8 * (wave + T::NW * i) + lrow, Cp) + kseg;
+
+    u32x4 ra[T::A_LOADS], rb[T::B_LOADS];
+    // Load i of the tile at column k0 (C >= 16), D first.
+    auto load_one = [&](uint32_t k0, int i) {
+        if (i < T::A_LOADS)
+            ra[i < T::A_LOADS ? i : 0] = *reinterpret_cast<const u32x4_any*>(
+                arow[i < T::A_LOADS ? i : 0] + min(k0 + kseg, C - 16u));
+        else
+            rb[i - T::A_LOADS] = *reinterpret_cast<const u32x4*>(brow[i - T::A_LOADS] + ql_col(k0));
+    };
+    auto store = [&](uint32_t k0, uint8_t* buf) {
+        if (k0 + T::BK > C && C % 16u != 0u) {   // the row's ragged last tile
+            const uint32_t k = k0 + kseg;
+            const uint32_t sh = 8u * min(k - min(k, C - 16u), 15u);
+#pragma unroll
+            for (int i = 0; i < T::A_LOADS; ++i) {
+                u64 lo = (u64)ra[i].x | ((u64)ra[i].y << 32), hi = (u64)ra[i].z | ((u64)ra[i].w << 32);
+                if (sh >= 64u) {
+                    lo = hi >> (sh - 64u);
+                } else if (sh != 0u) {
+                    lo = (lo >> sh) | (hi << (64u - sh));
+                    hi >>= sh;
+                }
+                ra[i] = u32x4{(uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32)};
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < T::A_LOADS; ++i) {
+            const int r = 8 * (wave + T::NW * i) + lrow;
+            *reinterpret_cast<u32x4*>(buf + r * T::BK + 16 * swz<128>(r, lane & 7)) =
+                ra[i] ^ u32x4{kCentreWord, kCentreWord, kCentreWord, kCentreWord};
+        }
+#pragma unroll
+        for (int i = 0; i < T::B_LOADS; ++i) {
+            const int r = 8 * (wave + T::NW * i) + lrow;
+            *reinterpret_cast<u32x4*>(buf + T::BM * T::BK + r * T::BK +
+                                      16 * swz<128>(r, lane & 7)) = rb[i];
+        }
+    };
+
+    i32x16 acc[T::TM][T::TN];
+#pragma unroll
+    for (int a = 0; a < T::TM; ++a)
+#pragma unroll
+        for (int b = 0; b < T::TN; ++b)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[a][b][v] = 0;
+
+    const int frow = lane & 31;
+    const int fseg = lane >> 5;
+    i32x4 fa[2][T::TM], fb[2][T::TN];
+    auto read_frags = [&](const uint8_t* buf, int ks, int f) {
+        const int seg = 2 * ks + fseg;
+#pragma unroll
+        for (int a = 0; a < T::TM; ++a) {
+            const int r = wm * T::TM * 32 + a * 32 + frow;
+            fa[f][a] = *reinterpret_cast<const i32x4*>(buf + r * T::BK + 16 * swz<128>(r, seg));
+        }
+#pragma unroll
+        for (int b = 0; b < T::TN; ++b) {
+            const int r = wn * T::TN * 32 + b * 32 + frow;
+            fb[f][b] = *reinterpret_cast<const i32x4*>(buf + T::BM * T::BK + r * T::BK +
+                                                       16 * swz<128>(r, seg));
+        }
+    };
+
+    if (ktiles > 0) {
+        if (C >= 16u) {
+#pragma unroll
+            for (int i = 0; i < T::LOADS; ++i) load_one(kt0 * T::BK, i);
+        } else {   // rows shorter than a load: one tile, byte by byte
+#pragma unroll
+            for (int i = 0; i < T::A_LOADS; ++i) {
+                uint32_t w[4] = {0, 0, 0, 0};
+                for (uint32_t x = 0; kseg + x < C; ++x)
+                    w[x >> 2] |= (uint32_t)arow[i][kseg + x] << (8 * (x & 3));
+                ra[i] = u32x4{w[0], w[1], w[2], w[3]};
+            }
+#pragma unroll
+            for (int i = T::A_LOADS; i < T::LOADS; ++i) load_one(0, i);
+        }
+        store(C >= 16u ? kt0 * T::BK : 0u, smem);
+    }
+    __syncthreads();
+    for (uint32_t u = 0; u < ktiles; ++u) {
+        const uint8_t* buf = smem + (u & 1u) * T::BUF_BYTES;
+        // Past the last tile the loads repeat it, into a buffer nobody reads.
+        const uint32_t k1 = (kt0 + min(u + 1u, ktiles - 1u)) * T::BK;
+        read_frags(buf, 0, 0);
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) {
+            if (ks < 3) read_frags(buf, ks + 1, (ks + 1) & 1);
+            __builtin_amdgcn_sched_barrier(0);
+            constexpr int kMfma = T::TM * T::TN;
+            const int lo = ks * kMfma < T::LOADS ? ks * kMfma : T::LOADS;
+            const int hi = (ks + 1) * kMfma < T::LOADS ? (ks + 1) * kMfma : T::LOADS;
+#pragma unroll
+            for (int a = 0; a < T::TM; ++a)
+#pragma unroll
+                for (int b = 0; b < T::TN; ++b)
+                    acc[a][b] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[ks & 1][a], fb[ks & 1][b],
+                                                                      acc[a][b], 0, 0, 0);
+            if (C >= 16u) {
+#pragma unroll
+                for (int i = lo; i < hi; ++i) load_one(k1, i);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if (C >= 16u) store(k1, smem + ((u + 1u) & 1u) * T::BUF_BYTES);
+        __syncthreads();
+    }
+    epi_wave<MODE, GATHER, T::TM, T::TN>(e, tl.split, acc, m0 + wm * T::TM * 32,
+                                          n0 + wn * T::TN * 32, lane);
+}
+
 // ---------------------------------------------------------------- GEMM, LDS ring
-// The main kernel for aligned databases with C a multiple of 16.  Global
-// tiles go straight to LDS with global_load_lds_dwordx4 (no register
+// The main kernel for databases with 16-byte aligned rows.  Global tiles go straight to LDS with global_load_lds_dwordx4 (no register
 // staging), into a ring of STAGES k-tiles of BK bytes, so STAGES-1 tiles are
 // in flight while one is consumed.  Centring of D (xor 0x80) is applied to
 // the A fragments in registers.
@@ -692,8 +748,9 @@ __global__ __launch_bounds__(T::THREADS) void k_gemm_ring(const uint8_t* __restr
 
     // Load i of k-tile t into its ring slot.  Every load is issued, so each
     // wave has the same count in flight per tile:
-    // * a D segment past column C reads the row's last 16 bytes instead (C
-    //   is a multiple of 16); those bytes meet zero-padded query bytes;
+    // * a D segment past column C reads the row's last 16-byte segment
+    //   instead; those bytes, and any of the row's padding in that segment,
+    //   meet zero-padded query bytes;
     // * t past the piece's last tile is clamped to it: such a load refills a
     //   slot no later iteration reads.
     const uint32_t t_last = ktiles ? ktiles - 1 : 0;
@@ -707,7 +764,7 @@ __global__ __launch_bounds__(T::THREADS) void k_gemm_ring(const uint8_t* __restr
         const uint32_t k0 = (kt0 + tt) * T::BK;
         uint8_t* dst = (a ? ringA + (t % T::SA) * T::A_BYTES : ringB + (t % T::SB) * T::B_BYTES) +
                        (wave + T::NW * blk(i)) * 1024;
-        const uint8_t* p = a ? src[i] + min(k0 + seg_off[i], C - 16u)
+        const uint8_t* p = a ? src[i] + min(k0 + seg_off[i], (C - 1u) & ~15u)
                              : src[i] + ql_col(k0);   // BK divides 128
         if (NTD && a)   // D read once: non-temporal
             __builtin_amdgcn_global_load_lds((glb_void_t*)p, (lds_void_t*)dst, 16, 0, kCpolNT);
@@ -1085,30 +1142,43 @@ pir_status set_roles_lds() {
 
 template <class T>
 pir_status launch_reg(const Gemm& g, hipStream_t s) {
-    if (g.exact || g.splits != 1) return PIR_ERR_UNSUPPORTED;
+    if (g.exact) return PIR_ERR_UNSUPPORTED;
     const uint32_t n_tiles = ceil_div(g.N, T::BN);
     const uint32_t m_tiles = ceil_div(g.e.M, T::BM);
-    const uint64_t blocks = (uint64_t)n_tiles * m_tiles;
+    const uint64_t blocks = (uint64_t)n_tiles * m_tiles * g.splits;
     if (blocks > 0x7FFFFFFFull) return PIR_ERR_SHAPE;
     const pir_db_t* db = g.db;
-#define PIR_GEMM(VEC, GATHER)                                                              \
-    k_gemm<T, VEC, GATHER><<<(uint32_t)blocks, 256, 0, s>>>(db->D, db->pitch, g.QL, g.Cp, \
-                                                             n_tiles, g.e)
-    const bool gather = g.e.rows != nullptr;
-    if (db->aligned) {
-        if (gather) PIR_GEMM(true, true); else PIR_GEMM(true, false);
+#define PIR_GEMM(GATHER, MODE)                                                              \
+    k_gemm<T, GATHER, MODE><<<(uint32_t)blocks, T::THREADS, T::LDS_BYTES, s>>>(             \
+        db->D, db->pitch, g.QL, g.Cp, n_tiles, m_tiles, g.kts, g.e)
+    if (g.splits > 1) {
+        if (g.e.rows) PIR_GEMM(true, kPart32); else PIR_GEMM(false, kPart32);
     } else {
-        if (gather) PIR_GEMM(false, true); else PIR_GEMM(false, false);
+        if (g.e.rows) PIR_GEMM(true, kFinal32); else PIR_GEMM(false, kFinal32);
     }
 #undef PIR_GEMM
     PIR_LAUNCH_CHECK();
     return PIR_OK;
 }
 
-// Kernel variants of the batched product.  Ring and roles variants need a
-// 16-byte aligned database with C a multiple of 16; 256-wide tiles need N a
-// multiple of 256 (batches above 32 queries, padded to 64).  Only ring
-// variants split K (and so serve the field form).
+template <class T>
+pir_status set_reg_lds() {
+    const void* fns[] = {
+        (const void*)k_gemm<T, false, kFinal32>, (const void*)k_gemm<T, true, kFinal32>,
+        (const void*)k_gemm<T, false, kPart32>, (const void*)k_gemm<T, true, kPart32>,
+    };
+    for (const void* f : fns)
+        if (hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, T::LDS_BYTES) !=
+            hipSuccess)
+            return PIR_ERR_DEVICE;
+    return PIR_OK;
+}
+
+// Kernel variants of the batched product.  Ring and roles variants may be
+// pinned on a 16-byte aligned database with C a multiple of 16; 256-wide tiles
+// need N a multiple of 256 (batches above 32 queries, padded to 64).  Ring
+// variants split K (and so serve the field form), register-staged ones on the
+// databases the ring does not serve.
 using Ring128x128S8 = Ring<4, 1, 1, 4, 8>;              // 128 KiB LDS
 using Ring128x128K128S4 = Ring<4, 1, 1, 4, 4, 128>;     // 128 KiB, 128-byte stages
 using Ring128x256S6 = Ring<2, 2, 2, 4, 6>;              // 144 KiB
@@ -1142,8 +1212,9 @@ using Narrow256x64K128S4 = Ring<8, 1, 1, 2, 4, 128, true>;    // <= 16 queries, 
 using Narrow128x32K128S6 = Ring<4, 1, 1, 1, 6, 128, true>;    // <= 8 queries, 120 KiB
 using Roles256x256A5B4 = Roles<2, 2, 4, 4, 5, 4>;       // 80 + 64 KiB
 using Roles128x256A10B4 = Roles<2, 2, 2, 4, 10, 4>;     // 80 + 64 KiB
-using Reg128x256 = Tile<2, 2, 2, 4, 128>;
-using Reg128x128 = Tile<4, 1, 1, 4, 128>;
+using Reg128x256 = Tile<4, 2, 1, 4>;                     // 8 waves, 96 KiB
+using Reg128x128 = Tile<4, 1, 1, 4>;                     // 4 waves, 64 KiB: two per CU
+using Reg256x256 = Tile<4, 2, 2, 4>;                     // 8 waves, 128 KiB
 
 enum Kind : uint8_t { kAuto, kRing, kRoles, kReg, kFew };
 
@@ -1168,7 +1239,7 @@ constexpr VariantInfo kVariants[] = {
     {"roles_256x256_a5b4", kRoles, 256, 256, 64, launch_roles<Roles256x256A5B4>},
     {"roles_128x256_a10b4", kRoles, 128, 256, 64, launch_roles<Roles128x256A10B4>},
     {"reg_128x256", kReg, 128, 256, 128, launch_reg<Reg128x256>},
-    {"reg_128x128", kReg, 128, 128, 128, launch_reg<Reg128x128>},
+    {"reg_128x128", kReg, 128, 128, 128, launch_reg<Reg128x128>, 2},
     {"few", kFew, 0, 0, 0, nullptr},   // dot4 stream, batches of at most kFewMax
     {"ring_128x128_k128_s2", kRing, 128, 128, 128, launch_ring<Ring128x128K128S2>, 2},
     {"narrow_256x32_k128_s4", kRing, 256, 32, 128, launch_ring<Narrow256x32K128S4>, 1, true},
@@ -1182,23 +1253,31 @@ constexpr VariantInfo kVariants[] = {
     {"narrow_128x32_k128_d8q6", kRing, 128, 32, 128, launch_ring<Narrow128x32K128D8>, 1, true},
     {"ring_256x256_k128_d3q2", kRing, 256, 256, 128, launch_ring<Ring256x256K128D3>},
     {"ring_256x256_k128_d2q3", kRing, 256, 256, 128, launch_ring<Ring256x256K128Q3>},
+    {"reg_256x256", kReg, 256, 256, 128, launch_reg<Reg256x256>},
 };
 constexpr uint32_t kNumVariants = sizeof(kVariants) / sizeof(kVariants[0]);
-constexpr uint32_t kVarRing128 = 2, kVarRing256 = 4, kVarReg256 = 10,
-                   kVarReg128 = 11, kVarFew = 12, kVarRing4wD3 = 23;
+constexpr uint32_t kVarRing128 = 2, kVarRing256 = 4, kVarReg128 = 11, kVarFew = 12,
+                   kVarRing4wD3 = 23, kVarReg256 = 25;
 constexpr bool same_name(const char* a, const char* b) {
     return *a == *b && (*a == '\0' || same_name(a + 1, b + 1));
 }
 // The built-in choices name table rows by index: keep them on their rows.
 static_assert(same_name(kVariants[kVarRing128].name, "ring_128x128_k128_s4") &&
                   same_name(kVariants[kVarRing256].name, "ring8w_128x256_k128_s3") &&
-                  same_name(kVariants[kVarReg256].name, "reg_128x256") &&
+                  same_name(kVariants[kVarReg256].name, "reg_256x256") &&
                   same_name(kVariants[kVarReg128].name, "reg_128x128") &&
                   same_name(kVariants[kVarFew].name, "few") &&
                   same_name(kVariants[kVarRing4wD3].name, "ring_256x256_k128_d3q2"),
               "default variant indices");
 
+// Databases the ring kernels may be pinned for and the field form runs on.
 bool ring_ok(const pir_db_t* db) { return db->aligned && (db->cols % 16 == 0); }
+
+// Databases the ring serves: aligned rows of any length (a row's last 16-byte
+// segment lies inside its pitch).  37 and 200 queries on 20000 rows of 10007
+// bytes, pitch 10240: 74 and 228 us, against 166 and 454 us while rows whose
+// length is not a multiple of 16 went through registers.
+bool ring_serves(const pir_db_t* db) { return db->aligned; }
 
 uint32_t padded_batch(uint32_t B) { return B <= 32u ? 32u : (B + 63u) / 64u * 64u; }
 
@@ -1221,10 +1300,12 @@ bool variant_valid(const pir_db_t* db, uint32_t B, uint32_t v) {
 // Matrix-core choice (any batch size, gathered rows allowed).  From 64
 // queries up, the four-wave 256 x 256 tile with the deeper D ring
 // (ring_256x256_k128_d3q2), which led the autotuner at 64-1024 queries on
-// 32768^2, 131072^2, 65536 x 32768 and the 3072 x 2^18 field form.
+// 32768^2, 131072^2, 65536 x 32768 and the 3072 x 2^18 field form.  Unaligned
+// rows: the 256 x 256 register-staged tile above 32 queries (37 queries on
+// 30000 x 20001: 233 us, 128 x 256 372, 128 x 128 350).
 uint32_t default_gemm(const pir_db_t* db, uint32_t B) {
     const uint32_t Bp = padded_batch(B);
-    if (!ring_ok(db)) return Bp == 32u ? kVarReg128 : kVarReg256;
+    if (!ring_serves(db)) return Bp == 32u ? kVarReg128 : kVarReg256;
     if (Bp == 32u) return kVarRing128;
     return kVarRing4wD3;
 }
@@ -1245,7 +1326,7 @@ uint32_t default_variant(const pir_db_t* db, uint32_t B) {
 // two-stage 256 x 256 tile that is fastest over the whole database (that
 // one took 1146 us for the same rows sorted, 980 us for consecutive rows).
 uint32_t default_rows(const pir_db_t* db, uint32_t B) {
-    return ring_ok(db) && padded_batch(B) >= 64u ? kVarRing256 : default_gemm(db, B);
+    return ring_serves(db) && padded_batch(B) >= 64u ? kVarRing256 : default_gemm(db, B);
 }
 
 struct SplitPlan {
@@ -1259,9 +1340,12 @@ struct SplitPlan {
 // piece) that minimises that time, with a small charge per piece for the
 // partials and the pipeline fill, considered only below two rounds of
 // tiles.  The field form also caps each piece at kExactSpan columns.
-SplitPlan plan_splits(uint32_t M, uint32_t N, uint32_t C, const VariantInfo& vi, bool exact) {
+// `reg`: register-staged tiles split too (on databases the ring does not
+// serve; elsewhere they are only run when pinned, whole).
+SplitPlan plan_splits(uint32_t M, uint32_t N, uint32_t C, const VariantInfo& vi, bool exact,
+                      bool reg) {
     const uint32_t ktiles = ceil_div(C, vi.bk);
-    if (vi.kind != kRing || ktiles == 0) return {1u, ktiles};
+    if (!(vi.kind == kRing || (reg && vi.kind == kReg)) || ktiles == 0) return {1u, ktiles};
     const uint64_t tiles = (uint64_t)ceil_div(M, vi.bm) * ceil_div(N, vi.bn);
     const uint32_t lo = exact ? ceil_div(ktiles, kExactSpan / vi.bk) : 1u;
     const uint64_t slots = (uint64_t)g_cus * std::max(1u, vi.per_cu);
@@ -1290,14 +1374,16 @@ struct BatchLayout {
 // wide layout has N limb columns: every ring variant valid for them (narrow
 // variants, one column tile, for N = 128: batches of at most 32), every
 // output row count up to R (gathered calls have fewer rows, and so may split
-// more), both forms.
+// more), both forms.  On a database the ring does not serve, every
+// register-staged variant instead.
 uint64_t worst_split_rows(const pir_db_t* db, uint32_t N_wide) {
     const uint32_t R = (uint32_t)db->rows, C = (uint32_t)db->cols;
-    const bool exact_ok = C <= kMaxExactCols;
+    const bool exact_ok = C <= kMaxExactCols && ring_ok(db);
+    const bool reg = !ring_serves(db);
     uint64_t worst = 0;   // splits x rows
     for (uint32_t v = 1; v < kNumVariants; ++v) {
         const VariantInfo& vi = kVariants[v];
-        if (vi.kind != kRing) continue;
+        if (vi.kind != (reg ? kReg : kRing)) continue;
         if (vi.narrow ? N_wide != 128u : N_wide % vi.bn != 0) continue;
         const uint32_t N = vi.narrow ? vi.bn : N_wide;
         const uint32_t nt = N / vi.bn;
@@ -1308,12 +1394,12 @@ uint64_t worst_split_rows(const pir_db_t* db, uint32_t N_wide) {
         for (uint32_t mt = 1; mt <= mt_hi + 1 && mt <= mt_all; ++mt) {
             const uint32_t M = mt == mt_all ? R : mt * vi.bm;
             for (int x = 0; x <= (exact_ok ? 1 : 0); ++x) {
-                const SplitPlan sp = plan_splits(M, N, C, vi, x == 1);
+                const SplitPlan sp = plan_splits(M, N, C, vi, x == 1, reg);
                 if (sp.splits > 1) worst = std::max<uint64_t>(worst, (uint64_t)sp.splits * M);
             }
         }
         for (int x = 0; x <= (exact_ok ? 1 : 0); ++x) {
-            const SplitPlan sp = plan_splits(R, N, C, vi, x == 1);
+            const SplitPlan sp = plan_splits(R, N, C, vi, x == 1, reg);
             if (sp.splits > 1) worst = std::max<uint64_t>(worst, (uint64_t)sp.splits * R);
         }
     }
@@ -1325,7 +1411,6 @@ uint64_t worst_split_rows(const pir_db_t* db, uint32_t N_wide) {
 // kept in the handle per padded-batch bucket (racing writers store the same
 // value).
 size_t partial_bound(const pir_db_t* db, uint32_t B, uint32_t N) {
-    if (!ring_ok(db)) return 0;
     std::atomic<uint64_t>& slot = db->split_rows[batch_bucket(N / 4)];
     uint64_t cached = slot.load(std::memory_order_relaxed);
     uint64_t worst;
@@ -1384,6 +1469,9 @@ pir_status mfma_init() {
     if ((st = set_ring_lds<Narrow128x32K128D8>()) != PIR_OK) return st;
     if ((st = set_ring_lds<Ring256x256K128D3>()) != PIR_OK) return st;
     if ((st = set_ring_lds<Ring256x256K128Q3>()) != PIR_OK) return st;
+    if ((st = set_reg_lds<Reg128x256>()) != PIR_OK) return st;
+    if ((st = set_reg_lds<Reg128x128>()) != PIR_OK) return st;
+    if ((st = set_reg_lds<Reg256x256>()) != PIR_OK) return st;
     if ((st = set_roles_lds<Roles256x256A5B4>()) != PIR_OK) return st;
     return set_roles_lds<Roles128x256A10B4>();
 }
@@ -1441,7 +1529,7 @@ pir_status mfma_plan_batch(const pir_db_t* db, uint32_t B, const uint32_t* rows,
     P.part_off = L.part_off;
     if ((uint64_t)L.Cp / kIngJ > g_max_grid_y) return PIR_ERR_SHAPE;   // ingest grid
     P.M = rows ? m : (uint32_t)db->rows;
-    const SplitPlan sp = plan_splits(P.M, L.N, C, vi, exact);
+    const SplitPlan sp = plan_splits(P.M, L.N, C, vi, exact, !ring_serves(db));
     P.splits = sp.splits;
     P.kts = sp.kts;
     const uint64_t blocks = (uint64_t)ceil_div(L.N, vi.bn) * ceil_div(P.M, vi.bm) * sp.splits;
@@ -1455,6 +1543,16 @@ pir_status mfma_plan_batch(const pir_db_t* db, uint32_t B, const uint32_t* rows,
     }
     *plan = P;
     return PIR_OK;
+}
+
+// Run in one piece what a fixed scratch cannot hold the partials of, on the
+// databases outside the ring variants' reach (a caller's 64 queries on an
+// unaligned database keep fitting the allocation-free entry point).
+void mfma_plan_fit(const pir_db_t* db, size_t scratch_bytes, BatchPlan* plan) {
+    if (plan->few || plan->splits <= 1 || plan->need <= scratch_bytes || ring_ok(db)) return;
+    plan->splits = 1;
+    plan->kts = ceil_div(db->cols, kVariants[plan->variant].bk);
+    plan->need = plan->part_off;
 }
 
 // Zero the column sums, then write the limb planes and column sums of the

@@ -87,3 +87,49 @@ def test_refresh_ragged(qp, R, C, m, pad, shift):
         assert np.array_equal(view.cpu().numpy(), D)
         assert np.array_equal(to_host_u32(db.answer_batch(to_dev_u32(Q))),
                               oracle.answer_batch(D, Q))
+
+
+@pytest.mark.parametrize("pad,shift", [(0, 0), (9, 5), (None, 0)])
+@pytest.mark.parametrize("R,C", [(1, 1), (3, 15), (40, 17), (127, 127), (129, 129), (257, 255),
+                                 (300, 1000), (513, 4113)])
+def test_batch_ragged(qp, R, C, pad, shift):
+    """The batched product's tiles, split-K pieces and ragged last k-tile on
+    unaligned rows and (pad None) on aligned rows of odd length, and the
+    incremental hint on some of the rows."""
+    if pad is None:
+        pad = -C % 16
+    banner(f"batch {R}x{C} pad={pad} shift={shift}")
+    g = np.random.default_rng(R * 17 + C + pad)
+    D = workload.db_bytes(g, R, C)
+    Q = workload.uniform_u32(g, (C, 130))
+    D[0], Q[:, 0] = 0x80, 0x80808080            # the centred products' extremes
+    D[-1], Q[:, -1] = 0xFF, 0xFFFFFFFF
+    ref = oracle.answer_batch(D, Q)
+    with qp.Database(resident(D, pad, shift)) as db:
+        for B in (3, 32, 33, 64, 130):
+            q = to_dev_u32(np.ascontiguousarray(Q[:, -B:]))
+            assert np.array_equal(to_host_u32(db.answer_batch(q)), ref[:, -B:]), B
+            assert np.array_equal(to_host_u32(db.answer_batch_qmajor(q.t().contiguous())),
+                                  ref[:, -B:].T), B
+        rows = workload.distinct_rows(g, R, (R + 2) // 3)
+        H = to_dev_u32(np.zeros((R, 130), dtype=np.uint32))
+        got = to_host_u32(db.hint_update_rows(to_dev_u32(rows), to_dev_u32(Q), H))
+        want = np.zeros_like(ref)
+        want[rows] = ref[rows]
+        assert np.array_equal(got, want)
+
+
+def test_noalloc_keeps_fitting(qp):
+    """256 queries on an unaligned database: the split product's partials
+    (over 80 MB) do not fit the fixed scratch, the whole product does."""
+    import torch
+    banner("noalloc 20000x1007 B=256")
+    R, C, B = 20000, 1007, 256
+    g = np.random.default_rng(8)
+    D = workload.db_bytes(g, R, C)
+    Q = workload.uniform_u32(g, (C, B))
+    with qp.Database(to_dev_u8(D)) as db:
+        out = torch.empty((R, B), dtype=torch.int32, device="cuda")
+        got = to_host_u32(db.answer_batch_noalloc(to_dev_u32(Q), out))
+        assert np.array_equal(got, to_host_u32(db.answer_batch(to_dev_u32(Q))))
+    assert np.array_equal(got[::997], oracle.answer_batch(D[::997], Q))
