@@ -58,6 +58,8 @@
 // 4 KiB tiles of 32 rows x 128 bytes (tile (n/32, k/128) at
 // ((n/32) * Cp/128 + k/128) * 4096, row n%32 at 128 (n%32) within it): the
 // ingest writes whole tiles and a 1 KiB block of a GEMM k-tile is contiguous.
+#include <type_traits>
+
 #include "qpir_internal.h"
 
 namespace {
@@ -82,6 +84,8 @@ enum : int {
     kPart32 = 1,      // split partial sum_k 2^(8k) P_k mod 2^32 (no centring terms)
     kFinalModP = 2,   // Out mod p
     kPart64 = 3,      // split partial sum_k 2^(8k) P_k, exact (mod 2^64)
+    kClientQuery = 4,    // kFinal32, then the client's query epilogue
+    kClientDecode = 5,   // kFinal32, then the client's decode
 };
 
 __global__ void k_zero_words(uint32_t* __restrict__ p, uint32_t n) {
@@ -222,11 +226,14 @@ struct Epi {
     uint32_t B, R, C;
     const uint32_t* rows;       // database row of output row i, or null
     const u64* colsum;          // exact column sums, B words
-    const uint32_t* rowsum;     // exact row sums (handle metadata)
+    const uint32_t* rowsum;     // row metadata: exact row sums, or row terms (see row_scale)
+    uint32_t row_scale;         // factor of rowsum mod 2^32
     uint32_t* out;
     uint64_t o_ldr, o_ldb;
-    void* part;                 // split-K partials [split][M][B]
+    void* part;                 // split-K partials [split][M][B], or [split][B][M] with by_rows
     uint32_t p;                 // modulus of the field form
+    bool by_rows;               // answers contiguous along rows: four rows per 16-byte access
+    ClientEpi client;           // client modes
 };
 
 __device__ inline uint32_t colterm32(const Epi& e, uint32_t b) {
@@ -252,7 +259,7 @@ __device__ inline void epi_put(const Epi& e, uint32_t split, uint32_t i, uint32_
         if (r >= e.R) return;
         uint32_t* dst = e.out + (uint64_t)r * e.o_ldr + (uint64_t)b * e.o_ldb;
         if (MODE == kFinal32)
-            *dst = (uint32_t)x + colterm32(e, b) + kCentreWord * e.rowsum[r];
+            *dst = (uint32_t)x + colterm32(e, b) + e.row_scale * e.rowsum[r];
         else
             *dst = (uint32_t)((x + colterm64(e, b) + (u64)kCentreWord * e.rowsum[r]) % e.p);
     } else {
@@ -264,36 +271,81 @@ __device__ inline void epi_put(const Epi& e, uint32_t split, uint32_t i, uint32_
     }
 }
 
-// Limb combination of four limb products (wide layout).
-template <int MODE, bool GATHER>
-__device__ inline void epi_store(const Epi& e, uint32_t split, uint32_t i, uint32_t b, int32_t p0,
-                                 int32_t p1, int32_t p2, int32_t p3) {
-    if (MODE == kFinal32 || MODE == kPart32)
-        epi_put<MODE, GATHER>(e, split, i, b,
-                              (uint32_t)p0 + ((uint32_t)p1 << 8) + ((uint32_t)p2 << 16) +
-                                  ((uint32_t)p3 << 24));
+// Answers of query b at rows i .. i+3 (i % 4 == 0, e.M % 4 == 0), finished
+// and stored; kClientQuery and kClientDecode add the client step's epilogue.
+template <int MODE>
+__device__ inline void rows4_store(const Epi& e, uint32_t i, uint32_t b, u32x4 x) {
+    x += colterm32(e, b) + e.row_scale * *reinterpret_cast<const u32x4*>(e.rowsum + i);
+    const uint64_t at = (uint64_t)b * e.o_ldb + i;
+    if (MODE == kClientQuery) {
+        x += *reinterpret_cast<const u32x4*>(e.client.add + at);
+        const uint32_t d = e.client.cols[b] - i;      // the queried column, if among the four
+        x.x += d == 0u ? kClientDelta : 0u;
+        x.y += d == 1u ? kClientDelta : 0u;
+        x.z += d == 2u ? kClientDelta : 0u;
+        x.w += d == 3u ? kClientDelta : 0u;
+    }
+    if (MODE == kClientDecode) {
+        const u32x4 y = *reinterpret_cast<const u32x4*>(e.client.add + at) - x + kClientDelta / 2u;
+        *reinterpret_cast<uint32_t*>(e.client.bytes + at) =
+            (y.x >> 24) | ((y.y >> 24) << 8) | ((y.z >> 24) << 16) | (y.w & 0xFF000000u);
+    } else {
+        *reinterpret_cast<u32x4*>(e.out + at) = x;
+    }
+}
+
+template <int MODE>
+__device__ inline void epi_put_rows4(const Epi& e, uint32_t split, uint32_t i, uint32_t b,
+                                     u32x4 x) {
+    if (i >= e.M || b >= e.B) return;
+    if (MODE == kPart32)
+        *reinterpret_cast<u32x4*>(static_cast<uint32_t*>(e.part) +
+                                  ((uint64_t)split * e.B + b) * e.M + i) = x;
     else
-        epi_put<MODE, GATHER>(e, split, i, b,
-                              limb64(p0) + (limb64(p1) << 8) + (limb64(p2) << 16) +
-                                  (limb64(p3) << 24));
+        rows4_store<MODE>(e, i, b, x);
+}
+
+template <int MODE>
+constexpr bool rows4_mode() {
+    return MODE == kFinal32 || MODE == kPart32 || MODE == kClientQuery || MODE == kClientDecode;
 }
 
 // Write a wave's accumulators through the epilogue: the four limb tiles of
 // query group g sit in acc[a][4g .. 4g+3] (C layout of the 32x32 MFMA: lane
-// holds column lane % 32, register v holds row 8 (v/4) + 4 (lane/32) + v%4).
+// holds column lane % 32, register v holds row 8 (v/4) + 4 (lane/32) + v%4,
+// so four consecutive registers are four consecutive rows).
 template <int MODE, bool GATHER, int TM, int TN>
 __device__ inline void epi_wave(const Epi& e, uint32_t split, const i32x16 (&acc)[TM][TN],
                                 uint32_t m_base, uint32_t n_base, int lane) {
+    constexpr bool kMod32 = rows4_mode<MODE>();
 #pragma unroll
     for (int g = 0; g < TN / 4; ++g) {
         const uint32_t bq = n_base / 4u + 32u * g + (uint32_t)(lane & 31);
 #pragma unroll
         for (int a = 0; a < TM; ++a) {
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const uint32_t i = m_base + a * 32 + 8 * (v / 4) + 4 * (lane >> 5) + (v % 4);
-                epi_store<MODE, GATHER>(e, split, i, bq, acc[a][4 * g][v], acc[a][4 * g + 1][v],
-                                        acc[a][4 * g + 2][v], acc[a][4 * g + 3][v]);
+            for (int v4 = 0; v4 < 4; ++v4) {
+                const uint32_t i = m_base + a * 32 + 8 * v4 + 4 * (lane >> 5);
+                u64 x[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const int v = 4 * v4 + j;
+                    const int32_t p0 = acc[a][4 * g][v], p1 = acc[a][4 * g + 1][v],
+                                  p2 = acc[a][4 * g + 2][v], p3 = acc[a][4 * g + 3][v];
+                    x[j] = kMod32 ? (u64)((uint32_t)p0 + ((uint32_t)p1 << 8) +
+                                          ((uint32_t)p2 << 16) + ((uint32_t)p3 << 24))
+                                  : limb64(p0) + (limb64(p1) << 8) + (limb64(p2) << 16) +
+                                        (limb64(p3) << 24);
+                }
+                const u32x4 x4 = {(uint32_t)x[0], (uint32_t)x[1], (uint32_t)x[2], (uint32_t)x[3]};
+                if constexpr (MODE == kClientQuery || MODE == kClientDecode) {
+                    epi_put_rows4<MODE>(e, split, i, bq, x4);
+                } else if (kMod32 && !GATHER && e.by_rows) {
+                    epi_put_rows4<MODE>(e, split, i, bq, x4);
+                } else {
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) epi_put<MODE, GATHER>(e, split, i + j, bq, x[j]);
+                }
             }
         }
     }
@@ -302,33 +354,46 @@ __device__ inline void epi_wave(const Epi& e, uint32_t split, const i32x16 (&acc
 // Narrow layout: in 32-column tile t of a wave, lane column c holds limb
 // c / 8 of query n_base / 4 + 8 t + c % 8 (C layout as above).  The four
 // limbs of a query sit in lanes c, c ^ 8, c ^ 16, c ^ 24 of the same half
-// wave; two xor shuffles add the shifted products and lanes with c < 8
-// store.
+// wave; two xor shuffles add the shifted products.  Then the lanes with c < 8
+// store, or, along rows, the lanes of limb l store the four rows of register
+// group l.
 template <int MODE, bool GATHER, int TM, int TN>
 __device__ inline void epi_wave_narrow(const Epi& e, uint32_t split, const i32x16 (&acc)[TM][TN],
                                        uint32_t m_base, uint32_t n_base, int lane) {
     const int c = lane & 31;
     const int limb = c >> 3;
+    constexpr bool kMod32 = rows4_mode<MODE>();
 #pragma unroll
     for (int t = 0; t < TN; ++t) {
         const uint32_t bq = n_base / 4u + 8u * t + (uint32_t)(c & 7);
 #pragma unroll
         for (int a = 0; a < TM; ++a) {
+            const uint32_t i0 = m_base + a * 32 + 4 * (lane >> 5);
+            if constexpr (kMod32) {
+                u32x4 x4[4];
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const uint32_t i = m_base + a * 32 + 8 * (v / 4) + 4 * (lane >> 5) + (v % 4);
-                u64 x;
-                if (MODE == kFinal32 || MODE == kPart32) {
+                for (int v = 0; v < 16; ++v) {
                     uint32_t y = (uint32_t)acc[a][t][v] << (8 * limb);
                     y += __shfl_xor(y, 8);
                     y += __shfl_xor(y, 16);
-                    x = y;
-                } else {
-                    x = limb64(acc[a][t][v]) << (8 * limb);
+                    x4[v / 4][v % 4] = y;
+                }
+                if (!GATHER && e.by_rows) {
+                    const u32x4 mine = limb == 0 ? x4[0] : (limb == 1 ? x4[1] : (limb == 2 ? x4[2] : x4[3]));
+                    epi_put_rows4<MODE>(e, split, i0 + 8 * limb, bq, mine);
+                } else if (limb == 0) {
+#pragma unroll
+                    for (int v = 0; v < 16; ++v)
+                        epi_put<MODE, GATHER>(e, split, i0 + 8 * (v / 4) + v % 4, bq, x4[v / 4][v % 4]);
+                }
+            } else {
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    u64 x = limb64(acc[a][t][v]) << (8 * limb);
                     x += __shfl_xor(x, 8);
                     x += __shfl_xor(x, 16);
+                    if (limb == 0) epi_put<MODE, GATHER>(e, split, i0 + 8 * (v / 4) + v % 4, bq, x);
                 }
-                if (limb == 0) epi_put<MODE, GATHER>(e, split, i, bq, x);
             }
         }
     }
@@ -350,7 +415,7 @@ __global__ __launch_bounds__(256) void k_finish(Epi e, uint32_t splits) {
         for (uint32_t s = 0; s < splits; ++s) v += part[s * plane];
         *dst = (uint32_t)(v % e.p);
     } else {
-        uint32_t v = colterm32(e, b) + kCentreWord * e.rowsum[r];
+        uint32_t v = colterm32(e, b) + e.row_scale * e.rowsum[r];
         const uint32_t* part = static_cast<const uint32_t*>(e.part) + idx;
         for (uint32_t s = 0; s < splits; ++s) v += part[s * plane];
         *dst = v;
@@ -369,12 +434,26 @@ __global__ __launch_bounds__(256) void k_finish4(Epi e, uint32_t splits) {
     const uint32_t r = e.rows ? e.rows[i] : i;
     if (r >= e.R) return;
     const uint64_t plane4 = (uint64_t)e.M * B4;
-    const uint32_t rs = kCentreWord * e.rowsum[r];
+    const uint32_t rs = e.row_scale * e.rowsum[r];
     u32x4 v = u32x4{colterm32(e, b) + rs, colterm32(e, b + 1) + rs, colterm32(e, b + 2) + rs,
                     colterm32(e, b + 3) + rs};
     const u32x4* part = static_cast<const u32x4*>(e.part) + g;
     for (uint32_t s = 0; s < splits; ++s) v += part[s * plane4];
     *reinterpret_cast<u32x4*>(e.out + (uint64_t)r * e.o_ldr + b) = v;
+}
+
+// The same for answers and partials contiguous along rows (query-major
+// answers, M % 4 == 0): four rows of a query per thread.
+template <int MODE>
+__global__ __launch_bounds__(256) void k_finish_rows(Epi e, uint32_t splits) {
+    const uint64_t g = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const uint32_t M4 = e.M / 4u;
+    if (g >= (uint64_t)M4 * e.B) return;
+    const uint32_t b = (uint32_t)(g / M4), i = 4u * (uint32_t)(g % M4);
+    const u32x4* part = static_cast<const u32x4*>(e.part) + g;
+    u32x4 v = part[0];
+    for (uint32_t s = 1; s < splits; ++s) v += part[(uint64_t)s * M4 * e.B];
+    rows4_store<MODE>(e, i, b, v);
 }
 
 // Workgroups are dealt round-robin to the 8 XCDs; give each XCD a
@@ -693,7 +772,17 @@ struct Ring {
 
 // Workgroup w covers tile tile_of(w) and, with split-K, the k-tiles
 // [split * kts, split * kts + kts) of its piece.
-template <class T, bool GATHER, int MODE, bool NTD>
+// PLANES (the client's products): column block i of e.client.n columns holds
+// byte plane i of a word matrix, and limbs below i are zero in the limb planes
+// there (both by value and as stored), so only the limb tiles from i up are
+// loaded, read and multiplied: 10 of 16 products.  A k-tile counts for the
+// block its first column lies in; what it holds of the next is zero for limb
+// i.  These products are bound by the loads into LDS (about 11 TB/s over the
+// chip); 64 secrets on 32768 x 1024 words, whole query call with its epilogue
+// and the operand kernel: 54 us with every limb and separate epilogues, 41.6
+// with the products left out and the epilogue fused (128 x 128 tile), 35.8
+// with the loads left out too (128 x 256).
+template <class T, bool GATHER, int MODE, bool NTD, bool PLANES = false>
 __global__ __launch_bounds__(T::THREADS) void k_gemm_ring(const uint8_t* __restrict__ D,
                                                           uint64_t pitch,
                                                           const int8_t* __restrict__ QL,
@@ -720,7 +809,6 @@ __global__ __launch_bounds__(T::THREADS) void k_gemm_ring(const uint8_t* __restr
     // i < A_LOADS carry D rows, the rest QL rows.
     const int lrow = lane / T::SEGS;
     const uint8_t* src[T::LOADS];
-    uint32_t seg_off[T::LOADS];
     // Load i of a stage's list: a D load (is_a) and its block index within
     // the D or QL part of the tile.
     auto is_a = [](int i) { return T::DX > 0 ? i >= T::B_LOADS : i < T::A_LOADS; };
@@ -728,13 +816,26 @@ __global__ __launch_bounds__(T::THREADS) void k_gemm_ring(const uint8_t* __restr
         return T::DX > 0 ? (i >= T::B_LOADS ? i - T::B_LOADS : i)
                          : (i < T::A_LOADS ? i : i - T::A_LOADS);
     };
+    // 1 KiB block of the D or QL part of a tile that load i of the list
+    // fills.  PLANES orders the QL loads by limb (a limb's rows are 4 blocks
+    // of every 16), the same number of each for every wave.
+    constexpr int kPerLimb = PLANES ? T::B_LOADS / 4 : 1;
+    static_assert(!PLANES || (T::DX == 0 && T::QX == 0 && T::B_LOADS % 4 == 0),
+                  "whole limbs per wave, one list order");
+    auto block_of = [&](int i) {
+        if (!PLANES || is_a(i)) return wave + T::NW * blk(i);
+        const int j = blk(i);
+        const int idx = wave + T::NW * (j % kPerLimb);
+        constexpr int kBlocks = 32 / T::RPB;     // blocks of one limb of 32 queries
+        return idx / kBlocks * 4 * kBlocks + j / kPerLimb * kBlocks + idx % kBlocks;
+    };
+    // A wave's blocks are whole swizzle periods apart (at least 32 rows, or
+    // limbs), so a lane has the same segment in all of them.
+    const uint32_t seg_off = 16u * swz<T::BK>(wave * T::RPB + lrow, lane % T::SEGS);
 #pragma unroll
     for (int i = 0; i < T::LOADS; ++i) {
         const bool a = is_a(i);
-        const int kb = wave + T::NW * blk(i);
-        const int r = kb * T::RPB + lrow;
-        const int seg = swz<T::BK>(r, lane % T::SEGS);
-        seg_off[i] = 16u * seg;
+        const int r = block_of(i) * T::RPB + lrow;
         if (a) {
             uint32_t mi = m0 + r;
             mi = mi < M ? mi : M - 1;
@@ -742,7 +843,7 @@ __global__ __launch_bounds__(T::THREADS) void k_gemm_ring(const uint8_t* __restr
             dr = dr < R ? dr : R - 1;
             src[i] = D + (uint64_t)dr * pitch;
         } else {
-            src[i] = reinterpret_cast<const uint8_t*>(QL) + ql_row(n0 + r, Cp) + seg_off[i];
+            src[i] = reinterpret_cast<const uint8_t*>(QL) + ql_row(n0 + r, Cp) + seg_off;
         }
     }
 
@@ -754,6 +855,7 @@ __global__ __launch_bounds__(T::THREADS) void k_gemm_ring(const uint8_t* __restr
     // * t past the piece's last tile is clamped to it: such a load refills a
     //   slot no later iteration reads.
     const uint32_t t_last = ktiles ? ktiles - 1 : 0;
+    const uint32_t c_last = (C - 1u) & ~15u;
     uint8_t* const ringA = smem;                          // SA D tiles
     uint8_t* const ringB = smem + T::SA * T::A_BYTES;     // SB QL tiles
     // Load i of the list issued at stage u: D tile u + SA - 1 or QL tile
@@ -763,8 +865,8 @@ __global__ __launch_bounds__(T::THREADS) void k_gemm_ring(const uint8_t* __restr
         const uint32_t tt = min(t, t_last);
         const uint32_t k0 = (kt0 + tt) * T::BK;
         uint8_t* dst = (a ? ringA + (t % T::SA) * T::A_BYTES : ringB + (t % T::SB) * T::B_BYTES) +
-                       (wave + T::NW * blk(i)) * 1024;
-        const uint8_t* p = a ? src[i] + min(k0 + seg_off[i], (C - 1u) & ~15u)
+                       block_of(i) * 1024;
+        const uint8_t* p = a ? src[i] + min(k0 + seg_off, c_last)
                              : src[i] + ql_col(k0);   // BK divides 128
         if (NTD && a)   // D read once: non-temporal
             __builtin_amdgcn_global_load_lds((glb_void_t*)p, (lds_void_t*)dst, 16, 0, kCpolNT);
@@ -791,7 +893,7 @@ __global__ __launch_bounds__(T::THREADS) void k_gemm_ring(const uint8_t* __restr
     // Fragments of one k-step of tile u (buffer buf).
     u32x4 fa[2][T::TM];
     i32x4 fb[2][T::TN];
-    auto read_frags = [&](uint32_t u, int ks, int buf) {
+    auto read_frags = [&](uint32_t u, int ks, int buf, int limb0) {
         const uint8_t* sa = ringA + (u % T::SA) * T::A_BYTES;
         const uint8_t* sb = ringB + (u % T::SB) * T::B_BYTES;
         const int seg = 2 * ks + fseg;
@@ -802,6 +904,7 @@ __global__ __launch_bounds__(T::THREADS) void k_gemm_ring(const uint8_t* __restr
         }
 #pragma unroll
         for (int b = 0; b < T::TN; ++b) {
+            if (PLANES && b % 4 < limb0) continue;
             const int r = wn * T::TN * 32 + b * 32 + frow;
             fb[buf][b] = *reinterpret_cast<const i32x4*>(sb + r * T::BK + 16 * swz<T::BK>(r, seg));
         }
@@ -810,15 +913,18 @@ __global__ __launch_bounds__(T::THREADS) void k_gemm_ring(const uint8_t* __restr
     // lo .. hi-1 of stage u's list placed between them, one after each MFMA
     // (VMEM and MFMA scheduling groups); narrow tiles, with more loads than
     // MFMAs, issue the rest after the last MFMA.
-    auto mfma_step = [&](const i32x4 (&ac)[T::TM], int buf, uint32_t u, int lo, int hi) {
-        constexpr int kMfma = T::TM * T::TN;
+    auto mfma_step = [&](const i32x4 (&ac)[T::TM], int buf, uint32_t u, int lo, int hi, auto limb0) {
+        constexpr int kLimb0 = decltype(limb0)::value;
+        constexpr int kMfma = T::TM * T::TN / 4 * (4 - kLimb0);
 #pragma unroll
         for (int a = 0; a < T::TM; ++a)
 #pragma unroll
             for (int b = 0; b < T::TN; ++b)
-                acc[a][b] = __builtin_amdgcn_mfma_i32_32x32x32_i8(ac[a], fb[buf][b], acc[a][b], 0, 0, 0);
+                if (!PLANES || b % 4 >= kLimb0)
+                    acc[a][b] = __builtin_amdgcn_mfma_i32_32x32x32_i8(ac[a], fb[buf][b], acc[a][b], 0, 0, 0);
+        constexpr int kSkip = PLANES ? kLimb0 * kPerLimb : 0;   // QL loads left out
 #pragma unroll
-        for (int i = lo; i < hi; ++i) issue_one(u, i);
+        for (int i = lo; i < hi; ++i) issue_one(u, i < T::A_LOADS ? i : i + kSkip);
         const int paired = hi - lo < kMfma ? hi - lo : kMfma;
 #pragma unroll
         for (int j = 0; j < paired; ++j) {
@@ -831,9 +937,9 @@ __global__ __launch_bounds__(T::THREADS) void k_gemm_ring(const uint8_t* __restr
         for (int j = paired; j < hi - lo; ++j) __builtin_amdgcn_sched_group_barrier(0x010, 1, 0);
         __builtin_amdgcn_sched_barrier(0);
     };
-    // First load of tile t_next issued in k-step j.
-    auto first_load = [](int j) {
-        return j < T::ISSUE_STEPS ? j * T::LOADS / T::ISSUE_STEPS : T::LOADS;
+    // First load of tile t_next issued in k-step j, of `loads`.
+    auto first_load = [](int j, int loads) {
+        return j < T::ISSUE_STEPS ? j * loads / T::ISSUE_STEPS : loads;
     };
 
     // The lists of the stages before the first, in the same order: stage v
@@ -848,7 +954,7 @@ __global__ __launch_bounds__(T::THREADS) void k_gemm_ring(const uint8_t* __restr
             }
     }
 
-    for (uint32_t u = 0; u < ktiles; ++u) {
+    auto stage = [&](uint32_t u, auto limb0) {
         // The loads issued after tile u's (see QL_WAIT) may still be in
         // flight; loads complete in order, so tile u has landed once at most
         // that many of this wave's loads are outstanding.  The barrier then
@@ -856,7 +962,11 @@ __global__ __launch_bounds__(T::THREADS) void k_gemm_ring(const uint8_t* __restr
         // (every wave's reads of it have returned: the last MFMAs of tile
         // u-1 waited for them), which are refilled with D tile u+SA-1 and
         // QL tile u+SB-1 while tile u is consumed.
-        wait_vmcnt<T::QL_WAIT>();
+        // A stage of column block i issues the loads of limbs i and up, which
+        // the tile it loads (of block i or later) reads, and never fewer than
+        // the stages after it: its own count bounds what may be outstanding.
+        constexpr int kLoads = T::LOADS - (PLANES ? decltype(limb0)::value * kPerLimb : 0);
+        wait_vmcnt<PLANES ? (T::STAGES - 2) * kLoads : T::QL_WAIT>();
         ring_barrier();
 
         // Per k-step: centre the A fragments, read the fragments of the next
@@ -865,17 +975,31 @@ __global__ __launch_bounds__(T::THREADS) void k_gemm_ring(const uint8_t* __restr
         // back to back waits on the address unit with no MFMA to run
         // (measured: about 40% of the loop); between MFMAs the waits overlap
         // them.  The scheduling barriers keep this order.
-        read_frags(u, 0, 0);
+        read_frags(u, 0, 0, decltype(limb0)::value);
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
             i32x4 a_c[T::TM];
 #pragma unroll
             for (int a = 0; a < T::TM; ++a) a_c[a] = __builtin_bit_cast(i32x4, fa[ks & 1][a] ^ centre);
             __builtin_amdgcn_sched_barrier(0);
-            if (ks + 1 < KS) read_frags(u, ks + 1, (ks + 1) & 1);
+            if (ks + 1 < KS) read_frags(u, ks + 1, (ks + 1) & 1, decltype(limb0)::value);
             __builtin_amdgcn_sched_barrier(0);
-            mfma_step(a_c, ks & 1, u, first_load(ks), first_load(ks + 1));
+            mfma_step(a_c, ks & 1, u, first_load(ks, kLoads), first_load(ks + 1, kLoads), limb0);
         }
+    };
+    uint32_t u = 0;
+    if constexpr (PLANES) {
+        // First k-tile of this piece past column block i.
+        auto last = [&](uint32_t i) {
+            const uint32_t t = ((i + 1u) * e.client.n + T::BK - 1u) / T::BK;
+            return min(ktiles, t > kt0 ? t - kt0 : 0u);
+        };
+        for (const uint32_t e0 = last(0); u < e0; ++u) stage(u, std::integral_constant<int, 0>{});
+        for (const uint32_t e1 = last(1); u < e1; ++u) stage(u, std::integral_constant<int, 1>{});
+        for (const uint32_t e2 = last(2); u < e2; ++u) stage(u, std::integral_constant<int, 2>{});
+        for (; u < ktiles; ++u) stage(u, std::integral_constant<int, 3>{});
+    } else {
+        for (; u < ktiles; ++u) stage(u, std::integral_constant<int, 0>{});
     }
     // Loads past the last tile may still be landing in LDS.
     wait_vmcnt<0>();
@@ -1092,6 +1216,39 @@ pir_status launch_ring(const Gemm& g, hipStream_t s) {
     return launch_ring_mode<T, false, kFinal32>(g, n_tiles, m_tiles, s);
 }
 
+// The client's products (limb planes with zeroed limbs, see k_gemm_ring).
+// One column tile covers the batch where the tile is wide enough.
+template <class T>
+pir_status launch_client(const Gemm& g, int mode, hipStream_t s) {
+    const uint32_t n_tiles = ceil_div(g.N, T::BN);
+    const uint32_t m_tiles = ceil_div(g.e.M, T::BM);
+    const uint64_t blocks = (uint64_t)n_tiles * m_tiles * g.splits;
+    if (blocks > 0x7FFFFFFFull) return PIR_ERR_SHAPE;
+#define PIR_CLIENT(MODE)                                                                       \
+    k_gemm_ring<T, false, MODE, false, true><<<(uint32_t)blocks, T::THREADS, T::LDS_BYTES, s>>>( \
+        g.db->D, g.db->pitch, g.QL, g.Cp, n_tiles, m_tiles, g.kts, g.e)
+    if (mode == kPart32) PIR_CLIENT(kPart32);
+    else if (mode == kClientQuery) PIR_CLIENT(kClientQuery);
+    else PIR_CLIENT(kClientDecode);
+#undef PIR_CLIENT
+    PIR_LAUNCH_CHECK();
+    return PIR_OK;
+}
+
+template <class T>
+pir_status set_client_lds() {
+    const void* fns[] = {
+        (const void*)k_gemm_ring<T, false, kPart32, false, true>,
+        (const void*)k_gemm_ring<T, false, kClientQuery, false, true>,
+        (const void*)k_gemm_ring<T, false, kClientDecode, false, true>,
+    };
+    for (const void* f : fns)
+        if (hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, T::LDS_BYTES) !=
+            hipSuccess)
+            return PIR_ERR_DEVICE;
+    return PIR_OK;
+}
+
 template <class T>
 pir_status set_ring_lds() {
     const void* fns[] = {
@@ -1225,6 +1382,7 @@ struct VariantInfo {
     pir_status (*launch)(const Gemm&, hipStream_t);
     uint32_t per_cu;        // workgroups resident per CU (LDS-limited ring variants)
     bool narrow;            // narrow QL layout: all queries in one column tile
+    pir_status (*client)(const Gemm&, int mode, hipStream_t);   // client's products, or null
 };
 
 constexpr VariantInfo kVariants[] = {
@@ -1232,16 +1390,19 @@ constexpr VariantInfo kVariants[] = {
     {"ring_128x128_s8", kRing, 128, 128, 64, launch_ring<Ring128x128S8>},
     {"ring_128x128_k128_s4", kRing, 128, 128, 128, launch_ring<Ring128x128K128S4>},
     {"ring_128x256_s6", kRing, 128, 256, 64, launch_ring<Ring128x256S6>},
-    {"ring8w_128x256_k128_s3", kRing, 128, 256, 128, launch_ring<Ring8w128x256K128S3>},
+    {"ring8w_128x256_k128_s3", kRing, 128, 256, 128, launch_ring<Ring8w128x256K128S3>, 1, false,
+     launch_client<Ring8w128x256K128S3>},
     {"ring8w_256x256_s4", kRing, 256, 256, 64, launch_ring<Ring8w256x256S4>},
-    {"ring8w_256x256_k128_s2", kRing, 256, 256, 128, launch_ring<Ring8w256x256K128S2>},
+    {"ring8w_256x256_k128_s2", kRing, 256, 256, 128, launch_ring<Ring8w256x256K128S2>, 1, false,
+     launch_client<Ring8w256x256K128S2>},
     {"ring_256x256_k128_s2", kRing, 256, 256, 128, launch_ring<Ring256x256K128S2>},
     {"roles_256x256_a5b4", kRoles, 256, 256, 64, launch_roles<Roles256x256A5B4>},
     {"roles_128x256_a10b4", kRoles, 128, 256, 64, launch_roles<Roles128x256A10B4>},
     {"reg_128x256", kReg, 128, 256, 128, launch_reg<Reg128x256>},
     {"reg_128x128", kReg, 128, 128, 128, launch_reg<Reg128x128>, 2},
     {"few", kFew, 0, 0, 0, nullptr},   // dot4 stream, batches of at most kFewMax
-    {"ring_128x128_k128_s2", kRing, 128, 128, 128, launch_ring<Ring128x128K128S2>, 2},
+    {"ring_128x128_k128_s2", kRing, 128, 128, 128, launch_ring<Ring128x128K128S2>, 2, false,
+     launch_client<Ring128x128K128S2>},
     {"narrow_256x32_k128_s4", kRing, 256, 32, 128, launch_ring<Narrow256x32K128S4>, 1, true},
     {"narrow_256x64_k128_s4", kRing, 256, 64, 128, launch_ring<Narrow256x64K128S4>, 1, true},
     {"narrow_128x32_k128_s6", kRing, 128, 32, 128, launch_ring<Narrow128x32K128S6>, 1, true},
@@ -1469,6 +1630,9 @@ pir_status mfma_init() {
     if ((st = set_ring_lds<Narrow128x32K128D8>()) != PIR_OK) return st;
     if ((st = set_ring_lds<Ring256x256K128D3>()) != PIR_OK) return st;
     if ((st = set_ring_lds<Ring256x256K128Q3>()) != PIR_OK) return st;
+    if ((st = set_client_lds<Ring128x128K128S2>()) != PIR_OK) return st;
+    if ((st = set_client_lds<Ring8w128x256K128S3>()) != PIR_OK) return st;
+    if ((st = set_client_lds<Ring8w256x256K128S2>()) != PIR_OK) return st;
     if ((st = set_reg_lds<Reg128x256>()) != PIR_OK) return st;
     if ((st = set_reg_lds<Reg128x128>()) != PIR_OK) return st;
     if ((st = set_reg_lds<Reg256x256>()) != PIR_OK) return st;
@@ -1582,12 +1746,20 @@ static pir_status ingest(const pir_db_t* db, const BatchIO& io, uint32_t B, cons
     return PIR_OK;
 }
 
+// Answers contiguous along rows, in whole aligned groups of four: 16-byte
+// stores along rows instead of one word per lane and row (128 queries' worth
+// of lines per store instruction).
+static bool mfma_by_rows(const BatchIO& io, const BatchPlan& P, const uint32_t* rows, bool exact) {
+    return !exact && !rows && P.M % 4 == 0 && io.o_ldr == 1 && io.o_ldb % 4 == 0 &&
+           (uintptr_t)io.out % 16 == 0;
+}
+
 // Enqueue a planned batched call; `ws` holds at least plan.need bytes.  With
 // `planes` (the wide-layout limb planes and column sums of these queries,
 // written by mfma_ingest_planes) the ingest is skipped.
 pir_status mfma_run_batch(const pir_db_t* db, const BatchIO& io, uint32_t B,
                           const uint32_t* rows, uint32_t modulus, const BatchPlan& P, void* ws,
-                          const void* planes, hipStream_t s) {
+                          const void* planes, const ClientEpi* client, hipStream_t s) {
     if (P.few) return few_answer_batch(db, io, B, modulus, ws, P.need, s);
     const uint32_t C = (uint32_t)db->cols;
     const bool exact = modulus != 0;
@@ -1610,22 +1782,42 @@ pir_status mfma_run_batch(const pir_db_t* db, const BatchIO& io, uint32_t B,
     g.exact = exact;
     g.splits = P.splits;
     g.kts = P.kts;
-    g.e = Epi{P.M,      B,        (uint32_t)db->rows, C, rows, colsum, db->rowsum, io.out,
-              io.o_ldr, io.o_ldb, base + P.part_off, modulus};
-    pir_status st = vi.launch(g, s);
-    if (st != PIR_OK || P.splits <= 1) return st;
+    g.e = Epi{P.M,       B,        (uint32_t)db->rows,   C,       rows,  colsum, db->rowterm,
+              db->row_scale, io.out, io.o_ldr, io.o_ldb, base + P.part_off, modulus,
+              mfma_by_rows(io, P, rows, exact), client ? *client : ClientEpi{}};
     const uint64_t n = (uint64_t)P.M * B;
+    if (client) {
+        const int mode = client->bytes ? kClientDecode : kClientQuery;
+        const pir_status st = vi.client(g, P.splits > 1 ? kPart32 : mode, s);
+        if (st != PIR_OK || P.splits <= 1) return st;
+        if (mode == kClientDecode)
+            k_finish_rows<kClientDecode><<<(uint32_t)((n / 4 + 255) / 256), 256, 0, s>>>(g.e, P.splits);
+        else
+            k_finish_rows<kClientQuery><<<(uint32_t)((n / 4 + 255) / 256), 256, 0, s>>>(g.e, P.splits);
+        PIR_LAUNCH_CHECK();
+        return PIR_OK;
+    }
+    const pir_status st = vi.launch(g, s);
+    if (st != PIR_OK || P.splits <= 1) return st;
     if (n == 0) return PIR_OK;
     const bool vec4 = !exact && B % 4 == 0 && io.o_ldb == 1 && io.o_ldr % 4 == 0 &&
                       (uintptr_t)io.out % 16 == 0;
     if (exact)
         k_finish<true><<<(uint32_t)((n + 255) / 256), 256, 0, s>>>(g.e, P.splits);
+    else if (g.e.by_rows)
+        k_finish_rows<kFinal32><<<(uint32_t)((n / 4 + 255) / 256), 256, 0, s>>>(g.e, P.splits);
     else if (vec4)
         k_finish4<<<(uint32_t)((n / 4 + 255) / 256), 256, 0, s>>>(g.e, P.splits);
     else
         k_finish<false><<<(uint32_t)((n + 255) / 256), 256, 0, s>>>(g.e, P.splits);
     PIR_LAUNCH_CHECK();
     return PIR_OK;
+}
+
+// Whether a planned product can end in the client's epilogue.
+bool mfma_client_fused(const BatchPlan& P, const BatchIO& io, const ClientEpi& client) {
+    return kVariants[P.variant].client && mfma_by_rows(io, P, nullptr, false) &&
+           (uintptr_t)client.add % 16 == 0 && (uintptr_t)client.bytes % 4 == 0;
 }
 
 pir_status mfma_answer_batch(const pir_db_t* db, const BatchIO& io, uint32_t B,
@@ -1640,7 +1832,7 @@ pir_status mfma_answer_batch(const pir_db_t* db, const BatchIO& io, uint32_t B,
         return PIR_ERR_WORKSPACE;
     if (planes && (planes_bytes < mfma_planes_bytes(db, B) || ((uintptr_t)planes % kWsAlign)))
         return PIR_ERR_WORKSPACE;
-    return mfma_run_batch(db, io, B, rows, modulus, plan, ws, planes, s);
+    return mfma_run_batch(db, io, B, rows, modulus, plan, ws, planes, nullptr, s);
 }
 
 size_t mfma_planes_bytes(const pir_db_t* db, uint32_t n) {

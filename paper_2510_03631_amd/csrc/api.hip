@@ -73,6 +73,8 @@ pir_status pir_db_open(uint8_t* d_D, uint64_t rows, uint64_t cols, uint64_t row_
         delete db;
         return PIR_ERR_NO_MEMORY;
     }
+    db->rowterm = db->rowsum;
+    db->row_scale = 0x80808080u;
     db->magic = kDbMagic;
     hipStream_t s = static_cast<hipStream_t>(stream);
     pir_status st = launch_rowsum(db, s);

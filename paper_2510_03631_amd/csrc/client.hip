@@ -26,7 +26,7 @@ namespace {
 
 constexpr int kCWaves = 4;
 constexpr int kBChunk = 16;     // secrets per pass over a row
-constexpr uint32_t kDelta = 1u << 24;
+constexpr uint32_t kDelta = kClientDelta;
 constexpr uint32_t kHalfDelta = 1u << 23;
 
 enum Epilogue { kQuery = 0, kDecode = 1 };
@@ -154,67 +154,128 @@ uint32_t grid_for(uint32_t rows, int rb) {
 // M_i, so M x = [M_0 | M_1 | M_2 | M_3] [x; 2^8 x; 2^16 x; 2^24 x]: a byte
 // matrix of 4n columns times a word vector of 4n entries, which is exactly
 // the Answer product D q.  A prepared client matrix holds the byte planes
-// (rows x 4n bytes, the same size as M) under a database handle, and a batch
+// (rows x 4n bytes, rows padded to 16) under a database handle, and a batch
 // of secrets runs on the matrix-core batched Answer, followed by the query
 // or decode epilogue.
+//
+// Limb L of 2^(8i) x is byte L - i of x, and zero for L < i.  The product
+// skips those limbs (10 of 16 byte products are left): they are stored as
+// the padding is, zero after centring, and the centring terms leave them
+// out.  With S_L the columns of planes i <= L, the sum over L of
+// 2^(8L) times
+//
+//   sum_(S_L) D q_L = P_L + 128 (sum_(S_L) q_L - 128 |S_L|) + 128 sum_(S_L) D
+//
+// gives the row term 128 sum_L 2^(8L) sum_(i <= L) (row sum of plane i),
+// kept with the planes, and a column term from sum_k x_k.
 
 constexpr uint32_t kClientMatMagic = 0x434D4154u;   // "CMAT"
 
-// planes[r][i n + k] = byte i of M[r][k]; one thread per word.
-__global__ void k_byte_planes(const uint32_t* __restrict__ M, uint64_t words, uint32_t n,
-                              uint8_t* __restrict__ planes) {
-    const uint64_t idx = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= words) return;
-    const uint64_t r = idx / n, k = idx % n;
-    const uint32_t w = M[idx];
-    uint8_t* row = planes + r * 4u * n;
+// One wave per row: planes[r][i n + k] = byte i of M[r][k], and the row
+// term.  A lane takes four words and writes a word of each plane (n % 4 == 0;
+// else single bytes).  128 MiB: 90 us with a byte store per plane and word,
+// 46 us now.
+__global__ __launch_bounds__(256) void k_byte_planes(const uint32_t* __restrict__ M, uint32_t rows,
+                                                     uint32_t n, uint64_t pitch,
+                                                     uint8_t* __restrict__ planes,
+                                                     uint32_t* __restrict__ rowterm) {
+    const uint32_t lane = threadIdx.x & 63;
+    const uint32_t waves = gridDim.x * (blockDim.x >> 6);
+    for (uint32_t r = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6); r < rows; r += waves) {
+        const uint32_t* src = M + (uint64_t)r * n;
+        uint8_t* dst = planes + r * pitch;
+        uint32_t sum[4] = {0, 0, 0, 0};
+        if (n % 4u == 0u) {
+            for (uint32_t k = 4u * lane; k < n; k += 256u) {
+                const uint32_t w0 = src[k], w1 = src[k + 1], w2 = src[k + 2], w3 = src[k + 3];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) row[(uint64_t)i * n + k] = (uint8_t)(w >> (8 * i));
+                for (int i = 0; i < 4; ++i) {
+                    const uint32_t b = ((w0 >> (8 * i)) & 0xFFu) | (((w1 >> (8 * i)) & 0xFFu) << 8) |
+                                       (((w2 >> (8 * i)) & 0xFFu) << 16) | ((w3 >> (8 * i)) << 24);
+                    *reinterpret_cast<uint32_t*>(dst + (uint64_t)i * n + k) = b;
+                    sum[i] = __builtin_amdgcn_udot4(b, 0x01010101u, sum[i], false);
+                }
+            }
+        } else {
+            for (uint32_t k = lane; k < n; k += 64u) {
+                const uint32_t w = src[k];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const uint32_t b = (w >> (8 * i)) & 0xFFu;
+                    dst[(uint64_t)i * n + k] = (uint8_t)b;
+                    sum[i] += b;
+                }
+            }
+        }
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) sum[i] += __shfl_xor(sum[i], off);
+        if (lane == 0) {
+            uint32_t term = 0, upto = 0;
+#pragma unroll
+            for (int L = 0; L < 4; ++L) {
+                upto += sum[L];
+                term += upto << (8 * L);
+            }
+            rowterm[r] = 128u * term;
+        }
+    }
 }
 
-// The batched Answer's operand for the secrets against the planes,
-// xs_b = [x_b; 2^8 x_b; 2^16 x_b; 2^24 x_b] (mod 2^32, 4n words), written
-// straight in its wide limb layout: block b writes the four limb rows of
-// query b over all Cp columns (zero past 4n, all zero for the padding
-// queries b >= B) and the exact sum of xs_b, so no clearing pass and no
+// The batched Answer's operand for the secrets against the planes, in its
+// wide limb layout: block b writes the four limb rows of query b over all Cp
+// columns (zero past 4n, in the planes above a limb, and for the padding
+// queries b >= B) and the column term's sum, so no clearing pass and no
 // atomics are needed.
-__global__ __launch_bounds__(256) void k_client_planes(const uint32_t* __restrict__ X,
-                                                       uint32_t B, uint32_t n, uint32_t Cp,
-                                                       int8_t* __restrict__ QL,
-                                                       uint64_t* __restrict__ colsum) {
-    __shared__ uint64_t s_sum[256];
+constexpr int kPlaneThreads = 1024;
+
+__global__ __launch_bounds__(kPlaneThreads) void k_client_planes(const uint32_t* __restrict__ X,
+                                                                 uint32_t B, uint32_t n,
+                                                                 uint32_t Cp,
+                                                                 int8_t* __restrict__ QL,
+                                                                 uint64_t* __restrict__ colsum) {
+    __shared__ uint32_t s_sum[kPlaneThreads / 64];
     const uint32_t b = blockIdx.x;
     const bool live = b < B;
     const uint32_t K = 4u * n;
     const uint32_t nrow = (b / 32u) * 128u + b % 32u;   // limb 0 row; limb L adds 32 L
-    uint64_t sum = 0;
-    for (uint32_t k = 4u * threadIdx.x; k < Cp; k += 4u * blockDim.x) {
+    const uint32_t* x = X + (uint64_t)b * n;
+    uint32_t sum = 0;
+    for (uint32_t j0 = 4u * threadIdx.x; j0 < Cp; j0 += 4u * kPlaneThreads) {
         uint32_t word[4] = {0u, 0u, 0u, 0u};
+        if (live && j0 < K) {
+            uint32_t i = j0 / n, k = j0 - i * n;
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            const uint32_t j = k + (uint32_t)c;
-            uint32_t w = 0;
-            if (live && j < K) {
-                w = X[(uint64_t)b * n + j % n] << (8u * (j / n));
-                sum += w;
-            }
+            for (int c = 0; c < 4; ++c) {
+                if (k == n) {
+                    k = 0;
+                    ++i;
+                }
+                if (i < 4u) {
+                    const uint32_t w = x[k++];
+                    if (i == 0) sum += w;
 #pragma unroll
-            for (int L = 0; L < 4; ++L) {
-                const uint32_t byte = (live && j < K) ? (((w >> (8 * L)) & 0xFFu) ^ 0x80u) : 0u;
-                word[L] |= byte << (8 * c);
+                    for (uint32_t L = 0; L < 4u; ++L)
+                        if (L >= i) word[L] |= (((w >> (8u * (L - i))) & 0xFFu) ^ 0x80u) << (8 * c);
+                }
             }
         }
 #pragma unroll
         for (int L = 0; L < 4; ++L)
-            *reinterpret_cast<uint32_t*>(QL + ql_row(nrow + 32u * L, Cp) + ql_col(k)) = word[L];
+            *reinterpret_cast<uint32_t*>(QL + ql_row(nrow + 32u * L, Cp) + ql_col(j0)) = word[L];
     }
-    s_sum[threadIdx.x] = sum;
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) sum += __shfl_xor(sum, off);
+    if ((threadIdx.x & 63) == 0) s_sum[threadIdx.x >> 6] = sum;
     __syncthreads();
-    for (uint32_t h = blockDim.x / 2; h > 0; h >>= 1) {
-        if (threadIdx.x < h) s_sum[threadIdx.x] += s_sum[threadIdx.x + h];
-        __syncthreads();
+    if (threadIdx.x == 0) {
+        uint32_t t = 0;
+        for (int w = 0; w < kPlaneThreads / 64; ++w) t += s_sum[w];
+        // sum over L of 2^(8L) (sum_(S_L) q_L - 128 n (L + 1)), in the form
+        // whose column term subtracts 4n * 0x80808080 again.
+        colsum[b] = live ? t * 0x01010101u - 128u * n * 0x04030201u + K * 0x80808080u : 0u;
     }
-    if (threadIdx.x == 0) colsum[b] = live ? s_sum[0] : 0u;
 }
 
 // Query epilogue, in place on the product: Qt[b][j] += E[b][j] (+ Delta at
@@ -247,7 +308,8 @@ struct pir_client_mat {
     uint32_t magic;
     uint32_t rows, n;
     int device;
-    uint8_t* planes;   // rows x 4n bytes, owned
+    uint8_t* planes;   // rows of 4n bytes padded to 16, owned
+    uint32_t* rowterm; // rows words, owned (the tail of the planes' allocation)
     pir_db_t* db;      // handle over the planes
 };
 
@@ -270,17 +332,22 @@ MatWs mat_ws(const pir_client_mat_t* m, uint32_t B, bool decode) {
     return w;
 }
 
-// Y[b] = M X[b] for the B secrets into y (B x rows words); `plan` made with
-// pre-ingested planes.
-pir_status mat_product(pir_client_mat_t* m, const uint32_t* X, uint32_t B, uint32_t* y,
-                       uint8_t* ws, const MatWs& w, const BatchPlan& plan, hipStream_t st) {
+// Y[b] = M X[b] for the B secrets into y (B x rows words), or, fused, the
+// client's epilogue on it; `plan` made with pre-ingested planes.
+pir_status mat_product(pir_client_mat_t* m, const uint32_t* X, uint32_t B, const BatchIO& io,
+                       uint8_t* ws, const MatWs& w, const BatchPlan& plan, const ClientEpi* fused,
+                       hipStream_t st) {
     uint8_t* planes = ws + w.planes_off;
-    k_client_planes<<<plan.Bp, 256, 0, st>>>(X, B, m->n, plan.Cp,
-                                             reinterpret_cast<int8_t*>(planes),
-                                             reinterpret_cast<uint64_t*>(planes + plan.colsum_off));
+    k_client_planes<<<plan.Bp, kPlaneThreads, 0, st>>>(
+        X, B, m->n, plan.Cp, reinterpret_cast<int8_t*>(planes),
+        reinterpret_cast<uint64_t*>(planes + plan.colsum_off));
     PIR_LAUNCH_CHECK();
-    const BatchIO io{nullptr, 1, 4u * m->n, y, 1, m->rows};   // query-major answers
-    return mfma_run_batch(m->db, io, B, nullptr, 0, plan, ws + w.ans_off, planes, st);
+    return mfma_run_batch(m->db, io, B, nullptr, 0, plan, ws + w.ans_off, planes, fused, st);
+}
+
+// Query-major answers of m's product at y.
+BatchIO mat_io(const pir_client_mat_t* m, uint32_t* y) {
+    return BatchIO{nullptr, 1, 4u * m->n, y, 1, m->rows};
 }
 
 }  // namespace
@@ -302,30 +369,40 @@ pir_status pir_client_mat_open(const uint32_t* d_M, uint32_t rows, uint32_t n,
         delete m;
         return PIR_ERR_DEVICE;
     }
-    const uint64_t bytes = (uint64_t)rows * 4u * n;
-    if (hipMalloc((void**)&m->planes, bytes) != hipSuccess) {
+    const uint64_t pitch = round_up((size_t)4u * n, 16);
+    const uint64_t bytes = (uint64_t)rows * pitch;
+    if (hipMalloc((void**)&m->planes, bytes + (uint64_t)rows * 4u) != hipSuccess) {
         delete m;
         return PIR_ERR_NO_MEMORY;
     }
+    m->rowterm = reinterpret_cast<uint32_t*>(m->planes + bytes);
     const hipStream_t st = static_cast<hipStream_t>(stream);
-    const uint64_t words = (uint64_t)rows * n;
-    k_byte_planes<<<grid1d(words), 256, 0, st>>>(d_M, words, n, m->planes);
+    k_byte_planes<<<(uint32_t)std::min<uint64_t>(((uint64_t)rows + 3) / 4, 8192), 256, 0, st>>>(
+        d_M, rows, n, pitch, m->planes, m->rowterm);
     pir_status s = hipGetLastError() == hipSuccess ? PIR_OK : PIR_ERR_DEVICE;
-    if (s == PIR_OK) s = pir_db_open(m->planes, rows, 4u * n, 4u * n, stream, &m->db);
+    if (s == PIR_OK) s = pir_db_open(m->planes, rows, 4u * n, pitch, stream, &m->db);
     if (s != PIR_OK) {
         (void)hipStreamSynchronize(st);
         (void)hipFree(m->planes);
         delete m;
         return s;
     }
-    // The product's default tile: a 128 x 128 ring with two 128-byte stages,
-    // two workgroups per CU (the client product has K = 4n, small beside
-    // its rows).  Measured at 32768 x 1024 words, whole query call: 16
-    // secrets 39 us against 44 us with the database default, 64 secrets 54
-    // against 60 us.  pir_client_mat_set_variant overrides it.
+    m->db->rowterm = m->rowterm;
+    m->db->row_scale = 1u;
+    // The product's default tiles, per batch bucket: 128 x 128 with two
+    // workgroups per CU up to 32 secrets, then one column tile of 64 queries,
+    // and the 256 x 256 tile where there are several.  Whole query calls at
+    // 32768 x 1024 words, us (128 x 128, 128 x 256, 256 x 256): 16 secrets
+    // 28.4, -, -; 64 secrets 41.9, 35.8, 42.9; 200 secrets 113, 106, 95.
+    // pir_client_mat_set_variant overrides them.
     for (uint32_t v = 1; v < mfma_variant_count(); ++v) {
-        if (strcmp(mfma_variant_name(v), "ring_128x128_k128_s2") != 0) continue;
-        for (uint32_t b = 8; b <= kMaxBatch; b *= 2) (void)pir_db_set_variant(m->db, b, v);
+        const char* name = mfma_variant_name(v);
+        for (uint32_t b = 1; b <= kMaxBatch; b *= 2) {
+            const char* want = b <= 32 ? "ring_128x128_k128_s2"
+                                       : (b <= 128 ? "ring8w_128x256_k128_s3"
+                                                   : "ring8w_256x256_k128_s2");
+            if (strcmp(name, want) == 0) (void)pir_db_set_variant(m->db, b, v);
+        }
     }
     m->magic = kClientMatMagic;
     *out = m;
@@ -368,8 +445,11 @@ pir_status pir_client_query_mat(pir_client_mat_t* A, const uint32_t* d_S, const 
     BatchPlan plan;   // every check of the product before anything is enqueued
     pir_status s = mfma_plan_batch(A->db, B, nullptr, 0, 0, true, &plan);
     if (s != PIR_OK) return s;
-    s = mat_product(A, d_S, B, d_Qt, static_cast<uint8_t*>(d_ws), w, plan, st);
-    if (s != PIR_OK) return s;
+    const BatchIO io = mat_io(A, d_Qt);
+    const ClientEpi epi{A->n, reinterpret_cast<const uint32_t*>(d_E), d_cols, nullptr};
+    const bool fused = mfma_client_fused(plan, io, epi);
+    s = mat_product(A, d_S, B, io, static_cast<uint8_t*>(d_ws), w, plan, fused ? &epi : nullptr, st);
+    if (s != PIR_OK || fused) return s;
     k_query_epilogue<<<grid1d((uint64_t)B * A->rows), 256, 0, st>>>(d_Qt, A->rows, B, d_E, d_cols);
     PIR_LAUNCH_CHECK();
     return PIR_OK;
@@ -393,8 +473,11 @@ pir_status pir_client_decode_mat(pir_client_mat_t* H, const uint32_t* d_S,
     if (s != PIR_OK) return s;
     uint8_t* ws = static_cast<uint8_t*>(d_ws);
     uint32_t* y = reinterpret_cast<uint32_t*>(ws + w.y_off);
-    s = mat_product(H, d_S, B, y, ws, w, plan, st);
-    if (s != PIR_OK) return s;
+    const BatchIO io = mat_io(H, y);
+    const ClientEpi epi{H->n, d_answers, nullptr, d_out};
+    const bool fused = mfma_client_fused(plan, io, epi);
+    s = mat_product(H, d_S, B, io, ws, w, plan, fused ? &epi : nullptr, st);
+    if (s != PIR_OK || fused) return s;
     const uint64_t count = (uint64_t)B * H->rows;
     k_decode_epilogue<<<grid1d(count), 256, 0, st>>>(y, d_answers, count, d_out);
     PIR_LAUNCH_CHECK();

@@ -17,6 +17,10 @@ struct pir_db {
     uint8_t* D;            // borrowed database bytes
     uint64_t rows, cols, pitch;
     uint32_t* rowsum;      // device, rows words: sum_j D[r][j]
+    // Row term of the centred product mod 2^32, row_scale * rowterm[r]: the
+    // row sums times 0x80808080, or a client matrix's own (client.hip).
+    const uint32_t* rowterm;
+    uint32_t row_scale;
     int device;
     bool aligned;          // D and pitch are multiples of 16
     uint8_t variant[kBuckets];        // kernel variant per batch bucket (0 = built-in choice)
@@ -59,6 +63,17 @@ struct BatchIO {
     uint64_t q_ldj, q_ldb;
     uint32_t* out;
     uint64_t o_ldr, o_ldb;
+};
+
+// The client's epilogue on a product y[b][r] with answers of query b
+// contiguous along rows: a query y + add + Delta at row cols[b], or (bytes set)
+// the decode (add - y + Delta / 2) >> 24.  n: columns of a byte plane.
+constexpr uint32_t kClientDelta = 1u << 24;
+struct ClientEpi {
+    uint32_t n;
+    const uint32_t* add;
+    const uint32_t* cols;
+    uint8_t* bytes;
 };
 
 // Limb planes of a batch (the matrix-core path's B operand): row n holds
@@ -118,9 +133,12 @@ pir_status mfma_plan_batch(const pir_db_t* db, uint32_t B, const uint32_t* rows,
 void mfma_plan_fit(const pir_db_t* db, size_t scratch_bytes, BatchPlan* plan);
 // Enqueue a planned call; `ws` must hold plan.need bytes, 256-byte aligned;
 // `planes` (or null) as written by mfma_ingest_planes for these queries.
+// `client` (or null): the client's product and epilogue in one, where
+// mfma_client_fused() allows it.
 pir_status mfma_run_batch(const pir_db_t* db, const BatchIO& io, uint32_t B,
                           const uint32_t* rows, uint32_t modulus, const BatchPlan& plan, void* ws,
-                          const void* planes, hipStream_t s);
+                          const void* planes, const ClientEpi* client, hipStream_t s);
+bool mfma_client_fused(const BatchPlan& plan, const BatchIO& io, const ClientEpi& client);
 // Plan, check the workspace against mfma_workspace_bytes (and the planes
 // against mfma_planes_bytes), run.
 pir_status mfma_answer_batch(const pir_db_t* db, const BatchIO& io, uint32_t B,
