@@ -505,15 +505,18 @@ uint32_t few_nq(uint32_t B) { return B <= 1 ? 1u : (B <= 2 ? 2u : 4u); }
 
 // Rows per workgroup and column splits.  The limb planes of NQ queries are
 // staged for a workgroup's rows, so it takes 64 (four waves of 16) and splits
-// to three workgroups per CU.  Below 32 MiB that leaves too few, and the
-// second launch of a split costs more than the staging: 16 rows (four waves
-// of 4).  us for one / two queries, 64 and 16 rows: 2048 x 3001 11.6 / 11.6
-// and 7.9 / 9.3; 4096 x 4096 8.5 / 9.8 and 9.0 / 11.3 (one launch, not two);
-// 8192 x 8192 15.8 / 19.7 and 20 / 28; 3072 x 2^18 131 / 155 and 183 / 286.
-uint32_t few_rows(const pir_db_t* db) { return db->rows * db->cols < (1ull << 25) ? 16u : 64u; }
+// to three workgroups per CU.  Below 32 MiB that leaves too few, and for one
+// or two queries the second launch of a split costs more than the staging: 16
+// rows (four waves of 4).  us for one / two / four queries, 64 and 16 rows:
+// 2048 x 3001 11.6 / 11.6 / 16.6 and 7.9 / 9.3 / 12.6; 4096 x 4096 8.5 / 9.8
+// / 13.3 and 9.0 / 11.3 / 17.5 (one launch, not two); 8192 x 8192 15.8 / 19.7
+// / 29.4 and 20 / 28 / 46; 3072 x 2^18 131 / 155 / 248 and 183 / 286 / 472.
+uint32_t few_rows(const pir_db_t* db, uint32_t B) {
+    return B <= 2u && db->rows * db->cols < (1ull << 25) ? 16u : 64u;
+}
 
-SplitPlan few_plan(const pir_db_t* db) {
-    const uint32_t rows = few_rows(db);
+SplitPlan few_plan(const pir_db_t* db, uint32_t B) {
+    const uint32_t rows = few_rows(db, B);
     const uint64_t blocks = row_blocks(db, rows);
     return rows == 16u ? plan_splits(db, 512 / blocks, kSlice) : plan_splits(db, 768 / blocks, kChunk);
 }
@@ -522,7 +525,7 @@ template <int NQ, int RW, int WV, bool EXACT>
 pir_status launch_few_t(const pir_db_t* db, const BatchIO& io, uint32_t B, uint32_t modulus,
                         void* ws, hipStream_t s) {
     constexpr uint32_t kRows = RW * WV;
-    const SplitPlan pl = few_plan(db);
+    const SplitPlan pl = few_plan(db, B);
     const uint32_t R = (uint32_t)db->rows, C = (uint32_t)db->cols;
     dim3 grid((R + kRows - 1) / kRows, pl.splits);
     const FewOut o{io.out, io.o_ldr, io.o_ldb, modulus, pl.splits > 1 ? ws : nullptr};
@@ -540,7 +543,7 @@ pir_status launch_few_t(const pir_db_t* db, const BatchIO& io, uint32_t B, uint3
 template <int NQ, bool EXACT>
 pir_status launch_few(const pir_db_t* db, const BatchIO& io, uint32_t B, uint32_t modulus,
                       void* ws, hipStream_t s) {
-    if (few_rows(db) == 64u) return launch_few_t<NQ, 16, 4, EXACT>(db, io, B, modulus, ws, s);
+    if (few_rows(db, B) == 64u) return launch_few_t<NQ, 16, 4, EXACT>(db, io, B, modulus, ws, s);
     return launch_few_t<NQ, 4, 4, EXACT>(db, io, B, modulus, ws, s);
 }
 
@@ -548,7 +551,7 @@ pir_status launch_few(const pir_db_t* db, const BatchIO& io, uint32_t B, uint32_
 
 size_t few_workspace_bytes(const pir_db_t* db, uint32_t B) {
     if (B == 0 || B > kFewMax) return 0;
-    const SplitPlan pl = few_plan(db);
+    const SplitPlan pl = few_plan(db, B);
     return round_up((size_t)pl.splits * B * db->rows * 8, kWsAlign);
 }
 

@@ -103,8 +103,8 @@ __global__ void k_zero_words(uint32_t* __restrict__ p, uint32_t n) {
 // packs and stores 16-byte chunk l % 8 of row l / 8, so one store covers
 // eight whole rows (1 KiB).  (Storing a thread's whole row as eight 16-byte
 // pieces made every store touch 64 lines: 1.6 TB/s at 128 queries.)  The
-// rows of limb 0 also sum their words: three lane shuffles combine the
-// eight chunks of a row, and one lane adds the exact column sum.
+// rows of limb 0 also sum their words (colsum set): three lane shuffles
+// combine the eight chunks of a row, and one lane adds the exact column sum.
 constexpr int kIngJ = 128;
 constexpr int kIngB = 64;
 
@@ -202,7 +202,7 @@ __global__ __launch_bounds__(256) void k_ingest(const uint32_t* __restrict__ Q, 
             for (int y = 0; y < 4; ++y) {
                 const int jl = 16 * e + 4 * x + y;
                 const uint32_t v = s[bl][jl];
-                if (limb == 0) sum += v;
+                if (limb == 0 && colsum) sum += v;
                 const uint32_t byte =
                     (live && j0 + jl < C) ? (((v >> (8 * limb)) & 0xFFu) ^ 0x80u) : 0u;
                 word |= byte << (8 * y);
@@ -211,7 +211,7 @@ __global__ __launch_bounds__(256) void k_ingest(const uint32_t* __restrict__ Q, 
         }
         *reinterpret_cast<u32x4*>(QL + ql_row(n0 + R, Cp) + ql_col(j0) + 16 * e) =
             u32x4{w[0], w[1], w[2], w[3]};
-        if (limb == 0) {
+        if (limb == 0 && colsum) {
             sum += __shfl_xor(sum, 1);
             sum += __shfl_xor(sum, 2);
             sum += __shfl_xor(sum, 4);
@@ -225,7 +225,7 @@ struct Epi {
     uint32_t M;                 // output rows (gathered rows, or R)
     uint32_t B, R, C;
     const uint32_t* rows;       // database row of output row i, or null
-    const u64* colsum;          // exact column sums, B words
+    const u64* colsum;          // exact column sums, B words, or null (see SUMS)
     const uint32_t* rowsum;     // row metadata: exact row sums, or row terms (see row_scale)
     uint32_t row_scale;         // factor of rowsum mod 2^32
     uint32_t* out;
@@ -236,11 +236,14 @@ struct Epi {
     ClientEpi client;           // client modes
 };
 
+// Column terms; zero where the product added them itself (k_gemm_ring, SUMS).
 __device__ inline uint32_t colterm32(const Epi& e, uint32_t b) {
+    if (!e.colsum) return 0u;
     return 128u * ((uint32_t)e.colsum[b] - e.C * kCentreWord);
 }
 
 __device__ inline u64 colterm64(const Epi& e, uint32_t b) {
+    if (!e.colsum) return 0ull;
     return 128ull * (e.colsum[b] - (u64)e.C * kCentreWord);
 }
 
@@ -249,8 +252,17 @@ __device__ inline u64 limb64(int32_t v) {
     return v == INT32_MIN ? (1ull << 31) : (u64)(int64_t)v;
 }
 
+// What is added to every limb combination of query b before it is stored:
+// its bias, and in the final modes the column term.
+template <int MODE>
+__device__ inline u64 query_term(const Epi& e, uint32_t b, u64 bias) {
+    if (MODE == kPart32 || MODE == kPart64 || b >= e.B) return bias;
+    return bias + (MODE == kFinalModP ? colterm64(e, b) : (u64)colterm32(e, b));
+}
+
 // Output element (local row i, query b) from its limb combination
-// x = sum_k 2^(8k) P_k (exact; only x mod 2^32 matters in the 32-bit modes).
+// x = sum_k 2^(8k) P_k plus the query's term (exact; only x mod 2^32 matters
+// in the 32-bit modes).
 template <int MODE, bool GATHER>
 __device__ inline void epi_put(const Epi& e, uint32_t split, uint32_t i, uint32_t b, u64 x) {
     if (i >= e.M || b >= e.B) return;
@@ -259,9 +271,9 @@ __device__ inline void epi_put(const Epi& e, uint32_t split, uint32_t i, uint32_
         if (r >= e.R) return;
         uint32_t* dst = e.out + (uint64_t)r * e.o_ldr + (uint64_t)b * e.o_ldb;
         if (MODE == kFinal32)
-            *dst = (uint32_t)x + colterm32(e, b) + e.row_scale * e.rowsum[r];
+            *dst = (uint32_t)x + e.row_scale * e.rowsum[r];
         else
-            *dst = (uint32_t)((x + colterm64(e, b) + (u64)kCentreWord * e.rowsum[r]) % e.p);
+            *dst = (uint32_t)((x + (u64)kCentreWord * e.rowsum[r]) % e.p);
     } else {
         const uint64_t at = ((uint64_t)split * e.M + i) * e.B + b;
         if (MODE == kPart32)
@@ -271,11 +283,11 @@ __device__ inline void epi_put(const Epi& e, uint32_t split, uint32_t i, uint32_
     }
 }
 
-// Answers of query b at rows i .. i+3 (i % 4 == 0, e.M % 4 == 0), finished
-// and stored; kClientQuery and kClientDecode add the client step's epilogue.
+// Answers of query b at rows i .. i+3 (i % 4 == 0, e.M % 4 == 0; the query's
+// term is in x), finished and stored; kClientQuery and kClientDecode add the client step's epilogue.
 template <int MODE>
 __device__ inline void rows4_store(const Epi& e, uint32_t i, uint32_t b, u32x4 x) {
-    x += colterm32(e, b) + e.row_scale * *reinterpret_cast<const u32x4*>(e.rowsum + i);
+    x += e.row_scale * *reinterpret_cast<const u32x4*>(e.rowsum + i);
     const uint64_t at = (uint64_t)b * e.o_ldb + i;
     if (MODE == kClientQuery) {
         x += *reinterpret_cast<const u32x4*>(e.client.add + at);
@@ -314,13 +326,18 @@ constexpr bool rows4_mode() {
 // query group g sit in acc[a][4g .. 4g+3] (C layout of the 32x32 MFMA: lane
 // holds column lane % 32, register v holds row 8 (v/4) + 4 (lane/32) + v%4,
 // so four consecutive registers are four consecutive rows).
+// bias[t] is added to every product of limb tile t (the lane's column).
 template <int MODE, bool GATHER, int TM, int TN>
 __device__ inline void epi_wave(const Epi& e, uint32_t split, const i32x16 (&acc)[TM][TN],
-                                uint32_t m_base, uint32_t n_base, int lane) {
+                                const int64_t (&bias)[TN], uint32_t m_base, uint32_t n_base,
+                                int lane) {
     constexpr bool kMod32 = rows4_mode<MODE>();
 #pragma unroll
     for (int g = 0; g < TN / 4; ++g) {
         const uint32_t bq = n_base / 4u + 32u * g + (uint32_t)(lane & 31);
+        const u64 qterm = query_term<MODE>(
+            e, bq, (u64)bias[4 * g] + ((u64)bias[4 * g + 1] << 8) + ((u64)bias[4 * g + 2] << 16) +
+                       ((u64)bias[4 * g + 3] << 24));
 #pragma unroll
         for (int a = 0; a < TM; ++a) {
 #pragma unroll
@@ -333,9 +350,10 @@ __device__ inline void epi_wave(const Epi& e, uint32_t split, const i32x16 (&acc
                     const int32_t p0 = acc[a][4 * g][v], p1 = acc[a][4 * g + 1][v],
                                   p2 = acc[a][4 * g + 2][v], p3 = acc[a][4 * g + 3][v];
                     x[j] = kMod32 ? (u64)((uint32_t)p0 + ((uint32_t)p1 << 8) +
-                                          ((uint32_t)p2 << 16) + ((uint32_t)p3 << 24))
+                                          ((uint32_t)p2 << 16) + ((uint32_t)p3 << 24) +
+                                          (uint32_t)qterm)
                                   : limb64(p0) + (limb64(p1) << 8) + (limb64(p2) << 16) +
-                                        (limb64(p3) << 24);
+                                        (limb64(p3) << 24) + qterm;
                 }
                 const u32x4 x4 = {(uint32_t)x[0], (uint32_t)x[1], (uint32_t)x[2], (uint32_t)x[3]};
                 if constexpr (MODE == kClientQuery || MODE == kClientDecode) {
@@ -359,13 +377,15 @@ __device__ inline void epi_wave(const Epi& e, uint32_t split, const i32x16 (&acc
 // group l.
 template <int MODE, bool GATHER, int TM, int TN>
 __device__ inline void epi_wave_narrow(const Epi& e, uint32_t split, const i32x16 (&acc)[TM][TN],
-                                       uint32_t m_base, uint32_t n_base, int lane) {
+                                       const int64_t (&bias)[TN], uint32_t m_base, uint32_t n_base,
+                                       int lane) {
     const int c = lane & 31;
     const int limb = c >> 3;
     constexpr bool kMod32 = rows4_mode<MODE>();
 #pragma unroll
     for (int t = 0; t < TN; ++t) {
         const uint32_t bq = n_base / 4u + 8u * t + (uint32_t)(c & 7);
+        const u64 qterm = query_term<MODE>(e, bq, 0);
 #pragma unroll
         for (int a = 0; a < TM; ++a) {
             const uint32_t i0 = m_base + a * 32 + 4 * (lane >> 5);
@@ -373,10 +393,10 @@ __device__ inline void epi_wave_narrow(const Epi& e, uint32_t split, const i32x1
                 u32x4 x4[4];
 #pragma unroll
                 for (int v = 0; v < 16; ++v) {
-                    uint32_t y = (uint32_t)acc[a][t][v] << (8 * limb);
+                    uint32_t y = ((uint32_t)acc[a][t][v] + (uint32_t)bias[t]) << (8 * limb);
                     y += __shfl_xor(y, 8);
                     y += __shfl_xor(y, 16);
-                    x4[v / 4][v % 4] = y;
+                    x4[v / 4][v % 4] = y + (uint32_t)qterm;
                 }
                 if (!GATHER && e.by_rows) {
                     const u32x4 mine = limb == 0 ? x4[0] : (limb == 1 ? x4[1] : (limb == 2 ? x4[2] : x4[3]));
@@ -389,10 +409,11 @@ __device__ inline void epi_wave_narrow(const Epi& e, uint32_t split, const i32x1
             } else {
 #pragma unroll
                 for (int v = 0; v < 16; ++v) {
-                    u64 x = limb64(acc[a][t][v]) << (8 * limb);
+                    u64 x = (limb64(acc[a][t][v]) + (u64)bias[t]) << (8 * limb);
                     x += __shfl_xor(x, 8);
                     x += __shfl_xor(x, 16);
-                    if (limb == 0) epi_put<MODE, GATHER>(e, split, i0 + 8 * (v / 4) + v % 4, bq, x);
+                    if (limb == 0)
+                        epi_put<MODE, GATHER>(e, split, i0 + 8 * (v / 4) + v % 4, bq, x + qterm);
                 }
             }
         }
@@ -451,7 +472,7 @@ __global__ __launch_bounds__(256) void k_finish_rows(Epi e, uint32_t splits) {
     if (g >= (uint64_t)M4 * e.B) return;
     const uint32_t b = (uint32_t)(g / M4), i = 4u * (uint32_t)(g % M4);
     const u32x4* part = static_cast<const u32x4*>(e.part) + g;
-    u32x4 v = part[0];
+    u32x4 v = part[0] + colterm32(e, b);
     for (uint32_t s = 1; s < splits; ++s) v += part[(uint64_t)s * M4 * e.B];
     rows4_store<MODE>(e, i, b, v);
 }
@@ -702,7 +723,8 @@ __global__ __launch_bounds__(T::THREADS) void k_gemm(const uint8_t* __restrict__
         if (C >= 16u) store(k1, smem + ((u + 1u) & 1u) * T::BUF_BYTES);
         __syncthreads();
     }
-    epi_wave<MODE, GATHER, T::TM, T::TN>(e, tl.split, acc, m0 + wm * T::TM * 32,
+    const int64_t bias[T::TN] = {};
+    epi_wave<MODE, GATHER, T::TM, T::TN>(e, tl.split, acc, bias, m0 + wm * T::TM * 32,
                                           n0 + wn * T::TN * 32, lane);
 }
 
@@ -782,7 +804,11 @@ struct Ring {
 // and the operand kernel: 54 us with every limb and separate epilogues, 41.6
 // with the products left out and the epilogue fused (128 x 128 tile), 35.8
 // with the loads left out too (128 x 256).
-template <class T, bool GATHER, int MODE, bool NTD, bool PLANES = false>
+// SUMS: the kernel sums the limb planes' entries q' of its columns beside the
+// products (four dot instructions per fragment) and adds 128 sum(q') to every
+// product, which is the column term, so the ingest neither clears nor sums:
+// one launch and the atomics less (see tile_sums).
+template <class T, bool GATHER, int MODE, bool NTD, bool SUMS, bool PLANES = false>
 __global__ __launch_bounds__(T::THREADS) void k_gemm_ring(const uint8_t* __restrict__ D,
                                                           uint64_t pitch,
                                                           const int8_t* __restrict__ QL,
@@ -890,6 +916,8 @@ __global__ __launch_bounds__(T::THREADS) void k_gemm_ring(const uint8_t* __restr
     const u32x4 centre = u32x4{kCentreWord, kCentreWord, kCentreWord, kCentreWord};
     constexpr int KS = T::KS;
 
+    int32_t qsum[T::TN] = {};
+
     // Fragments of one k-step of tile u (buffer buf).
     u32x4 fa[2][T::TM];
     i32x4 fb[2][T::TN];
@@ -922,6 +950,15 @@ __global__ __launch_bounds__(T::THREADS) void k_gemm_ring(const uint8_t* __restr
             for (int b = 0; b < T::TN; ++b)
                 if (!PLANES || b % 4 >= kLimb0)
                     acc[a][b] = __builtin_amdgcn_mfma_i32_32x32x32_i8(ac[a], fb[buf][b], acc[a][b], 0, 0, 0);
+        if constexpr (SUMS) {
+#pragma unroll
+            for (int b = 0; b < T::TN; ++b) {
+                if (PLANES && b % 4 < kLimb0) continue;
+#pragma unroll
+                for (int w = 0; w < 4; ++w)
+                    qsum[b] = __builtin_amdgcn_sdot4(fb[buf][b][w], 0x01010101, qsum[b], false);
+            }
+        }
         constexpr int kSkip = PLANES ? kLimb0 * kPerLimb : 0;   // QL loads left out
 #pragma unroll
         for (int i = lo; i < hi; ++i) issue_one(u, i < T::A_LOADS ? i : i + kSkip);
@@ -1004,11 +1041,18 @@ __global__ __launch_bounds__(T::THREADS) void k_gemm_ring(const uint8_t* __restr
     // Loads past the last tile may still be landing in LDS.
     wait_vmcnt<0>();
 
+    int64_t bias[T::TN] = {};
+    if constexpr (SUMS) {
+        // The lane's column: its half's entries and the other half's.
+#pragma unroll
+        for (int b = 0; b < T::TN; ++b)
+            bias[b] = 128 * (int64_t)(qsum[b] + __shfl_xor(qsum[b], 32));
+    }
     if constexpr (T::NARROW)
-        epi_wave_narrow<MODE, GATHER, T::TM, T::TN>(e, tl.split, acc, m0 + wm * T::TM * 32,
+        epi_wave_narrow<MODE, GATHER, T::TM, T::TN>(e, tl.split, acc, bias, m0 + wm * T::TM * 32,
                                                      n0 + wn * T::TN * 32, lane);
     else
-        epi_wave<MODE, GATHER, T::TM, T::TN>(e, tl.split, acc, m0 + wm * T::TM * 32,
+        epi_wave<MODE, GATHER, T::TM, T::TN>(e, tl.split, acc, bias, m0 + wm * T::TM * 32,
                                               n0 + wn * T::TN * 32, lane);
 }
 
@@ -1157,7 +1201,8 @@ __global__ __launch_bounds__(256) void k_gemm_roles(const uint8_t* __restrict__ 
                     acc[a][b] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[a], fb[b], acc[a][b], 0, 0, 0);
         }
     }
-    epi_wave<kFinal32, GATHER, T::TM, T::TN>(e, 0, acc, m0 + wm * T::TM * 32,
+    const int64_t bias[T::TN] = {};
+    epi_wave<kFinal32, GATHER, T::TM, T::TN>(e, 0, acc, bias, m0 + wm * T::TM * 32,
                                               n0 + wn * T::TN * 32, lane);
 }
 
@@ -1179,23 +1224,39 @@ uint32_t ceil_div(uint64_t a, uint64_t b) { return (uint32_t)((a + b - 1) / b); 
 // With one column tile (a batch no wider than the tile), each byte of D is
 // read by one workgroup only, so D's loads are marked non-temporal and do
 // not evict the limb planes every workgroup re-reads.
-template <class T, bool GATHER, int MODE>
-pir_status launch_ring_mode(const Gemm& g, uint32_t n_tiles, uint32_t m_tiles, hipStream_t s) {
+template <class T, bool GATHER, int MODE, bool SUMS>
+pir_status launch_ring_sums(const Gemm& g, uint32_t n_tiles, uint32_t m_tiles, hipStream_t s) {
     const uint64_t blocks = (uint64_t)n_tiles * m_tiles * g.splits;
     if (blocks > 0x7FFFFFFFull) return PIR_ERR_SHAPE;
     bool nt = false;
     if constexpr (!GATHER) {
         if (n_tiles == 1) {
             nt = true;
-            k_gemm_ring<T, false, MODE, true><<<(uint32_t)blocks, T::THREADS, T::LDS_BYTES, s>>>(
-                g.db->D, g.db->pitch, g.QL, g.Cp, n_tiles, m_tiles, g.kts, g.e);
+            k_gemm_ring<T, false, MODE, true, SUMS>
+                <<<(uint32_t)blocks, T::THREADS, T::LDS_BYTES, s>>>(
+                    g.db->D, g.db->pitch, g.QL, g.Cp, n_tiles, m_tiles, g.kts, g.e);
         }
     }
     if (!nt)
-        k_gemm_ring<T, GATHER, MODE, false><<<(uint32_t)blocks, T::THREADS, T::LDS_BYTES, s>>>(
+        k_gemm_ring<T, GATHER, MODE, false, SUMS><<<(uint32_t)blocks, T::THREADS, T::LDS_BYTES, s>>>(
             g.db->D, g.db->pitch, g.QL, g.Cp, n_tiles, m_tiles, g.kts, g.e);
     PIR_LAUNCH_CHECK();
     return PIR_OK;
+}
+
+// Whether a tile has the summing kernel: at most 128 limb rows.
+template <class T>
+constexpr bool can_sum() {
+    return T::BN <= 128;
+}
+
+template <class T, bool GATHER, int MODE>
+pir_status launch_ring_mode(const Gemm& g, uint32_t n_tiles, uint32_t m_tiles, hipStream_t s) {
+    if constexpr (can_sum<T>() && !GATHER) {
+        if (!g.e.colsum) return launch_ring_sums<T, GATHER, MODE, true>(g, n_tiles, m_tiles, s);
+    }
+    if constexpr (T::BN < 128 && !GATHER) return PIR_ERR_UNSUPPORTED;   // always summed (tile_sums)
+    else return launch_ring_sums<T, GATHER, MODE, false>(g, n_tiles, m_tiles, s);
 }
 
 template <class T>
@@ -1225,7 +1286,8 @@ pir_status launch_client(const Gemm& g, int mode, hipStream_t s) {
     const uint64_t blocks = (uint64_t)n_tiles * m_tiles * g.splits;
     if (blocks > 0x7FFFFFFFull) return PIR_ERR_SHAPE;
 #define PIR_CLIENT(MODE)                                                                       \
-    k_gemm_ring<T, false, MODE, false, true><<<(uint32_t)blocks, T::THREADS, T::LDS_BYTES, s>>>( \
+    k_gemm_ring<T, false, MODE, false, (T::BN <= 128), true>                                  \
+        <<<(uint32_t)blocks, T::THREADS, T::LDS_BYTES, s>>>(                                   \
         g.db->D, g.db->pitch, g.QL, g.Cp, n_tiles, m_tiles, g.kts, g.e)
     if (mode == kPart32) PIR_CLIENT(kPart32);
     else if (mode == kClientQuery) PIR_CLIENT(kClientQuery);
@@ -1238,9 +1300,28 @@ pir_status launch_client(const Gemm& g, int mode, hipStream_t s) {
 template <class T>
 pir_status set_client_lds() {
     const void* fns[] = {
-        (const void*)k_gemm_ring<T, false, kPart32, false, true>,
-        (const void*)k_gemm_ring<T, false, kClientQuery, false, true>,
-        (const void*)k_gemm_ring<T, false, kClientDecode, false, true>,
+        (const void*)k_gemm_ring<T, false, kPart32, false, (T::BN <= 128), true>,
+        (const void*)k_gemm_ring<T, false, kClientQuery, false, (T::BN <= 128), true>,
+        (const void*)k_gemm_ring<T, false, kClientDecode, false, (T::BN <= 128), true>,
+    };
+    for (const void* f : fns)
+        if (hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, T::LDS_BYTES) !=
+            hipSuccess)
+            return PIR_ERR_DEVICE;
+    return PIR_OK;
+}
+
+template <class T, bool SUMS>
+pir_status set_ring_lds_sums() {
+    const void* fns[] = {
+        (const void*)k_gemm_ring<T, false, kFinal32, false, SUMS>,
+        (const void*)k_gemm_ring<T, false, kPart32, false, SUMS>,
+        (const void*)k_gemm_ring<T, false, kPart64, false, SUMS>,
+        (const void*)k_gemm_ring<T, false, kFinalModP, false, SUMS>,
+        (const void*)k_gemm_ring<T, false, kFinal32, true, SUMS>,
+        (const void*)k_gemm_ring<T, false, kPart32, true, SUMS>,
+        (const void*)k_gemm_ring<T, false, kPart64, true, SUMS>,
+        (const void*)k_gemm_ring<T, false, kFinalModP, true, SUMS>,
     };
     for (const void* f : fns)
         if (hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, T::LDS_BYTES) !=
@@ -1251,17 +1332,17 @@ pir_status set_client_lds() {
 
 template <class T>
 pir_status set_ring_lds() {
+    if constexpr (can_sum<T>()) {
+        const pir_status st = set_ring_lds_sums<T, true>();
+        if (st != PIR_OK) return st;
+    }
+    if constexpr (T::BN >= 128) {
+        const pir_status st = set_ring_lds_sums<T, false>();
+        if (st != PIR_OK) return st;
+    }
     const void* fns[] = {
-        (const void*)k_gemm_ring<T, false, kFinal32, false>,
-        (const void*)k_gemm_ring<T, true, kFinal32, false>,
-        (const void*)k_gemm_ring<T, false, kPart32, false>,
-        (const void*)k_gemm_ring<T, true, kPart32, false>,
-        (const void*)k_gemm_ring<T, false, kPart64, false>,
-        (const void*)k_gemm_ring<T, false, kFinalModP, false>,
-        (const void*)k_gemm_ring<T, false, kFinal32, true>,
-        (const void*)k_gemm_ring<T, false, kPart32, true>,
-        (const void*)k_gemm_ring<T, false, kPart64, true>,
-        (const void*)k_gemm_ring<T, false, kFinalModP, true>,
+        (const void*)k_gemm_ring<T, true, kFinal32, false, false>,
+        (const void*)k_gemm_ring<T, true, kPart32, false, false>,
     };
     for (const void* f : fns)
         if (hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, T::LDS_BYTES) !=
@@ -1719,16 +1800,18 @@ void mfma_plan_fit(const pir_db_t* db, size_t scratch_bytes, BatchPlan* plan) {
     plan->need = plan->part_off;
 }
 
-// Zero the column sums, then write the limb planes and column sums of the
+// Write the limb planes and (sums) the column sums, cleared first, of the
 // queries into `base` (the layout of `P`).
 static pir_status ingest(const pir_db_t* db, const BatchIO& io, uint32_t B, const BatchPlan& P,
-                  bool narrow, uint8_t* base, hipStream_t s) {
+                  bool narrow, bool sums, uint8_t* base, hipStream_t s) {
     const uint32_t C = (uint32_t)db->cols;
     int8_t* QL = reinterpret_cast<int8_t*>(base);
-    u64* colsum = reinterpret_cast<u64*>(base + P.colsum_off);
-    k_zero_words<<<(2 * P.Bp + 255) / 256, 256, 0, s>>>(reinterpret_cast<uint32_t*>(colsum),
-                                                         2 * P.Bp);
-    PIR_LAUNCH_CHECK();
+    u64* colsum = sums ? reinterpret_cast<u64*>(base + P.colsum_off) : nullptr;
+    if (sums) {
+        k_zero_words<<<(2 * P.Bp + 255) / 256, 256, 0, s>>>(reinterpret_cast<uint32_t*>(colsum),
+                                                             2 * P.Bp);
+        PIR_LAUNCH_CHECK();
+    }
     dim3 ig((P.Bp + kIngB - 1) / kIngB, P.Cp / kIngJ);
     const bool qmajor = io.q_ldj == 1;
     const bool vec = ((uintptr_t)io.Q % 16 == 0) &&
@@ -1744,6 +1827,17 @@ static pir_status ingest(const pir_db_t* db, const BatchIO& io, uint32_t B, cons
 #undef PIR_INGEST
     PIR_LAUNCH_CHECK();
     return PIR_OK;
+}
+
+// Whether the product sums the limb planes itself (SUMS).  Narrow tiles have
+// the issue slots to spare; the 128-row tiles do while the launch and the
+// atomics weigh more than the dot instructions (32 queries: 4096 x 4096 20.9
+// -> 19.1 us, 16384 x 16384 74.7 -> 73.7, 65536 x 32768 408 -> 462; 8 queries
+// on 8192 x 8192 22.8 -> 20.6 us with the narrow tile).
+static bool tile_sums(const pir_db_t* db, const VariantInfo& vi, const uint32_t* rows,
+                      bool client) {
+    if (vi.kind != kRing || vi.bn > 128u || rows) return false;
+    return vi.bn < 128u || client || db->rows * db->cols <= (1ull << 28);
 }
 
 // Answers contiguous along rows, in whole aligned groups of four: 16-byte
@@ -1767,9 +1861,10 @@ pir_status mfma_run_batch(const pir_db_t* db, const BatchIO& io, uint32_t B,
     uint8_t* base = static_cast<uint8_t*>(ws);
     const uint8_t* qbase = planes ? static_cast<const uint8_t*>(planes) : base;
     const int8_t* QL = reinterpret_cast<const int8_t*>(qbase);
-    const u64* colsum = reinterpret_cast<const u64*>(qbase + P.colsum_off);
+    const bool sums = !tile_sums(db, vi, rows, client != nullptr);
+    const u64* colsum = sums ? reinterpret_cast<const u64*>(qbase + P.colsum_off) : nullptr;
     if (!planes) {
-        const pir_status st = ingest(db, io, B, P, vi.narrow, base, s);
+        const pir_status st = ingest(db, io, B, P, vi.narrow, sums, base, s);
         if (st != PIR_OK) return st;
     }
     if (P.M == 0) return PIR_OK;
@@ -1852,5 +1947,5 @@ pir_status mfma_ingest_planes(const pir_db_t* db, const uint32_t* A, uint32_t n,
     P.Cp = L.Cp;
     P.colsum_off = L.colsum_off;
     const BatchIO io{A, n, 1, nullptr, n, 1};
-    return ingest(db, io, n, P, false, static_cast<uint8_t*>(planes), s);
+    return ingest(db, io, n, P, false, true, static_cast<uint8_t*>(planes), s);
 }
