@@ -58,6 +58,9 @@
 // 4 KiB tiles of 32 rows x 128 bytes (tile (n/32, k/128) at
 // ((n/32) * Cp/128 + k/128) * 4096, row n%32 at 128 (n%32) within it): the
 // ingest writes whole tiles and a 1 KiB block of a GEMM k-tile is contiguous.
+#include <algorithm>
+#include <cmath>
+#include <iterator>
 #include <type_traits>
 
 #include "qpir_internal.h"
@@ -75,7 +78,7 @@ constexpr int kCpolNT = 2;   // cache-policy operand of a load: nt (non-temporal
 constexpr int kKPad = 256;                    // QL rows are zero-padded to a multiple of this
 constexpr uint32_t kExactSpan = 1u << 17;     // columns one exact int32 accumulation may cover
 constexpr uint32_t kMaxExactCols = 1u << 23;  // D q < 2^64 and exact row sums
-constexpr uint32_t kMaxSplits = 16;           // split-K pieces chosen for occupancy
+constexpr uint32_t kMaxSplits = 64;           // split-K pieces chosen for occupancy
 
 
 // Epilogue modes.
@@ -1498,7 +1501,8 @@ constexpr VariantInfo kVariants[] = {
     {"reg_256x256", kReg, 256, 256, 128, launch_reg<Reg256x256>},
 };
 constexpr uint32_t kNumVariants = sizeof(kVariants) / sizeof(kVariants[0]);
-constexpr uint32_t kVarRing128 = 2, kVarRing256 = 4, kVarReg128 = 11, kVarFew = 12,
+constexpr uint32_t kVarRing128 = 2, kVarRing256 = 4, kVarReg128x256 = 10, kVarReg128 = 11,
+                   kVarFew = 12, kVarRing128x2 = 13, kVarNarrow256 = 15, kVarNarrow128 = 16,
                    kVarRing4wD3 = 23, kVarReg256 = 25;
 constexpr bool same_name(const char* a, const char* b) {
     return *a == *b && (*a == '\0' || same_name(a + 1, b + 1));
@@ -1508,6 +1512,10 @@ static_assert(same_name(kVariants[kVarRing128].name, "ring_128x128_k128_s4") &&
                   same_name(kVariants[kVarRing256].name, "ring8w_128x256_k128_s3") &&
                   same_name(kVariants[kVarReg256].name, "reg_256x256") &&
                   same_name(kVariants[kVarReg128].name, "reg_128x128") &&
+                  same_name(kVariants[kVarReg128x256].name, "reg_128x256") &&
+                  same_name(kVariants[kVarRing128x2].name, "ring_128x128_k128_s2") &&
+                  same_name(kVariants[kVarNarrow256].name, "narrow_256x64_k128_s4") &&
+                  same_name(kVariants[kVarNarrow128].name, "narrow_128x32_k128_s6") &&
                   same_name(kVariants[kVarFew].name, "few") &&
                   same_name(kVariants[kVarRing4wD3].name, "ring_256x256_k128_d3q2"),
               "default variant indices");
@@ -1539,26 +1547,124 @@ bool variant_valid(const pir_db_t* db, uint32_t B, uint32_t v) {
     return (4u * padded_batch(B)) % vi.bn == 0;
 }
 
-// Matrix-core choice (any batch size, gathered rows allowed).  From 64
-// queries up, the four-wave 256 x 256 tile with the deeper D ring
-// (ring_256x256_k128_d3q2), which led the autotuner at 64-1024 queries on
-// 32768^2, 131072^2, 65536 x 32768 and the 3072 x 2^18 field form.  Unaligned
-// rows: the 256 x 256 register-staged tile above 32 queries (37 queries on
-// 30000 x 20001: 233 us, 128 x 256 372, 128 x 128 350).
-uint32_t default_gemm(const pir_db_t* db, uint32_t B) {
-    const uint32_t Bp = padded_batch(B);
-    if (!ring_serves(db)) return Bp == 32u ? kVarReg128 : kVarReg256;
-    if (Bp == 32u) return kVarRing128;
-    return kVarRing4wD3;
+struct SplitPlan {
+    uint32_t splits, kts;
+    double us;              // estimated time of the product and its finish
+};
+
+// Time of one k-tile of a workgroup with the chip full, microseconds: what a
+// CU's share of the memory (6.7 TB/s of database bytes), of the loads into
+// LDS (both operands, 10.8 TB/s) or of the matrix cores (2.2 POP/s) takes;
+// workgroups on one CU share them, and register-staged tiles pay their LDS
+// stores on top (15%; 128 x 256, whose eight waves each wait for few loads,
+// 60%: 64 queries on unaligned 20000 x 10007 bytes 113 us, 256 x 256 85).  Against whole calls: 128 x 32 0.63 (60000 x 12000 0.61,
+// 32768 x 32768 0.73), 128 x 128 0.78 (0.76-0.83), 128 x 256 1.17 (1.05-1.3),
+// 256 x 256 1.95 (1.9-2.1).
+double ktile_us(const VariantInfo& vi) {
+    const double bytes = vi.bm / 26e3, lds = (vi.bm + vi.bn) / 42e3;
+    const double ops = 2.0 * vi.bm * vi.bn / 8.6e6;
+    const double us = vi.bk * std::max({bytes, lds, ops}) * std::max(1u, vi.per_cu);
+    return vi.kind == kReg ? (vi.bm < vi.bn ? 1.6 : 1.15) * us : us;
+}
+
+// Split-K plan for a ring variant.  LDS lets one or two ring workgroups
+// (per_cu) reside on a CU, so a launch runs in ceil(tiles * S / slots)
+// rounds of 1/S of the K range each, slots = CUs * per_cu, and each round
+// also fills and drains the ring (about kFillTiles k-tiles); splitting adds
+// the finish launch, a pass of it per piece, and one write and one read of S
+// partials.  The plan is
+// the S (up to kMaxSplits, at least two k-tiles per piece) of the least sum,
+// looked for below two rounds of tiles; for a number of rounds the best S is
+// the most that fits in them or, if less, where the partials' growth meets
+// the product's gain.  With the partials at a flat 0.5% of the product per
+// piece, a few ten thousand rows were split far too often: 60000 x 12000, 64
+// queries in 13 pieces, 390 us, whole 243.  The field form also caps each
+// piece at kExactSpan columns.
+// `reg`: register-staged tiles split too (on databases the ring does not
+// serve; elsewhere they are only run when pinned, whole).
+constexpr double kFillTiles = 3, kFinishUs = 3, kPieceUs = 0.3, kPartialBytesPerUs = 5e6;
+SplitPlan plan_splits(uint32_t M, uint32_t N, uint32_t C, const VariantInfo& vi, bool exact,
+                      bool reg) {
+    const uint32_t ktiles = ceil_div(C, vi.bk);
+    const uint64_t mt = ceil_div(M, vi.bm), tiles = mt * ceil_div(N, vi.bn);
+    const uint64_t slots = (uint64_t)g_cus * std::max(1u, vi.per_cu);
+    const double tk = ktile_us(vi);
+    // Per piece, from whole tiles: one bound for every M of as many tiles.
+    const double part =
+        kPieceUs + 2.0 * (exact ? 8 : 4) * (double)(mt * vi.bm) * (N / 4) / kPartialBytesPerUs;
+    SplitPlan best{1u, ktiles, 1e30};
+    auto consider = [&](uint64_t want) {
+        const uint32_t kts = ceil_div(ktiles, (uint32_t)want);
+        const uint32_t sp = ceil_div(ktiles, kts);
+        const double us = (double)ceil_div(tiles * sp, slots) * (kts + kFillTiles) * tk +
+                          (sp > 1 ? kFinishUs + sp * part : 0.0);
+        if (us < best.us) best = {sp, kts, us};
+    };
+    const bool can_split = (vi.kind == kRing || (reg && vi.kind == kReg)) && ktiles != 0 && tiles != 0;
+    if (!can_split) {
+        best.us = (double)ceil_div(tiles, slots) * (ktiles + kFillTiles) * tk;
+        return best;
+    }
+    const uint64_t lo = exact ? ceil_div(ktiles, kExactSpan / vi.bk) : 1u;
+    consider(lo);
+    if (tiles < 2ull * slots) {
+        const uint64_t hi = std::max<uint64_t>(lo, std::min(kMaxSplits, ktiles / 2));
+        for (uint64_t r = 1; r <= 4; ++r) {
+            const uint64_t fit = r * slots / tiles;
+            const uint64_t gain = (uint64_t)std::sqrt(r * ktiles * tk / part);
+            consider(std::max(lo, std::min({hi, fit, gain})));
+        }
+    }
+    return best;
+}
+
+// Matrix-core choice (any batch size, gathered rows allowed): of the tiles
+// that led the autotuner somewhere, the one whose plan takes least time.
+// Large databases get the tiles that a rule on the batch alone gave (128 x
+// 128 up to 32 queries, 256 x 256 above); small ones, whose tiles leave
+// CUs idle, smaller tiles, and up to 8 and 16 queries the narrow tiles,
+// which stage a quarter and half of the query bytes.  Whole calls, microseconds, with the rule
+// on the batch alone (and its split plan) and with this one:
+//                     8 queries      48           128          256
+//   2000 x 5000      18.8   17.7   30.0  21.0   34.6  24.5   38.6  32.7
+//   1500 x 30000     30.4   23.9   53.0  41.7   60.0  51.8   76.3  77.9
+//   20000 x 10007    67.9   46.6   76.4  72.4    160   132    246   244
+//   60000 x 12000     186    119    288   195    489   371    732   718
+// `wide`: the limb planes are laid out already, or rows gathered: no narrow
+// tile.
+uint32_t default_gemm(const pir_db_t* db, uint32_t B, uint32_t M, bool exact, bool wide) {
+    static constexpr uint32_t ring[] = {kVarNarrow128, kVarNarrow256, kVarRing128,
+                                        kVarRing128x2, kVarRing256,   kVarRing4wD3};
+    static constexpr uint32_t reg[] = {kVarReg128, kVarReg128x256, kVarReg256};
+    const bool staged = !ring_serves(db);
+    const uint32_t* list = staged ? reg : ring;
+    const size_t n = staged ? std::size(reg) : std::size(ring);
+    uint32_t best = staged ? kVarReg128 : kVarRing128;
+    double best_us = 1e30;
+    for (size_t i = 0; i < n; ++i) {
+        const VariantInfo& vi = kVariants[list[i]];
+        if (vi.narrow ? wide || 4u * B > vi.bn : (4u * padded_batch(B)) % vi.bn != 0) continue;
+        const uint32_t N = 4u * layout_batch(vi, B);
+        const double us = plan_splits(M, N, (uint32_t)db->cols, vi, exact, staged).us;
+        if (us < best_us) {
+            best_us = us;
+            best = list[i];
+        }
+    }
+    return best;
 }
 
 // The dot4 stream beats the padded matrix-core tile up to two queries; at
 // four it is bound by VALU issue (measured at 32768 x 32768: 173 vs 254 us
-// for one query, 194 vs 236 us for two, 400 vs 224 us for four).
+// for one query, 194 vs 236 us for two, 400 vs 224 us for four), which
+// databases of up to kFewSmall bytes, bound by launches, do not notice (one
+// launch or two instead of three; four queries: 1024 x 1024 12-14 vs 16-18
+// us, 5000 x 2001 16 vs 17-21, 4096 x 4096 16 vs 17; 30000 x 3000 38 vs 31).
 constexpr uint32_t kFewDefault = 2;
+constexpr uint64_t kFewSmall = 1ull << 24;
 
-uint32_t default_variant(const pir_db_t* db, uint32_t B) {
-    return B <= kFewDefault ? kVarFew : default_gemm(db, B);
+bool few_default(const pir_db_t* db, uint32_t B) {
+    return B <= kFewDefault || (B <= kFewMax && db->rows * db->cols <= kFewSmall);
 }
 
 // Gathered rows (the incremental hint): scattered row addresses add
@@ -1567,44 +1673,9 @@ uint32_t default_variant(const pir_db_t* db, uint32_t B) {
 // n = 1024, on two machines: 1001-1019 us, against 1007-1294 us for the
 // two-stage 256 x 256 tile that is fastest over the whole database (that
 // one took 1146 us for the same rows sorted, 980 us for consecutive rows).
-uint32_t default_rows(const pir_db_t* db, uint32_t B) {
-    return ring_serves(db) && padded_batch(B) >= 64u ? kVarRing256 : default_gemm(db, B);
-}
-
-struct SplitPlan {
-    uint32_t splits, kts;
-};
-
-// Split-K plan for a ring variant.  LDS lets one or two ring workgroups
-// (per_cu) reside on a CU, so a launch runs in ceil(tiles * S / slots)
-// rounds of 1/S of the K range each, slots = CUs * per_cu; pick the S (up
-// to kMaxSplits, at least two k-tiles per
-// piece) that minimises that time, with a small charge per piece for the
-// partials and the pipeline fill, considered only below two rounds of
-// tiles.  The field form also caps each piece at kExactSpan columns.
-// `reg`: register-staged tiles split too (on databases the ring does not
-// serve; elsewhere they are only run when pinned, whole).
-SplitPlan plan_splits(uint32_t M, uint32_t N, uint32_t C, const VariantInfo& vi, bool exact,
-                      bool reg) {
-    const uint32_t ktiles = ceil_div(C, vi.bk);
-    if (!(vi.kind == kRing || (reg && vi.kind == kReg)) || ktiles == 0) return {1u, ktiles};
-    const uint64_t tiles = (uint64_t)ceil_div(M, vi.bm) * ceil_div(N, vi.bn);
-    const uint32_t lo = exact ? ceil_div(ktiles, kExactSpan / vi.bk) : 1u;
-    const uint64_t slots = (uint64_t)g_cus * std::max(1u, vi.per_cu);
-    uint32_t best = lo;
-    if (tiles < 2ull * slots) {
-        const uint32_t hi = std::max(lo, std::min(kMaxSplits, ktiles / 2));
-        double best_t = 1e30;
-        for (uint32_t sp = lo; sp <= hi; ++sp) {
-            const double t = (double)ceil_div(tiles * sp, slots) / sp + 0.005 * sp;
-            if (t < best_t) {
-                best_t = t;
-                best = sp;
-            }
-        }
-    }
-    const uint32_t kts = ceil_div(ktiles, best);
-    return {ceil_div(ktiles, kts), kts};
+uint32_t default_rows(const pir_db_t* db, uint32_t B, uint32_t m) {
+    return ring_serves(db) && padded_batch(B) >= 64u ? kVarRing256
+                                                     : default_gemm(db, B, m, false, true);
 }
 
 struct BatchLayout {
@@ -1747,12 +1818,19 @@ pir_status mfma_plan_batch(const pir_db_t* db, uint32_t B, const uint32_t* rows,
     if (exact && planes) return PIR_ERR_UNSUPPORTED;
 
     uint32_t v = (rows ? db->variant_rows : db->variant)[batch_bucket(B)];
-    if (v == 0 || !variant_valid(db, B, v)) v = rows ? default_rows(db, B) : default_variant(db, B);
-    if (rows && kVariants[v].kind == kFew) v = default_gemm(db, B);
+    const uint32_t M = rows ? m : (uint32_t)db->rows;
+    if (v == 0 || !variant_valid(db, B, v))
+        v = rows                               ? default_rows(db, B, m)
+            : !planes && few_default(db, B)    ? kVarFew
+                                               : default_gemm(db, B, M, exact, planes);
+    if (rows && kVariants[v].kind == kFew) v = default_gemm(db, B, m, false, true);
     // Pre-ingested planes are in the wide layout: matrix-core variants that read it.
-    if (planes && (kVariants[v].kind == kFew || kVariants[v].narrow)) v = default_gemm(db, B);
+    if (planes && (kVariants[v].kind == kFew || kVariants[v].narrow))
+        v = default_gemm(db, B, M, exact, true);
     if (exact && kVariants[v].kind != kRing && kVariants[v].kind != kFew)
-        v = (B <= kFewDefault || (B <= kFewMax && !ring_ok(db))) ? kVarFew : default_gemm(db, B);
+        v = (few_default(db, B) || (B <= kFewMax && !ring_ok(db)))
+                ? kVarFew
+                : default_gemm(db, B, M, true, false);
     if (exact && (kVariants[v].kind == kReg || kVariants[v].kind == kRoles ||
                   (kVariants[v].kind == kRing && !ring_ok(db))))
         return PIR_ERR_UNSUPPORTED;   // field form beyond kFewMax queries needs the ring kernels
@@ -1773,7 +1851,7 @@ pir_status mfma_plan_batch(const pir_db_t* db, uint32_t B, const uint32_t* rows,
     P.colsum_off = L.colsum_off;
     P.part_off = L.part_off;
     if ((uint64_t)L.Cp / kIngJ > g_max_grid_y) return PIR_ERR_SHAPE;   // ingest grid
-    P.M = rows ? m : (uint32_t)db->rows;
+    P.M = M;
     const SplitPlan sp = plan_splits(P.M, L.N, C, vi, exact, !ring_serves(db));
     P.splits = sp.splits;
     P.kts = sp.kts;
@@ -1790,14 +1868,17 @@ pir_status mfma_plan_batch(const pir_db_t* db, uint32_t B, const uint32_t* rows,
     return PIR_OK;
 }
 
-// Run in one piece what a fixed scratch cannot hold the partials of, on the
-// databases outside the ring variants' reach (a caller's 64 queries on an
-// unaligned database keep fitting the allocation-free entry point).
-void mfma_plan_fit(const pir_db_t* db, size_t scratch_bytes, BatchPlan* plan) {
-    if (plan->few || plan->splits <= 1 || plan->need <= scratch_bytes || ring_ok(db)) return;
-    plan->splits = 1;
-    plan->kts = ceil_div(db->cols, kVariants[plan->variant].bk);
-    plan->need = plan->part_off;
+// Fewer pieces, or one, where a fixed scratch cannot hold the partials of
+// the plan: the allocation-free entry point serves every batch whose limb planes
+// fit.
+void mfma_plan_fit(const pir_db_t* db, uint32_t B, size_t scratch_bytes, BatchPlan* plan) {
+    if (plan->few || plan->splits <= 1 || plan->need <= scratch_bytes) return;
+    const uint32_t ktiles = ceil_div(db->cols, kVariants[plan->variant].bk);
+    const size_t piece = (size_t)plan->M * B * 8;
+    const size_t room = scratch_bytes > plan->part_off ? (scratch_bytes - plan->part_off) / piece : 0;
+    plan->kts = ceil_div(ktiles, std::max<size_t>(room, 1));
+    plan->splits = ceil_div(ktiles, plan->kts);
+    plan->need = plan->part_off + (plan->splits > 1 ? plan->splits * piece : 0);
 }
 
 // Write the limb planes and (sums) the column sums, cleared first, of the

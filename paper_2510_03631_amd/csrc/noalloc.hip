@@ -53,7 +53,7 @@ extern "C" pir_status pir_answer_batch_noalloc(pir_db_t* db, const uint32_t* d_Q
     BatchPlan plan;
     const pir_status st = mfma_plan_batch(db, B, nullptr, 0, 0, false, &plan);
     if (st != PIR_OK) return st;
-    mfma_plan_fit(db, PIR_NOALLOC_SCRATCH_BYTES, &plan);
+    mfma_plan_fit(db, B, PIR_NOALLOC_SCRATCH_BYTES, &plan);
     if (plan.need > (size_t)PIR_NOALLOC_SCRATCH_BYTES) return PIR_ERR_SHAPE;
     const BatchIO io{d_Q, B, 1, d_out, B, 1};
     return mfma_run_batch(db, io, B, nullptr, 0, plan, g_scratch[dev], nullptr, nullptr,

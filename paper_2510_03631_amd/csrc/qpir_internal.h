@@ -130,7 +130,7 @@ pir_status mfma_plan_batch(const pir_db_t* db, uint32_t B, const uint32_t* rows,
                            uint32_t modulus, bool planes, BatchPlan* plan);
 // Drop the split-K of a plan whose partials do not fit `scratch_bytes`, where
 // the whole product does not need it.
-void mfma_plan_fit(const pir_db_t* db, size_t scratch_bytes, BatchPlan* plan);
+void mfma_plan_fit(const pir_db_t* db, uint32_t B, size_t scratch_bytes, BatchPlan* plan);
 // Enqueue a planned call; `ws` must hold plan.need bytes, 256-byte aligned;
 // `planes` (or null) as written by mfma_ingest_planes for these queries.
 // `client` (or null): the client's product and epilogue in one, where
