@@ -87,8 +87,13 @@ enum : int {
     kPart32 = 1,      // split partial sum_k 2^(8k) P_k mod 2^32 (no centring terms)
     kFinalModP = 2,   // Out mod p
     kPart64 = 3,      // split partial sum_k 2^(8k) P_k, exact (mod 2^64)
-    kClientQuery = 4,    // kFinal32, then the client's query epilogue
-    kClientDecode = 5,   // kFinal32, then the client's decode
+    // By rows: answers and partials contiguous along rows, four rows per
+    // store.  Modes of their own: a branch at every store, or one around two copies of
+    // the epilogue (which spilled), cost 0.7 us a tile.
+    kFinal32Rows = 4,
+    kPart32Rows = 5,
+    kClientQuery = 6,    // kFinal32Rows, then the client's query epilogue
+    kClientDecode = 7,   // kFinal32Rows, then the client's decode
 };
 
 __global__ void k_zero_words(uint32_t* __restrict__ p, uint32_t n) {
@@ -255,74 +260,135 @@ __device__ inline u64 limb64(int32_t v) {
     return v == INT32_MIN ? (1ull << 31) : (u64)(int64_t)v;
 }
 
+template <int MODE>
+constexpr bool partial_mode() {
+    return MODE == kPart32 || MODE == kPart32Rows || MODE == kPart64;
+}
+
+template <int MODE>
+constexpr bool by_rows_mode() {
+    return MODE >= kFinal32Rows;
+}
+
+template <int MODE>
+constexpr bool mod32_mode() {
+    return MODE != kFinalModP && MODE != kPart64;
+}
+
 // What is added to every limb combination of query b before it is stored:
 // its bias, and in the final modes the column term.
 template <int MODE>
 __device__ inline u64 query_term(const Epi& e, uint32_t b, u64 bias) {
-    if (MODE == kPart32 || MODE == kPart64 || b >= e.B) return bias;
+    if (partial_mode<MODE>() || b >= e.B) return bias;
     return bias + (MODE == kFinalModP ? colterm64(e, b) : (u64)colterm32(e, b));
 }
 
-// Output element (local row i, query b) from its limb combination
-// x = sum_k 2^(8k) P_k plus the query's term (exact; only x mod 2^32 matters
-// in the 32-bit modes).
-template <int MODE, bool GATHER>
-__device__ inline void epi_put(const Epi& e, uint32_t split, uint32_t i, uint32_t b, u64 x) {
+using gu32 = __attribute__((address_space(1))) uint32_t;
+using gu32x4 = __attribute__((address_space(1))) u32x4;
+
+// What the stores of a wave's rows need of the database: the row sums of its
+// lane's 16 TM rows (register v of tile a holds row m_base + 32 a + 8 (v/4)
+// + 4 (lane/32) + v%4) and, gathered, the rows themselves.  All are loaded
+// before the first store: a load between stores waits for every store before
+// it, 64 times a tile (1024 queries on 32768 x 32768: 3900 -> 3860 us).
+template <int MODE, bool GATHER, int TM>
+struct RowTerms {
+    static constexpr bool kUsed = !partial_mode<MODE>();
+    uint32_t sum[kUsed ? TM : 1][16], row[kUsed && GATHER ? TM : 1][16];
+
+    __device__ RowTerms(const Epi& e, uint32_t m_base, int lane) {
+        if constexpr (kUsed) {
+#pragma unroll
+            for (int a = 0; a < TM; ++a) {
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    uint32_t i = m_base + a * 32 + 8 * (v / 4) + 4 * (lane >> 5) + v % 4;
+                    if constexpr (GATHER) {
+                        i = e.rows[i < e.M ? i : e.M - 1u];
+                        row[a][v] = i;
+                    }
+                    sum[a][v] = e.rowsum[i < e.R ? i : e.R - 1u];
+                }
+            }
+        }
+    }
+    __device__ u32x4 sum4(int a, int v4) const {
+        return u32x4{sum[a][4 * v4], sum[a][4 * v4 + 1], sum[a][4 * v4 + 2], sum[a][4 * v4 + 3]};
+    }
+};
+
+// Output element (local row i, query b; register v of tile a) from its limb
+// combination x = sum_k 2^(8k) P_k plus the query's term (exact; only x mod
+// 2^32 matters in the 32-bit modes).
+template <int MODE, bool GATHER, int TM>
+__device__ inline void epi_put(const Epi& e, uint32_t split, uint32_t i, uint32_t b, u64 x,
+                               const RowTerms<MODE, GATHER, TM>& t, int a, int v) {
     if (i >= e.M || b >= e.B) return;
-    if (MODE == kFinal32 || MODE == kFinalModP) {
-        const uint32_t r = GATHER ? e.rows[i] : i;
+    if constexpr (MODE == kFinal32 || MODE == kFinalModP) {
+        uint32_t r = i;
+        if constexpr (GATHER) r = t.row[a][v];
         if (r >= e.R) return;
-        uint32_t* dst = e.out + (uint64_t)r * e.o_ldr + (uint64_t)b * e.o_ldb;
-        if (MODE == kFinal32)
-            *dst = (uint32_t)x + e.row_scale * e.rowsum[r];
+        gu32* dst = (gu32*)e.out + (uint64_t)r * e.o_ldr + (uint64_t)b * e.o_ldb;
+        if constexpr (MODE == kFinal32)
+            *dst = (uint32_t)x + e.row_scale * t.sum[a][v];
         else
-            *dst = (uint32_t)((x + (u64)kCentreWord * e.rowsum[r]) % e.p);
+            *dst = (uint32_t)((x + (u64)kCentreWord * t.sum[a][v]) % e.p);
     } else {
         const uint64_t at = ((uint64_t)split * e.M + i) * e.B + b;
-        if (MODE == kPart32)
+        if constexpr (MODE == kPart32)
             static_cast<uint32_t*>(e.part)[at] = (uint32_t)x;
         else
             static_cast<u64*>(e.part)[at] = x;
     }
 }
 
-// Answers of query b at rows i .. i+3 (i % 4 == 0, e.M % 4 == 0; the query's
-// term is in x), finished and stored; kClientQuery and kClientDecode add the client step's epilogue.
+// The client step's operand for query b at rows i .. i+3, and the queried column.
 template <int MODE>
-__device__ inline void rows4_store(const Epi& e, uint32_t i, uint32_t b, u32x4 x) {
-    x += e.row_scale * *reinterpret_cast<const u32x4*>(e.rowsum + i);
+__device__ inline u32x4 client_add(const Epi& e, uint32_t i, uint32_t b) {
+    if constexpr (MODE != kClientQuery && MODE != kClientDecode) return u32x4{0u, 0u, 0u, 0u};
+    if (i >= e.M || b >= e.B) return u32x4{0u, 0u, 0u, 0u};
+    return *reinterpret_cast<const u32x4*>(e.client.add + (uint64_t)b * e.o_ldb + i);
+}
+
+template <int MODE>
+__device__ inline uint32_t client_col(const Epi& e, uint32_t b) {
+    if constexpr (MODE != kClientQuery) return 0u;
+    return b < e.B ? e.client.cols[b] : 0u;
+}
+
+// Answers of query b at rows i .. i+3 (i % 4 == 0, e.M % 4 == 0; the query's
+// and the rows' terms are in x) stored; kClientQuery and kClientDecode add
+// the client step's epilogue.
+template <int MODE>
+__device__ inline void rows4_store(const Epi& e, uint32_t i, uint32_t b, u32x4 x, u32x4 add,
+                                   uint32_t col) {
     const uint64_t at = (uint64_t)b * e.o_ldb + i;
-    if (MODE == kClientQuery) {
-        x += *reinterpret_cast<const u32x4*>(e.client.add + at);
-        const uint32_t d = e.client.cols[b] - i;      // the queried column, if among the four
+    if constexpr (MODE == kClientQuery) {
+        x += add;
+        const uint32_t d = col - i;      // the queried column, if among the four
         x.x += d == 0u ? kClientDelta : 0u;
         x.y += d == 1u ? kClientDelta : 0u;
         x.z += d == 2u ? kClientDelta : 0u;
         x.w += d == 3u ? kClientDelta : 0u;
     }
-    if (MODE == kClientDecode) {
-        const u32x4 y = *reinterpret_cast<const u32x4*>(e.client.add + at) - x + kClientDelta / 2u;
-        *reinterpret_cast<uint32_t*>(e.client.bytes + at) =
+    if constexpr (MODE == kClientDecode) {
+        const u32x4 y = add - x + kClientDelta / 2u;
+        *(gu32*)(e.client.bytes + at) =
             (y.x >> 24) | ((y.y >> 24) << 8) | ((y.z >> 24) << 16) | (y.w & 0xFF000000u);
     } else {
-        *reinterpret_cast<u32x4*>(e.out + at) = x;
+        *(gu32x4*)((gu32*)e.out + at) = x;
     }
 }
 
 template <int MODE>
 __device__ inline void epi_put_rows4(const Epi& e, uint32_t split, uint32_t i, uint32_t b,
-                                     u32x4 x) {
+                                     u32x4 x, u32x4 rowsum, u32x4 add, uint32_t col) {
     if (i >= e.M || b >= e.B) return;
-    if (MODE == kPart32)
+    if constexpr (MODE == kPart32Rows)
         *reinterpret_cast<u32x4*>(static_cast<uint32_t*>(e.part) +
                                   ((uint64_t)split * e.B + b) * e.M + i) = x;
     else
-        rows4_store<MODE>(e, i, b, x);
-}
-
-template <int MODE>
-constexpr bool rows4_mode() {
-    return MODE == kFinal32 || MODE == kPart32 || MODE == kClientQuery || MODE == kClientDecode;
+        rows4_store<MODE>(e, i, b, x + e.row_scale * rowsum, add, col);
 }
 
 // Write a wave's accumulators through the epilogue: the four limb tiles of
@@ -330,22 +396,33 @@ constexpr bool rows4_mode() {
 // holds column lane % 32, register v holds row 8 (v/4) + 4 (lane/32) + v%4,
 // so four consecutive registers are four consecutive rows).
 // bias[t] is added to every product of limb tile t (the lane's column).
-template <int MODE, bool GATHER, int TM, int TN>
+// BY_TILE: the row terms of one 32-row tile at a time, where all of them
+// would not fit the registers.
+template <int MODE, bool GATHER, int TM, int TN,
+          bool BY_TILE = TM == 4 && (GATHER || MODE == kFinalModP)>
 __device__ inline void epi_wave(const Epi& e, uint32_t split, const i32x16 (&acc)[TM][TN],
                                 const int64_t (&bias)[TN], uint32_t m_base, uint32_t n_base,
                                 int lane) {
-    constexpr bool kMod32 = rows4_mode<MODE>();
+    constexpr bool kMod32 = mod32_mode<MODE>();
+    using Rows = RowTerms<MODE, GATHER, BY_TILE ? 1 : TM>;
+    Rows rt(e, m_base, lane);
+    auto row4 = [&](int a, int v4) { return m_base + a * 32 + 8 * v4 + 4 * (lane >> 5); };
 #pragma unroll
     for (int g = 0; g < TN / 4; ++g) {
         const uint32_t bq = n_base / 4u + 32u * g + (uint32_t)(lane & 31);
         const u64 qterm = query_term<MODE>(
             e, bq, (u64)bias[4 * g] + ((u64)bias[4 * g + 1] << 8) + ((u64)bias[4 * g + 2] << 16) +
                        ((u64)bias[4 * g + 3] << 24));
+        const uint32_t col = client_col<MODE>(e, bq);
+        u32x4 add[TM][4];
+#pragma unroll
+        for (int k = 0; k < 4 * TM; ++k) add[k / 4][k % 4] = client_add<MODE>(e, row4(k / 4, k % 4), bq);
 #pragma unroll
         for (int a = 0; a < TM; ++a) {
+            if (BY_TILE && (g || a)) rt = Rows(e, m_base + a * 32, lane);
+            const int ta = BY_TILE ? 0 : a;
 #pragma unroll
             for (int v4 = 0; v4 < 4; ++v4) {
-                const uint32_t i = m_base + a * 32 + 8 * v4 + 4 * (lane >> 5);
                 u64 x[4];
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
@@ -358,14 +435,17 @@ __device__ inline void epi_wave(const Epi& e, uint32_t split, const i32x16 (&acc
                                   : limb64(p0) + (limb64(p1) << 8) + (limb64(p2) << 16) +
                                         (limb64(p3) << 24) + qterm;
                 }
-                const u32x4 x4 = {(uint32_t)x[0], (uint32_t)x[1], (uint32_t)x[2], (uint32_t)x[3]};
-                if constexpr (MODE == kClientQuery || MODE == kClientDecode) {
-                    epi_put_rows4<MODE>(e, split, i, bq, x4);
-                } else if (kMod32 && !GATHER && e.by_rows) {
-                    epi_put_rows4<MODE>(e, split, i, bq, x4);
+                const uint32_t i = row4(a, v4);
+                if constexpr (by_rows_mode<MODE>()) {
+                    const u32x4 x4 = {(uint32_t)x[0], (uint32_t)x[1], (uint32_t)x[2],
+                                      (uint32_t)x[3]};
+                    u32x4 rs = {0u, 0u, 0u, 0u};
+                    if constexpr (Rows::kUsed) rs = rt.sum4(ta, v4);
+                    epi_put_rows4<MODE>(e, split, i, bq, x4, rs, add[a][v4], col);
                 } else {
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) epi_put<MODE, GATHER>(e, split, i + j, bq, x[j]);
+                    for (int j = 0; j < 4; ++j)
+                        epi_put(e, split, i + j, bq, x[j], rt, ta, 4 * v4 + j);
                 }
             }
         }
@@ -384,7 +464,8 @@ __device__ inline void epi_wave_narrow(const Epi& e, uint32_t split, const i32x1
                                        int lane) {
     const int c = lane & 31;
     const int limb = c >> 3;
-    constexpr bool kMod32 = rows4_mode<MODE>();
+    constexpr bool kMod32 = mod32_mode<MODE>();
+    const RowTerms<MODE, GATHER, TM> rt(e, m_base, lane);
 #pragma unroll
     for (int t = 0; t < TN; ++t) {
         const uint32_t bq = n_base / 4u + 8u * t + (uint32_t)(c & 7);
@@ -401,13 +482,19 @@ __device__ inline void epi_wave_narrow(const Epi& e, uint32_t split, const i32x1
                     y += __shfl_xor(y, 16);
                     x4[v / 4][v % 4] = y + (uint32_t)qterm;
                 }
-                if (!GATHER && e.by_rows) {
-                    const u32x4 mine = limb == 0 ? x4[0] : (limb == 1 ? x4[1] : (limb == 2 ? x4[2] : x4[3]));
-                    epi_put_rows4<MODE>(e, split, i0 + 8 * limb, bq, mine);
+                if constexpr (by_rows_mode<MODE>()) {
+                    auto of_limb = [&](u32x4 y0, u32x4 y1, u32x4 y2, u32x4 y3) {
+                        return limb == 0 ? y0 : (limb == 1 ? y1 : (limb == 2 ? y2 : y3));
+                    };
+                    u32x4 rs = {0u, 0u, 0u, 0u};
+                    if constexpr (rt.kUsed)
+                        rs = of_limb(rt.sum4(a, 0), rt.sum4(a, 1), rt.sum4(a, 2), rt.sum4(a, 3));
+                    epi_put_rows4<MODE>(e, split, i0 + 8 * limb, bq,
+                                                    of_limb(x4[0], x4[1], x4[2], x4[3]), rs, rs, 0u);
                 } else if (limb == 0) {
 #pragma unroll
                     for (int v = 0; v < 16; ++v)
-                        epi_put<MODE, GATHER>(e, split, i0 + 8 * (v / 4) + v % 4, bq, x4[v / 4][v % 4]);
+                        epi_put(e, split, i0 + 8 * (v / 4) + v % 4, bq, (u64)x4[v / 4][v % 4], rt, a, v);
                 }
             } else {
 #pragma unroll
@@ -416,7 +503,7 @@ __device__ inline void epi_wave_narrow(const Epi& e, uint32_t split, const i32x1
                     x += __shfl_xor(x, 8);
                     x += __shfl_xor(x, 16);
                     if (limb == 0)
-                        epi_put<MODE, GATHER>(e, split, i0 + 8 * (v / 4) + v % 4, bq, x + qterm);
+                        epi_put(e, split, i0 + 8 * (v / 4) + v % 4, bq, x + qterm, rt, a, v);
                 }
             }
         }
@@ -433,16 +520,21 @@ __global__ __launch_bounds__(256) void k_finish(Epi e, uint32_t splits) {
     if (r >= e.R) return;
     const uint64_t plane = (uint64_t)e.M * e.B;
     uint32_t* dst = e.out + (uint64_t)r * e.o_ldr + (uint64_t)b * e.o_ldb;
+    const uint32_t rowsum = e.rowsum[r];
     if (EXACT) {
-        u64 v = colterm64(e, b) + (u64)kCentreWord * e.rowsum[r];
+        const u64 ct = colterm64(e, b);
         const u64* part = static_cast<const u64*>(e.part) + idx;
-        for (uint32_t s = 0; s < splits; ++s) v += part[s * plane];
-        *dst = (uint32_t)(v % e.p);
+        u64 v = part[0];
+#pragma unroll 4
+        for (uint32_t s = 1; s < splits; ++s) v += part[s * plane];
+        *dst = (uint32_t)((v + ct + (u64)kCentreWord * rowsum) % e.p);
     } else {
-        uint32_t v = colterm32(e, b) + e.row_scale * e.rowsum[r];
+        const uint32_t ct = colterm32(e, b);
         const uint32_t* part = static_cast<const uint32_t*>(e.part) + idx;
-        for (uint32_t s = 0; s < splits; ++s) v += part[s * plane];
-        *dst = v;
+        uint32_t v = part[0];
+#pragma unroll 4
+        for (uint32_t s = 1; s < splits; ++s) v += part[s * plane];
+        *dst = v + ct + e.row_scale * rowsum;
     }
 }
 
@@ -458,12 +550,15 @@ __global__ __launch_bounds__(256) void k_finish4(Epi e, uint32_t splits) {
     const uint32_t r = e.rows ? e.rows[i] : i;
     if (r >= e.R) return;
     const uint64_t plane4 = (uint64_t)e.M * B4;
-    const uint32_t rs = e.row_scale * e.rowsum[r];
-    u32x4 v = u32x4{colterm32(e, b) + rs, colterm32(e, b + 1) + rs, colterm32(e, b + 2) + rs,
-                    colterm32(e, b + 3) + rs};
     const u32x4* part = static_cast<const u32x4*>(e.part) + g;
-    for (uint32_t s = 0; s < splits; ++s) v += part[s * plane4];
-    *reinterpret_cast<u32x4*>(e.out + (uint64_t)r * e.o_ldr + b) = v;
+    const uint32_t rowsum = e.rowsum[r];
+    u32x4 ct = {0u, 0u, 0u, 0u};
+    if (e.colsum)
+        ct = u32x4{colterm32(e, b), colterm32(e, b + 1), colterm32(e, b + 2), colterm32(e, b + 3)};
+    u32x4 v = part[0];
+#pragma unroll 4
+    for (uint32_t s = 1; s < splits; ++s) v += part[s * plane4];
+    *reinterpret_cast<u32x4*>(e.out + (uint64_t)r * e.o_ldr + b) = v + ct + e.row_scale * rowsum;
 }
 
 // The same for answers and partials contiguous along rows (query-major
@@ -475,9 +570,13 @@ __global__ __launch_bounds__(256) void k_finish_rows(Epi e, uint32_t splits) {
     if (g >= (uint64_t)M4 * e.B) return;
     const uint32_t b = (uint32_t)(g / M4), i = 4u * (uint32_t)(g % M4);
     const u32x4* part = static_cast<const u32x4*>(e.part) + g;
-    u32x4 v = part[0] + colterm32(e, b);
+    const u32x4 rowsum = *reinterpret_cast<const u32x4*>(e.rowsum + i);
+    const u32x4 add = client_add<MODE>(e, i, b);
+    const uint32_t col = client_col<MODE>(e, b), ct = colterm32(e, b);
+    u32x4 v = part[0];
+#pragma unroll 4
     for (uint32_t s = 1; s < splits; ++s) v += part[(uint64_t)s * M4 * e.B];
-    rows4_store<MODE>(e, i, b, v);
+    rows4_store<MODE>(e, i, b, v + ct + e.row_scale * rowsum, add, col);
 }
 
 // Workgroups are dealt round-robin to the 8 XCDs; give each XCD a
@@ -1205,7 +1304,7 @@ __global__ __launch_bounds__(256) void k_gemm_roles(const uint8_t* __restrict__ 
         }
     }
     const int64_t bias[T::TN] = {};
-    epi_wave<kFinal32, GATHER, T::TM, T::TN>(e, 0, acc, bias, m0 + wm * T::TM * 32,
+    epi_wave<kFinal32, GATHER, T::TM, T::TN, T::TM == 4>(e, 0, acc, bias, m0 + wm * T::TM * 32,
                                               n0 + wn * T::TN * 32, lane);
 }
 
@@ -1274,9 +1373,11 @@ pir_status launch_ring(const Gemm& g, hipStream_t s) {
     }
     if (g.splits > 1) {
         if (gather) return launch_ring_mode<T, true, kPart32>(g, n_tiles, m_tiles, s);
+        if (g.e.by_rows) return launch_ring_mode<T, false, kPart32Rows>(g, n_tiles, m_tiles, s);
         return launch_ring_mode<T, false, kPart32>(g, n_tiles, m_tiles, s);
     }
     if (gather) return launch_ring_mode<T, true, kFinal32>(g, n_tiles, m_tiles, s);
+    if (g.e.by_rows) return launch_ring_mode<T, false, kFinal32Rows>(g, n_tiles, m_tiles, s);
     return launch_ring_mode<T, false, kFinal32>(g, n_tiles, m_tiles, s);
 }
 
@@ -1292,7 +1393,7 @@ pir_status launch_client(const Gemm& g, int mode, hipStream_t s) {
     k_gemm_ring<T, false, MODE, false, (T::BN <= 128), true>                                  \
         <<<(uint32_t)blocks, T::THREADS, T::LDS_BYTES, s>>>(                                   \
         g.db->D, g.db->pitch, g.QL, g.Cp, n_tiles, m_tiles, g.kts, g.e)
-    if (mode == kPart32) PIR_CLIENT(kPart32);
+    if (mode == kPart32Rows) PIR_CLIENT(kPart32Rows);
     else if (mode == kClientQuery) PIR_CLIENT(kClientQuery);
     else PIR_CLIENT(kClientDecode);
 #undef PIR_CLIENT
@@ -1303,7 +1404,7 @@ pir_status launch_client(const Gemm& g, int mode, hipStream_t s) {
 template <class T>
 pir_status set_client_lds() {
     const void* fns[] = {
-        (const void*)k_gemm_ring<T, false, kPart32, false, (T::BN <= 128), true>,
+        (const void*)k_gemm_ring<T, false, kPart32Rows, false, (T::BN <= 128), true>,
         (const void*)k_gemm_ring<T, false, kClientQuery, false, (T::BN <= 128), true>,
         (const void*)k_gemm_ring<T, false, kClientDecode, false, (T::BN <= 128), true>,
     };
@@ -1319,10 +1420,14 @@ pir_status set_ring_lds_sums() {
     const void* fns[] = {
         (const void*)k_gemm_ring<T, false, kFinal32, false, SUMS>,
         (const void*)k_gemm_ring<T, false, kPart32, false, SUMS>,
+        (const void*)k_gemm_ring<T, false, kFinal32Rows, false, SUMS>,
+        (const void*)k_gemm_ring<T, false, kPart32Rows, false, SUMS>,
         (const void*)k_gemm_ring<T, false, kPart64, false, SUMS>,
         (const void*)k_gemm_ring<T, false, kFinalModP, false, SUMS>,
         (const void*)k_gemm_ring<T, false, kFinal32, true, SUMS>,
         (const void*)k_gemm_ring<T, false, kPart32, true, SUMS>,
+        (const void*)k_gemm_ring<T, false, kFinal32Rows, true, SUMS>,
+        (const void*)k_gemm_ring<T, false, kPart32Rows, true, SUMS>,
         (const void*)k_gemm_ring<T, false, kPart64, true, SUMS>,
         (const void*)k_gemm_ring<T, false, kFinalModP, true, SUMS>,
     };
@@ -1393,9 +1498,13 @@ pir_status launch_reg(const Gemm& g, hipStream_t s) {
     k_gemm<T, GATHER, MODE><<<(uint32_t)blocks, T::THREADS, T::LDS_BYTES, s>>>(             \
         db->D, db->pitch, g.QL, g.Cp, n_tiles, m_tiles, g.kts, g.e)
     if (g.splits > 1) {
-        if (g.e.rows) PIR_GEMM(true, kPart32); else PIR_GEMM(false, kPart32);
+        if (g.e.rows) PIR_GEMM(true, kPart32);
+        else if (g.e.by_rows) PIR_GEMM(false, kPart32Rows);
+        else PIR_GEMM(false, kPart32);
     } else {
-        if (g.e.rows) PIR_GEMM(true, kFinal32); else PIR_GEMM(false, kFinal32);
+        if (g.e.rows) PIR_GEMM(true, kFinal32);
+        else if (g.e.by_rows) PIR_GEMM(false, kFinal32Rows);
+        else PIR_GEMM(false, kFinal32);
     }
 #undef PIR_GEMM
     PIR_LAUNCH_CHECK();
@@ -1407,6 +1516,7 @@ pir_status set_reg_lds() {
     const void* fns[] = {
         (const void*)k_gemm<T, false, kFinal32>, (const void*)k_gemm<T, true, kFinal32>,
         (const void*)k_gemm<T, false, kPart32>, (const void*)k_gemm<T, true, kPart32>,
+        (const void*)k_gemm<T, false, kFinal32Rows>, (const void*)k_gemm<T, false, kPart32Rows>,
     };
     for (const void* f : fns)
         if (hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, T::LDS_BYTES) !=
@@ -1964,7 +2074,7 @@ pir_status mfma_run_batch(const pir_db_t* db, const BatchIO& io, uint32_t B,
     const uint64_t n = (uint64_t)P.M * B;
     if (client) {
         const int mode = client->bytes ? kClientDecode : kClientQuery;
-        const pir_status st = vi.client(g, P.splits > 1 ? kPart32 : mode, s);
+        const pir_status st = vi.client(g, P.splits > 1 ? kPart32Rows : mode, s);
         if (st != PIR_OK || P.splits <= 1) return st;
         if (mode == kClientDecode)
             k_finish_rows<kClientDecode><<<(uint32_t)((n / 4 + 255) / 256), 256, 0, s>>>(g.e, P.splits);
@@ -1981,7 +2091,7 @@ pir_status mfma_run_batch(const pir_db_t* db, const BatchIO& io, uint32_t B,
     if (exact)
         k_finish<true><<<(uint32_t)((n + 255) / 256), 256, 0, s>>>(g.e, P.splits);
     else if (g.e.by_rows)
-        k_finish_rows<kFinal32><<<(uint32_t)((n / 4 + 255) / 256), 256, 0, s>>>(g.e, P.splits);
+        k_finish_rows<kFinal32Rows><<<(uint32_t)((n / 4 + 255) / 256), 256, 0, s>>>(g.e, P.splits);
     else if (vec4)
         k_finish4<<<(uint32_t)((n / 4 + 255) / 256), 256, 0, s>>>(g.e, P.splits);
     else
