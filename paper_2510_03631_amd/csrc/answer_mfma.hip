@@ -1692,6 +1692,7 @@ double ktile_us(const VariantInfo& vi) {
 // piece at kExactSpan columns.
 // `reg`: register-staged tiles split too (on databases the ring does not
 // serve; elsewhere they are only run when pinned, whole).
+constexpr uint64_t kMaxRounds = 2;
 constexpr double kFillTiles = 3, kFinishUs = 3, kPieceUs = 0.3, kPartialBytesPerUs = 5e6;
 SplitPlan plan_splits(uint32_t M, uint32_t N, uint32_t C, const VariantInfo& vi, bool exact,
                       bool reg) {
@@ -1719,7 +1720,7 @@ SplitPlan plan_splits(uint32_t M, uint32_t N, uint32_t C, const VariantInfo& vi,
     consider(lo);
     if (tiles < 2ull * slots) {
         const uint64_t hi = std::max<uint64_t>(lo, std::min(kMaxSplits, ktiles / 2));
-        for (uint64_t r = 1; r <= 4; ++r) {
+        for (uint64_t r = 1; r <= kMaxRounds; ++r) {
             const uint64_t fit = r * slots / tiles;
             const uint64_t gain = (uint64_t)std::sqrt(r * ktiles * tk / part);
             consider(std::max(lo, std::min({hi, fit, gain})));
@@ -1793,14 +1794,15 @@ struct BatchLayout {
     size_t colsum_off, part_off, total;
 };
 
-// Largest (splits x output rows) of any split-K plan for the batches whose
+// At least (splits x output rows) of any split-K plan for the batches whose
 // wide layout has N limb columns: every ring variant valid for them (narrow
 // variants, one column tile, for N = 128: batches of at most 32), every
 // output row count up to R (gathered calls have fewer rows, and so may split
-// more), both forms.  On a database the ring does not serve, every
-// register-staged variant instead.
+// more), both forms.  A plan's pieces fill at most kMaxRounds rounds of tiles
+// and number at most kMaxSplits, or are the exact form's fewest.  On a
+// database the ring does not serve, every register-staged variant instead.
 uint64_t worst_split_rows(const pir_db_t* db, uint32_t N_wide) {
-    const uint32_t R = (uint32_t)db->rows, C = (uint32_t)db->cols;
+    const uint64_t R = db->rows, C = db->cols;
     const bool exact_ok = C <= kMaxExactCols && ring_ok(db);
     const bool reg = !ring_serves(db);
     uint64_t worst = 0;   // splits x rows
@@ -1808,31 +1810,20 @@ uint64_t worst_split_rows(const pir_db_t* db, uint32_t N_wide) {
         const VariantInfo& vi = kVariants[v];
         if (vi.kind != (reg ? kReg : kRing)) continue;
         if (vi.narrow ? N_wide != 128u : N_wide % vi.bn != 0) continue;
-        const uint32_t N = vi.narrow ? vi.bn : N_wide;
-        const uint32_t nt = N / vi.bn;
-        const uint32_t mt_all = ceil_div(R, vi.bm);
-        // Row counts where the plan may split for occupancy, then R itself.
+        const uint64_t nt = vi.narrow ? 1u : N_wide / vi.bn;
         const uint64_t slots = (uint64_t)g_cus * std::max(1u, vi.per_cu);
-        const uint32_t mt_hi = std::min<uint64_t>(mt_all, (2ull * slots + nt - 1) / nt);
-        for (uint32_t mt = 1; mt <= mt_hi + 1 && mt <= mt_all; ++mt) {
-            const uint32_t M = mt == mt_all ? R : mt * vi.bm;
-            for (int x = 0; x <= (exact_ok ? 1 : 0); ++x) {
-                const SplitPlan sp = plan_splits(M, N, C, vi, x == 1, reg);
-                if (sp.splits > 1) worst = std::max<uint64_t>(worst, (uint64_t)sp.splits * M);
-            }
-        }
-        for (int x = 0; x <= (exact_ok ? 1 : 0); ++x) {
-            const SplitPlan sp = plan_splits(R, N, C, vi, x == 1, reg);
-            if (sp.splits > 1) worst = std::max<uint64_t>(worst, (uint64_t)sp.splits * R);
-        }
+        const uint32_t ktiles = ceil_div(C, vi.bk);
+        const uint64_t hi = std::min(kMaxSplits, ktiles / 2);
+        if (hi > 1) worst = std::max(worst, std::min(hi * R, kMaxRounds * slots / nt * vi.bm));
+        const uint64_t lo = exact_ok ? ceil_div(ktiles, kExactSpan / vi.bk) : 1u;
+        if (lo > 1) worst = std::max(worst, lo * R);
     }
     return worst;
 }
 
 // Split-K partial bytes the workspace reserves for batch B (8 bytes per
-// partial).  The scan above costs tens of microseconds, so its result is
-// kept in the handle per padded-batch bucket (racing writers store the same
-// value).
+// partial).  The bound is kept in the handle per padded-batch bucket (racing
+// writers store the same value).
 size_t partial_bound(const pir_db_t* db, uint32_t B, uint32_t N) {
     std::atomic<uint64_t>& slot = db->split_rows[batch_bucket(N / 4)];
     uint64_t cached = slot.load(std::memory_order_relaxed);
