@@ -37,16 +37,18 @@
 // finishing kernel adds the S partials and the centring terms.
 //
 // Kernels
-//   k_zero_words  clear the column sums
-//   k_ingest      Q -> QL (N x Cp centred int8, K-contiguous) and exact
-//                 64-bit colsum[b] = sum_j Q[j][b]
+//   k_zero_words  clear the column sums, where the ingest sums
+//   k_ingest      Q -> QL (N x Cp centred int8, K-contiguous) and, unless
+//                 the tiles sum for themselves (tile_sums), exact 64-bit
+//                 colsum[b] = sum_j Q[j][b]
 //   k_gemm_ring   int8 MFMA 32x32x32; global tiles go straight to LDS
 //                 (global_load_lds_dwordx4) into a ring of stages; fused
 //                 epilogue, optional row gather, optional split-K
 //   k_gemm_roles  the same with separate loader waves for D and QL
-//   k_gemm        register-staged LDS tiles, for databases the ring cannot
-//                 serve (rows not 16-byte aligned)
+//   k_gemm        register-staged LDS tiles, two buffers, for databases the
+//                 ring cannot serve (rows not 16-byte aligned)
 //   k_finish      sums split-K partials and adds the centring terms
+//                 (k_finish4, k_finish_rows: four outputs a thread)
 //
 // QL row index of (query b, limb k): n = (b / 32) * 128 + k * 32 + (b % 32),
 // so the four limbs of a query land in the same lane of four adjacent 32x32
@@ -1692,8 +1694,14 @@ double ktile_us(const VariantInfo& vi) {
 // piece at kExactSpan columns.
 // `reg`: register-staged tiles split too (on databases the ring does not
 // serve; elsewhere they are only run when pinned, whole).
-constexpr uint64_t kMaxRounds = 2;
 constexpr double kFillTiles = 3, kFinishUs = 3, kPieceUs = 0.3, kPartialBytesPerUs = 5e6;
+
+// Rounds of tiles a plan may split into: tiles that fill more than half the
+// chip gain by pieces in up to four (1024 field queries on 3072 x 2^18, 192
+// tiles: four pieces in three rounds 3.4 ms, two in two 4.2), fewer tiles
+// fill one or two well.
+constexpr uint64_t max_rounds(uint64_t tiles, uint64_t slots) { return 2 * tiles > slots ? 4 : 2; }
+
 SplitPlan plan_splits(uint32_t M, uint32_t N, uint32_t C, const VariantInfo& vi, bool exact,
                       bool reg) {
     const uint32_t ktiles = ceil_div(C, vi.bk);
@@ -1720,7 +1728,7 @@ SplitPlan plan_splits(uint32_t M, uint32_t N, uint32_t C, const VariantInfo& vi,
     consider(lo);
     if (tiles < 2ull * slots) {
         const uint64_t hi = std::max<uint64_t>(lo, std::min(kMaxSplits, ktiles / 2));
-        for (uint64_t r = 1; r <= kMaxRounds; ++r) {
+        for (uint64_t r = 1; r <= max_rounds(tiles, slots); ++r) {
             const uint64_t fit = r * slots / tiles;
             const uint64_t gain = (uint64_t)std::sqrt(r * ktiles * tk / part);
             consider(std::max(lo, std::min({hi, fit, gain})));
@@ -1798,7 +1806,7 @@ struct BatchLayout {
 // wide layout has N limb columns: every ring variant valid for them (narrow
 // variants, one column tile, for N = 128: batches of at most 32), every
 // output row count up to R (gathered calls have fewer rows, and so may split
-// more), both forms.  A plan's pieces fill at most kMaxRounds rounds of tiles
+// more), both forms.  A plan's pieces fill at most max_rounds rounds of tiles
 // and number at most kMaxSplits, or are the exact form's fewest.  On a
 // database the ring does not serve, every register-staged variant instead.
 uint64_t worst_split_rows(const pir_db_t* db, uint32_t N_wide) {
@@ -1814,7 +1822,8 @@ uint64_t worst_split_rows(const pir_db_t* db, uint32_t N_wide) {
         const uint64_t slots = (uint64_t)g_cus * std::max(1u, vi.per_cu);
         const uint32_t ktiles = ceil_div(C, vi.bk);
         const uint64_t hi = std::min(kMaxSplits, ktiles / 2);
-        if (hi > 1) worst = std::max(worst, std::min(hi * R, kMaxRounds * slots / nt * vi.bm));
+        const uint64_t rounds = max_rounds(nt * ceil_div(R, vi.bm), slots);
+        if (hi > 1) worst = std::max(worst, std::min(hi * R, rounds * slots / nt * vi.bm));
         const uint64_t lo = exact_ok ? ceil_div(ktiles, kExactSpan / vi.bk) : 1u;
         if (lo > 1) worst = std::max(worst, lo * R);
     }
@@ -2012,14 +2021,16 @@ static pir_status ingest(const pir_db_t* db, const BatchIO& io, uint32_t B, cons
 }
 
 // Whether the product sums the limb planes itself (SUMS).  Narrow tiles have
-// the issue slots to spare; the 128-row tiles do while the launch and the
-// atomics weigh more than the dot instructions (32 queries: 4096 x 4096 20.9
-// -> 19.1 us, 16384 x 16384 74.7 -> 73.7, 65536 x 32768 408 -> 462; 8 queries
-// on 8192 x 8192 22.8 -> 20.6 us with the narrow tile).
-static bool tile_sums(const pir_db_t* db, const VariantInfo& vi, const uint32_t* rows,
-                      bool client) {
+// the issue slots to spare (8 queries on 8192 x 8192 22.8 -> 20.6 us); 128 x
+// 128 tiles do for one column tile and while the launch and the atomics weigh
+// more than the dot instructions (32 queries: 4096 x 4096 20.9 -> 19.1 us,
+// 16384 x 16384 74.7 -> 73.7, 65536 x 32768 408 -> 462; 64 queries, two
+// column tiles: 8192 x 8192 34.8 -> 39.4, 16384 x 8192 49.9 -> 61.7).
+static bool tile_sums(const pir_db_t* db, const VariantInfo& vi, const BatchPlan& P,
+                      const uint32_t* rows, bool client) {
     if (vi.kind != kRing || vi.bn > 128u || rows) return false;
-    return vi.bn < 128u || client || db->rows * db->cols <= (1ull << 28);
+    return vi.bn < 128u || client ||
+           (P.N <= 128u && db->rows * db->cols <= (1ull << 28));
 }
 
 // Answers contiguous along rows, in whole aligned groups of four: 16-byte
@@ -2043,7 +2054,7 @@ pir_status mfma_run_batch(const pir_db_t* db, const BatchIO& io, uint32_t B,
     uint8_t* base = static_cast<uint8_t*>(ws);
     const uint8_t* qbase = planes ? static_cast<const uint8_t*>(planes) : base;
     const int8_t* QL = reinterpret_cast<const int8_t*>(qbase);
-    const bool sums = !tile_sums(db, vi, rows, client != nullptr);
+    const bool sums = !tile_sums(db, vi, P, rows, client != nullptr);
     const u64* colsum = sums ? reinterpret_cast<const u64*>(qbase + P.colsum_off) : nullptr;
     if (!planes) {
         const pir_status st = ingest(db, io, B, P, vi.narrow, sums, base, s);
