@@ -86,7 +86,8 @@ uint32_t pir_version(void);
  *   rows, cols R >= 1, C >= 1, both < 2^31.
  *   row_pitch  bytes between row starts, >= cols.  The fast paths need
  *              d_D and row_pitch to be multiples of 16; other values are
- *              served by slower, equally exact kernels.
+ *              served exactly too (streams at the same rate, batches by
+ *              register-staged tiles).
  *   stream     stream for the metadata pass (per-row byte sums, R words of
  *              device memory allocated and owned by the handle).  The call
  *              synchronizes this stream before returning.

@@ -21,8 +21,8 @@ __device__ inline uint32_t add_bytes(const u32x4 d, uint32_t acc) {
 
 // One wave per row: byte sums through v_dot4_u32_u8 against 0x01010101.
 // Bound by reading D.  Rows start anywhere and have any length; four loads
-// per lane in flight (20000 unaligned rows of 10007 bytes, byte loads 142 us
-// before, 44 us now).
+// per lane in flight (20000 unaligned rows of 10007 bytes: byte loads 142-189
+// us, 30.6 us now).
 __global__ __launch_bounds__(256) void k_rowsum(const uint8_t* __restrict__ D, uint64_t pitch,
                                                 uint32_t R, uint32_t C,
                                                 uint32_t* __restrict__ rowsum) {
@@ -53,8 +53,8 @@ __global__ __launch_bounds__(256) void k_rowsum(const uint8_t* __restrict__ D, u
 
 // A refreshed row: one workgroup copies new row i into place and sums its
 // bytes on the way, four 16-byte pieces per thread in flight (a second pass
-// that read the row back took as long again: 328 rows of 16384 bytes, 13.4 us
-// in two kernels, 4.6 us here).
+// that read the row back took as long again: 328 rows of 16384 bytes, 14.3 us
+// in two kernels, 5.1 us here).
 __global__ __launch_bounds__(256) void k_update_rows(uint8_t* __restrict__ D, uint64_t pitch,
                                                      uint32_t R, uint32_t C,
                                                      const uint32_t* __restrict__ rows,
