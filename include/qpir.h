@@ -159,8 +159,8 @@ pir_status pir_answer_batch(pir_db_t* db, const uint32_t* d_Q, uint32_t B, uint3
  * array keeps the last call's contents; each call rewrites what it reads.
  * Errors: as pir_answer_batch, and PIR_ERR_SHAPE (nothing enqueued) when
  * the call needs more than PIR_NOALLOC_SCRATCH_BYTES of scratch (about
- * 4 * B * C bytes of limb planes plus the split-K partials; 64 queries fit
- * a 32768 x 32768 database), PIR_ERR_DEVICE when the array's address could
+ * 4 * B * C bytes of limb planes; the product is split along C only as far
+ * as its partials fit beside them; 64 queries fit a 32768 x 32768 database), PIR_ERR_DEVICE when the array's address could
  * not be resolved on this device.
  */
 #define PIR_NOALLOC_SCRATCH_BYTES (64u << 20)
