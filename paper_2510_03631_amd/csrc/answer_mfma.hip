@@ -119,9 +119,13 @@ constexpr int kIngJ = 128;
 constexpr int kIngB = 64;
 
 // VEC: 16-byte loads (4 consecutive queries of a row, or 4 consecutive
-// coordinates of a query), when the query matrix is 16-byte aligned and the
-// contiguous extent (B, or C for QMAJOR) is a multiple of 4; each thread then
-// has its whole share of the tile (8 loads, 128 bytes) in flight at once.
+// coordinates of a query) at any word address, where the contiguous extent
+// (B, or C for QMAJOR) is at least 4; the last group of a ragged extent is
+// loaded four words before its end, and words that two lanes then hold are
+// stored twice.  Each thread has its whole share of the tile (8 loads, 128
+// bytes) in flight at once; with a word per load, 8 of 32 in flight, a
+// call of 37 queries on 20000 x 10007 took 100.8 us, 88.9 so.
+typedef u32x4 word_u32x4 __attribute__((aligned(4)));
 template <bool QMAJOR, bool VEC>
 __global__ __launch_bounds__(256) void k_ingest(const uint32_t* __restrict__ Q, uint64_t ldj,
                                                 uint64_t ldb, uint32_t C, uint32_t B, uint32_t Bp,
@@ -141,16 +145,23 @@ __global__ __launch_bounds__(256) void k_ingest(const uint32_t* __restrict__ Q, 
         for (int p = 0; p < 8; ++p) {
             const uint32_t b = b0 + br + 8 * p;
             v[p] = (j < C && b < B)
-                       ? *reinterpret_cast<const u32x4*>(Q + (uint64_t)b * ldb + j)
+                       ? *reinterpret_cast<const word_u32x4*>(Q + (uint64_t)b * ldb + min(j, C - 4u))
                        : u32x4{0, 0, 0, 0};
         }
+        const int at = (int)(j < C ? min(j, C - 4u) : j) - (int)j0;
+        const int past = (int)min(C - j0, (uint32_t)kIngJ);   // coordinates the block holds
 #pragma unroll
         for (int p = 0; p < 8; ++p) {
             const int bl = br + 8 * p;
-            s[bl][4 * j4 + 0] = v[p].x;
-            s[bl][4 * j4 + 1] = v[p].y;
-            s[bl][4 * j4 + 2] = v[p].z;
-            s[bl][4 * j4 + 3] = v[p].w;
+#pragma unroll
+            for (int x = 0; x < 4; ++x) {
+                if (C % 4u == 0) {              // uniform: whole groups only
+                    s[bl][4 * j4 + x] = v[p][x];
+                } else {
+                    if (at + x >= 0) s[bl][at + x] = v[p][x];
+                    if (at < 4 * j4 && 4 * j4 + x >= past) s[bl][4 * j4 + x] = 0u;
+                }
+            }
         }
     } else if (VEC) {
         const int q4 = t & 15, jr = t >> 4;
@@ -160,16 +171,18 @@ __global__ __launch_bounds__(256) void k_ingest(const uint32_t* __restrict__ Q, 
         for (int p = 0; p < 8; ++p) {
             const uint32_t j = j0 + jr + 16 * p;
             v[p] = (j < C && b < B)
-                       ? *reinterpret_cast<const u32x4*>(Q + (uint64_t)j * ldj + b)
+                       ? *reinterpret_cast<const word_u32x4*>(Q + (uint64_t)j * ldj + min(b, B - 4u))
                        : u32x4{0, 0, 0, 0};
         }
+        const int at = (int)(b < B ? min(b, B - 4u) : b) - (int)b0;
 #pragma unroll
         for (int p = 0; p < 8; ++p) {
             const int jl = jr + 16 * p;
-            s[4 * q4 + 0][jl] = v[p].x;
-            s[4 * q4 + 1][jl] = v[p].y;
-            s[4 * q4 + 2][jl] = v[p].z;
-            s[4 * q4 + 3][jl] = v[p].w;
+#pragma unroll
+            for (int x = 0; x < 4; ++x) {
+                if (B % 4u == 0) s[4 * q4 + x][jl] = v[p][x];
+                else if (at + x >= 0) s[at + x][jl] = v[p][x];
+            }
         }
     } else if (QMAJOR) {
         const int jl = t & (kIngJ - 1);
@@ -2005,8 +2018,7 @@ static pir_status ingest(const pir_db_t* db, const BatchIO& io, uint32_t B, cons
     }
     dim3 ig((P.Bp + kIngB - 1) / kIngB, P.Cp / kIngJ);
     const bool qmajor = io.q_ldj == 1;
-    const bool vec = ((uintptr_t)io.Q % 16 == 0) &&
-                     (qmajor ? (io.q_ldb % 4 == 0 && C % 4 == 0) : (io.q_ldj % 4 == 0 && B % 4 == 0));
+    const bool vec = (qmajor ? C : B) >= 4u;
 #define PIR_INGEST(QM, V)                                                                  \
     k_ingest<QM, V><<<ig, 256, 0, s>>>(io.Q, io.q_ldj, io.q_ldb, C, B, P.Bp, P.Cp, QL, colsum, \
                                        narrow)
