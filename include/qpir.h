@@ -56,9 +56,10 @@ typedef enum pir_status {
     PIR_ERR_NO_MEMORY = 3,     /* device or host allocation failed */
     PIR_ERR_DEVICE = 4,        /* a HIP call or kernel launch failed */
     PIR_ERR_UNSUPPORTED = 5,   /* device is not gfx950, or no kernel serves this
-                                  combination (field form on gathered rows or on
-                                  an unaligned database beyond 4 queries, a
-                                  variant the database cannot run) */
+                                  combination (field form on gathered rows, or beyond
+                                  4 queries where rows are not 16-byte aligned or C
+                                  is no multiple of 16; a variant the database
+                                  cannot run) */
     PIR_ERR_WORKSPACE = 6,     /* workspace missing, too small or misaligned */
     PIR_ERR_BUSY = 7,          /* serving queue full: request not admitted */
     PIR_ERR_TIMEOUT = 8        /* wait ended before the request completed */
@@ -193,9 +194,9 @@ pir_status pir_answer_batch_qmajor(pir_db_t* db, const uint32_t* d_Qt, uint32_t 
  *   p      modulus, 2 <= p < 2^32 (prime for Shamir sharing; not checked).
  *   d_Q    C x B words, row-major.   d_out  R x B words in [0, p), row-major.
  *   d_ws   workspace of pir_workspace_bytes(db, B) bytes.
- * Requires a 16-byte aligned database with C a multiple of 16
- * (PIR_ERR_UNSUPPORTED otherwise) and C <= 2^23 (PIR_ERR_SHAPE).  p < 2
- * gives PIR_ERR_INVALID_ARG.  B == 0 is a no-op.
+ * Up to four queries run on any database; more need 16-byte aligned rows
+ * with C a multiple of 16 (PIR_ERR_UNSUPPORTED otherwise).  C <= 2^23
+ * (PIR_ERR_SHAPE).  p < 2 gives PIR_ERR_INVALID_ARG.  B == 0 is a no-op.
  */
 pir_status pir_answer_batch_modp(pir_db_t* db, const uint32_t* d_Q, uint32_t B, uint32_t p,
                                  uint32_t* d_out, void* d_ws, size_t ws_bytes,

@@ -1950,7 +1950,9 @@ pir_status mfma_plan_batch(const pir_db_t* db, uint32_t B, const uint32_t* rows,
     // Pre-ingested planes are in the wide layout: matrix-core variants that read it.
     if (planes && (kVariants[v].kind == kFew || kVariants[v].narrow))
         v = default_gemm(db, B, M, exact, true);
-    if (exact && kVariants[v].kind != kRing && kVariants[v].kind != kFew)
+    // The field form runs on ring tiles, over rows of whole 16-byte pieces, and
+    // on the dot4 stream, which takes any rows.
+    if (exact && kVariants[v].kind != kFew && (kVariants[v].kind != kRing || !ring_ok(db)))
         v = (few_default(db, B) || (B <= kFewMax && !ring_ok(db)))
                 ? kVarFew
                 : default_gemm(db, B, M, true, false);

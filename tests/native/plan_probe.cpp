@@ -1,0 +1,43 @@
+// Plans of calls, on the CPU: handles are filled in by hand, nothing is
+// enqueued and no device is touched.  Reads one call per line from stdin and
+// writes one line each (see tests/test_plans.py):
+//   batch R C pitch aligned B modulus m variant  ->  status name splits kts need workspace
+// m > 0: the call gathers m rows; variant: pinned for B's bucket (0: none).
+#include <cstdio>
+#include <cstring>
+#include <memory>
+
+#include "qpir_internal.h"
+
+static std::unique_ptr<pir_db> handle(uint64_t R, uint64_t C, uint64_t pitch, int aligned) {
+    std::unique_ptr<pir_db> db(new pir_db());
+    db->magic = kDbMagic;
+    db->D = reinterpret_cast<uint8_t*>(uintptr_t{4096});
+    db->rows = R;
+    db->cols = C;
+    db->pitch = pitch;
+    db->aligned = aligned != 0;
+    return db;
+}
+
+int main() {
+    char op[16];
+    unsigned long long R, C, pitch;
+    unsigned B, mod, m, v;
+    int aligned;
+    while (scanf("%15s %llu %llu %llu %d %u", op, &R, &C, &pitch, &aligned, &B) == 6) {
+        const auto db = handle(R, C, pitch, aligned);
+        if (strcmp(op, "batch") == 0) {
+            if (scanf("%u %u %u", &mod, &m, &v) != 3) return 2;
+            (m ? db->variant_rows : db->variant)[batch_bucket(B)] = (uint8_t)v;
+            BatchPlan p{};
+            const auto* rows = reinterpret_cast<const uint32_t*>(m ? uintptr_t{4096} : 0);
+            const pir_status st = mfma_plan_batch(db.get(), B, rows, m, mod, false, &p);
+            printf("%d %s %u %u %zu %zu\n", (int)st, mfma_variant_name(p.variant), p.splits, p.kts,
+                   p.need, mfma_workspace_bytes(db.get(), B));
+        } else {
+            return 2;
+        }
+    }
+    return 0;
+}

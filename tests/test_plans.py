@@ -1,0 +1,51 @@
+"""The batched calls' plans (status, kernel, split-K pieces, scratch) over
+shapes, alignments and forms, from the library's own planner on the CPU."""
+import os
+import random
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+PKG = os.path.join(ROOT, "paper_2510_03631_amd")
+OK, SHAPE, UNSUPPORTED = 0, 2, 5
+P = 4294967291
+
+
+@pytest.fixture(scope="module")
+def probe(tmp_path_factory):
+    """Run the planner on a list of calls; one list of words for each."""
+    exe = str(tmp_path_factory.mktemp("plan") / "plan_probe")
+    subprocess.run(["g++", "-O1", "-std=c++17", "-w", "-D__HIP_PLATFORM_AMD__",
+                    "-I", os.path.join(ROOT, "include"), "-I", os.path.join(PKG, "csrc"),
+                    "-I", "/opt/rocm/include", os.path.join(ROOT, "tests", "native", "plan_probe.cpp"),
+                    "-o", exe, os.path.join(PKG, "libqpir.so"), "-L/opt/rocm/lib", "-lamdhip64",
+                    f"-Wl,-rpath,{PKG},-rpath,/opt/rocm/lib"], check=True)
+
+    def run(calls):
+        text = "".join(" ".join(str(x) for x in c) + "\n" for c in calls)
+        out = subprocess.run([exe], input=text, capture_output=True, text=True, check=True).stdout
+        lines = [l.split() for l in out.splitlines()]
+        assert len(lines) == len(calls)
+        return lines
+    return run
+
+
+def pitch16(C):
+    return (C + 15) // 16 * 16
+
+
+def test_field_form_serves_up_to_four_queries_everywhere(probe):
+    """Aligned and unaligned rows, lengths that are and are not multiples of
+    16, below and above 16 MiB; more queries need rows of whole 16-byte
+    pieces at aligned addresses."""
+    rng = random.Random(1)
+    calls = []
+    for R, C in [(4096, 8200), (20000, 10007), (1000, 100), (3, 5), (4096, 8192), (30000, 30000)] + [
+            (rng.randint(1, 1 << 18), rng.randint(1, 1 << 16)) for _ in range(300)]:
+        for B in (1, 2, 3, 4, 5, 8, 64, 200):
+            for pitch, aligned in ((pitch16(C), 1), (C, int(C % 16 == 0)), (pitch16(C), 0)):
+                calls.append(("batch", R, C, pitch, aligned, B, P, 0, 0))
+    for c, r in zip(calls, probe(calls)):
+        served = c[5] <= 4 or (c[4] and c[2] % 16 == 0)
+        assert int(r[0]) == (OK if served else UNSUPPORTED), (c, r)
