@@ -3,6 +3,7 @@
 // writes one line each (see tests/test_plans.py):
 //   batch R C pitch aligned B modulus m variant  ->  status name splits kts need workspace
 // m > 0: the call gathers m rows; variant: pinned for B's bucket (0: none).
+//   noalloc R C pitch aligned B  ->  status name splits kts need, of the allocation-free call
 #include <cstdio>
 #include <cstring>
 #include <memory>
@@ -35,6 +36,14 @@ int main() {
             const pir_status st = mfma_plan_batch(db.get(), B, rows, m, mod, false, &p);
             printf("%d %s %u %u %zu %zu\n", (int)st, mfma_variant_name(p.variant), p.splits, p.kts,
                    p.need, mfma_workspace_bytes(db.get(), B));
+        } else if (strcmp(op, "noalloc") == 0) {
+            BatchPlan p{};
+            pir_status st = mfma_plan_batch(db.get(), B, nullptr, 0, 0, false, &p);
+            if (st == PIR_OK) {
+                mfma_plan_fit(db.get(), B, PIR_NOALLOC_SCRATCH_BYTES, &p);
+                if (p.need > PIR_NOALLOC_SCRATCH_BYTES) st = PIR_ERR_SHAPE;
+            }
+            printf("%d %s %u %u %zu\n", (int)st, mfma_variant_name(p.variant), p.splits, p.kts, p.need);
         } else {
             return 2;
         }

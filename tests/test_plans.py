@@ -49,3 +49,21 @@ def test_field_form_serves_up_to_four_queries_everywhere(probe):
     for c, r in zip(calls, probe(calls)):
         served = c[5] <= 4 or (c[4] and c[2] % 16 == 0)
         assert int(r[0]) == (OK if served else UNSUPPORTED), (c, r)
+
+
+def test_noalloc_serves_what_its_planes_allow(probe):
+    """Three and more queries are refused only where the limb planes (4 bytes
+    a query and column, queries and columns padded) alone pass the scratch."""
+    rng = random.Random(2)
+    calls = []
+    for R, C in [(1 << 24, 1), (2808755, 2), (7000000, 1), (1 << 21, 8), (1 << 22, 4)] + [
+            (rng.randint(1, 1 << rng.randint(4, 24)), rng.randint(1, 1 << rng.randint(3, 17)))
+            for _ in range(300)]:
+        for B in (3, 4, 5, 16, 64, 200):
+            calls.append(("noalloc", R, C, pitch16(C), 1, B))
+            calls.append(("noalloc", R, C, C, int(C % 16 == 0), B))
+    for c, r in zip(calls, probe(calls)):
+        Bp = 32 if c[5] <= 32 else (c[5] + 63) // 64 * 64
+        planes = 4 * Bp * ((c[2] + 255) // 256 * 256) + 8 * Bp + 512
+        if planes <= 64 << 20:
+            assert int(r[0]) == OK, (c, r)
