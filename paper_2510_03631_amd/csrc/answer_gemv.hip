@@ -521,6 +521,15 @@ SplitPlan few_plan(const pir_db_t* db, uint32_t B) {
     return rows == 16u ? plan_splits(db, 512 / blocks, kSlice) : plan_splits(db, 768 / blocks, kChunk);
 }
 
+// Whether a call's answers and queries share memory.  An unsplit launch
+// would overwrite queries that other workgroups still read.
+bool few_overlap(const pir_db_t* db, const BatchIO& io, uint32_t B) {
+    const uint64_t q_words = (db->cols - 1) * io.q_ldj + (uint64_t)(B - 1) * io.q_ldb + 1;
+    const uint64_t o_words = (db->rows - 1) * io.o_ldr + (uint64_t)(B - 1) * io.o_ldb + 1;
+    const uintptr_t q = (uintptr_t)io.Q, o = (uintptr_t)io.out;
+    return q < o + 4 * o_words && o < q + 4 * q_words;
+}
+
 template <int NQ, int RW, int WV, bool EXACT>
 pir_status launch_few_t(const pir_db_t* db, const BatchIO& io, uint32_t B, uint32_t modulus,
                         void* ws, hipStream_t s) {
@@ -528,11 +537,12 @@ pir_status launch_few_t(const pir_db_t* db, const BatchIO& io, uint32_t B, uint3
     const SplitPlan pl = few_plan(db, B);
     const uint32_t R = (uint32_t)db->rows, C = (uint32_t)db->cols;
     dim3 grid((R + kRows - 1) / kRows, pl.splits);
-    const FewOut o{io.out, io.o_ldr, io.o_ldb, modulus, pl.splits > 1 ? ws : nullptr};
+    const bool partials = pl.splits > 1 || few_overlap(db, io, B);
+    const FewOut o{io.out, io.o_ldr, io.o_ldb, modulus, partials ? ws : nullptr};
     k_answer_few<NQ, RW, WV, EXACT><<<grid, 64 * WV, 0, s>>>(
         db->D, db->pitch, R, C, io.Q, io.q_ldj, io.q_ldb, B, pl.cols_per_split, o);
     PIR_LAUNCH_CHECK();
-    if (pl.splits == 1) return PIR_OK;
+    if (!partials) return PIR_OK;
     const uint64_t n = (uint64_t)R * B;
     k_few_finish<EXACT><<<(uint32_t)((n + 255) / 256), 256, 0, s>>>(
         ws, R, B, pl.splits, modulus, io.out, io.o_ldr, io.o_ldb);
