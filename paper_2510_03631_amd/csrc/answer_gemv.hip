@@ -294,18 +294,18 @@ pir_status launch_answer1(const pir_db_t* db, const uint32_t* q, uint32_t* a, vo
 
 struct GemvVariant {
     const char* name;
-    uint32_t rows_per_block;
+    uint32_t rows_per_block, threads;
     pir_status (*launch)(const pir_db_t*, const uint32_t*, uint32_t*, void*, size_t, hipStream_t);
 };
 
 const GemvVariant kGemv[] = {
-    {"auto", 0, nullptr},
-    {"rows16", 64, launch_answer1<16, 4>},
-    {"rows8", 32, launch_answer1<8, 4>},
-    {"rows32", 128, launch_answer1<32, 4>},
-    {"rows8w8", 64, launch_answer1<8, 8>},
-    {"rows4", 16, launch_answer1<4, 4>},
-    {"rows2", 8, launch_answer1<2, 4>},
+    {"auto", 0, 0, nullptr},
+    {"rows16", 64, 256, launch_answer1<16, 4>},
+    {"rows8", 32, 256, launch_answer1<8, 4>},
+    {"rows32", 128, 256, launch_answer1<32, 4>},
+    {"rows8w8", 64, 512, launch_answer1<8, 8>},
+    {"rows4", 16, 256, launch_answer1<4, 4>},
+    {"rows2", 8, 256, launch_answer1<2, 4>},
 };
 constexpr uint32_t kNumGemv = sizeof(kGemv) / sizeof(kGemv[0]);
 constexpr uint32_t kGemvLong = 3, kGemvLarge = 4, kGemvMid = 5, kGemvSmall = 6;
@@ -327,10 +327,17 @@ constexpr uint32_t kGemvLong = 3, kGemvLarge = 4, kGemvMid = 5, kGemvSmall = 6;
 //   40000 x 26001    197      199    171        -        -
 //   32768 x 32768    162      158    162      186      178
 //   131072 x 131072 2483     2408   2460     2524     2536
-uint32_t gemv_auto(const pir_db_t* db) {
+// A grid holds fewer than 2^32 threads: databases of more rows than the choice
+// covers so take the tile of the most rows per thread.
+uint32_t gemv_by_size(const pir_db_t* db) {
     if (db->rows >= 32768u && db->cols >= 32768u) return kGemvLong;
     if (db->rows * db->cols >= (1ull << 28)) return kGemvLarge;
     return db->rows >= 16384u ? kGemvMid : kGemvSmall;
+}
+
+uint32_t gemv_auto(const pir_db_t* db) {
+    const uint32_t v = gemv_by_size(db);
+    return row_blocks(db, kGemv[v].rows_per_block) * kGemv[v].threads < (1ull << 32) ? v : kGemvLong;
 }
 
 // ---------------------------------------------------------------- few queries
@@ -596,9 +603,17 @@ size_t gemv_workspace_bytes(const pir_db_t* db) {
     return m;
 }
 
+static uint32_t gemv_choice(const pir_db_t* db) {
+    const uint32_t v = db->variant[0];
+    return v == 0 || v >= kNumGemv ? gemv_auto(db) : v;
+}
+
+GemvPlan gemv_plan(const pir_db_t* db) {
+    const uint32_t v = gemv_choice(db), rows = kGemv[v].rows_per_block;
+    return {v, (uint32_t)row_blocks(db, rows), answer1_plan(db, rows).splits, kGemv[v].threads};
+}
+
 pir_status gemv_answer(const pir_db_t* db, const uint32_t* q, uint32_t* a, void* ws,
                        size_t ws_bytes, hipStream_t s) {
-    uint32_t v = db->variant[0];
-    if (v == 0 || v >= kNumGemv) v = gemv_auto(db);
-    return kGemv[v].launch(db, q, a, ws, ws_bytes, s);
+    return kGemv[gemv_choice(db)].launch(db, q, a, ws, ws_bytes, s);
 }

@@ -91,6 +91,12 @@ __device__ inline uint32_t ql_col(uint32_t k) { return (k >> 7) * 4096u + (k & 1
 uint32_t gemv_variant_count();
 const char* gemv_variant_name(uint32_t v);
 size_t gemv_workspace_bytes(const pir_db_t* db);
+// Kernel and grid of a single-query call: row blocks x column splits
+// workgroups of `threads` threads.
+struct GemvPlan {
+    uint32_t variant, row_blocks, splits, threads;
+};
+GemvPlan gemv_plan(const pir_db_t* db);
 pir_status gemv_answer(const pir_db_t* db, const uint32_t* q, uint32_t* a, void* ws,
                        size_t ws_bytes, hipStream_t s);
 

@@ -4,6 +4,7 @@
 //   batch R C pitch aligned B modulus m variant  ->  status name splits kts need workspace
 // m > 0: the call gathers m rows; variant: pinned for B's bucket (0: none).
 //   noalloc R C pitch aligned B  ->  status name splits kts need, of the allocation-free call
+//   answer R C pitch aligned 0  ->  name row_blocks splits threads, of the single query
 #include <cstdio>
 #include <cstring>
 #include <memory>
@@ -44,6 +45,9 @@ int main() {
                 if (p.need > PIR_NOALLOC_SCRATCH_BYTES) st = PIR_ERR_SHAPE;
             }
             printf("%d %s %u %u %zu\n", (int)st, mfma_variant_name(p.variant), p.splits, p.kts, p.need);
+        } else if (strcmp(op, "answer") == 0) {
+            const GemvPlan p = gemv_plan(db.get());
+            printf("%s %u %u %u\n", gemv_variant_name(p.variant), p.row_blocks, p.splits, p.threads);
         } else {
             return 2;
         }

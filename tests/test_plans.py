@@ -67,3 +67,14 @@ def test_noalloc_serves_what_its_planes_allow(probe):
         planes = 4 * Bp * ((c[2] + 255) // 256 * 256) + 8 * Bp + 512
         if planes <= 64 << 20:
             assert int(r[0]) == OK, (c, r)
+
+
+def test_single_query_grid_fits(probe):
+    """A launch holds fewer than 2^32 threads along x, for any row count up
+    to 2^30 (and beyond)."""
+    calls = [("answer", R, C, C, int(C % 16 == 0), 0)
+             for R in (1, 1 << 20, (1 << 28) - 15, (1 << 28) - 3, 1 << 28, 1 << 29, (1 << 29) + 3,
+                       (1 << 30) - 1, (1 << 31) - 200)
+             for C in (1, 2, 16, 100, 256, 1 << 10)]
+    for c, r in zip(calls, probe(calls)):
+        assert int(r[1]) * int(r[3]) < 1 << 32, (c, r)
