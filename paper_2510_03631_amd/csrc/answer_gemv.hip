@@ -245,24 +245,31 @@ uint64_t row_blocks(const pir_db_t* db, uint32_t rows_per_block) {
 }
 
 // Single query.  Blocks of 64 rows and more run long, so the splits even out
-// the workgroups over the 256 CUs (eight waves of 8 rows, us: 3072 x 2^18, 48
-// blocks: 6 splits 163, 16 splits 129; 12288 x 40000, 192 blocks: not split
-// 90, 4 splits 83; 8192 x 32768, 128 blocks: 2 splits 48).  Smaller ones only
-// split where there are fewer than four per CU (1024 x 65536, two rows per
-// wave: 8 splits 16.2, not split 52; 2048 x 3001: not split 6.0, two 7.0).
+// the workgroups over the 256 CUs: the least of (rounds of workgroups) times
+// (whole chunks of a piece, and half a chunk's time to start) plus a tenth per
+// piece for its partials; up to 16 pieces, or one per CU for fewer than 16
+// blocks.  Eight waves of 8 rows, us: 3072 x 2^18, 48 blocks: 6 splits 163,
+// 16 splits 129; 12288 x 40000, 192 blocks: not split 90, 4 splits 83; 6736 x
+// 21568, 106 blocks: 2 splits 31, 8 splits 28; 64 x 2^22, one block: 16
+// splits 383, 128 splits 98.  Over 30 random shapes the pieces so chosen take
+// 0.9% more than the best count of each.  Smaller blocks only split where
+// there are fewer than four per CU (1024 x 65536, two rows per wave: 8 splits
+// 16.2, not split 52; 2048 x 3001: not split 6.0, two 7.0).
 SplitPlan answer1_plan(const pir_db_t* db, uint32_t rows_per_block) {
     const uint64_t blocks = row_blocks(db, rows_per_block);
     if (rows_per_block < 64) return plan_splits(db, 1024 / blocks, kSlice);
-    uint64_t best = 1;
-    double best_t = 1e300;
-    for (uint64_t s = 1; s <= 16; ++s) {
-        const double t = (double)((blocks * s + 255) / 256) / s * (1.0 + 0.03 * s);
+    const uint64_t chunks = (db->cols + kChunk - 1) / kChunk;
+    const uint64_t most = std::min(chunks, std::max<uint64_t>(16, 256 / blocks));
+    uint64_t best = chunks, best_t = ~0ull;   // chunks of a piece; time in twentieths of a chunk
+    for (uint64_t s = 1; s <= most; ++s) {
+        const uint64_t each = (chunks + s - 1) / s, pieces = (chunks + each - 1) / each;
+        const uint64_t t = (blocks * pieces + 255) / 256 * (20 * each + 10) + 2 * pieces;
         if (t < best_t) {
             best_t = t;
-            best = s;
+            best = each;
         }
     }
-    return plan_splits(db, best, kSlice);
+    return SplitPlan{(uint32_t)((chunks + best - 1) / best), (uint32_t)(best * kChunk)};
 }
 
 size_t split_bytes(const pir_db_t* db, uint32_t rows_per_block) {
@@ -308,31 +315,48 @@ const GemvVariant kGemv[] = {
     {"rows2", 8, 256, launch_answer1<2, 4>},
 };
 constexpr uint32_t kNumGemv = sizeof(kGemv) / sizeof(kGemv[0]);
-constexpr uint32_t kGemvLong = 3, kGemvLarge = 4, kGemvMid = 5, kGemvSmall = 6;
+constexpr uint32_t kGemvShort = 2, kGemvLong = 3, kGemvLarge = 4, kGemvMid = 5, kGemvSmall = 6;
 
-// Built-in choice.  While the whole stream lasts some tens of microseconds,
-// many short workgroups fill the chip most evenly; a longer one runs better
-// with more loads in flight per wave and the query slice staged once for
-// eight waves, and long rows with the fewest workgroups.  us, best split of
-// each:
-//                    rows16  rows32  rows8w8  rows4   rows2
-//   2048 x 3001       16.8      -       -       7.4     6.0
-//   4096 x 4096        7.9      -      7.3      6.8     5.5
-//   8192 x 8192       14.2     17.6   14.4     14.1    13.0
-//   65536 x 1024      12.9      -     12.9     11.9      -
-//   20000 x 10007     48.4      -     46.7     42.8      -
-//   4096 x 65536      46.2      -     45.9     46.5      -
-//   12288 x 40000     87.6      -     83.4     81.3      -
-//   3072 x 2^18      127        -    129      130        -
-//   40000 x 26001    197      199    171        -        -
-//   32768 x 32768    162      158    162      186      178
-//   131072 x 131072 2483     2408   2460     2524     2536
+// Built-in choice.  Few rows per wave and many short workgroups fill the chip
+// evenly while the rows give whole rounds of workgroups on the 256 CUs; where
+// they do not (one workgroup in four rounds for a CU, three for most), and on
+// larger databases, eight waves of 8 rows with split columns come out even.
+// Short rows pay a wave's start and end per row, so they take more rows a
+// wave; databases of at most 1024 rows only fill the chip by splitting their
+// columns, where few rows a wave leave most pieces to split.  GPU us with the
+// splits of answer1_plan (200 random shapes, 2^22 to 2^30 bytes: 1.3% over the
+// fastest kernel of each in the geometric mean):
+//                    rows16  rows32  rows8w8  rows8  rows4   rows2
+//   300 x 1000000     117     194     110      78     67      64
+//   2048 x 3001        9.3    16.2     8.6     6.9    5.9     5.1
+//   4096 x 4096        9.2    13.7     7.8     6.7    6.6     6.1
+//   8192 x 8192       16.5    18.2    15.1    16.3   14.2    14.6
+//   4352 x 42752      35.1    35.5    33.5    35.1   37.5    47.2
+//   6320 x 24320      28.3    27.9    27.5    28.4   31.5    32.0
+//   72880 x 256       11.2    13.5    11.4    10.3   11.9    15.7
+//   333824 x 512      37.4    48.4    39.6    38.3   47.1    66.9
+//   20000 x 10007     46.2    48.8    45.0    47.3   41.8    45.5
+//   262144 x 2048     84.5    79.7    84.4    77.0   75.9    78.7
+//   8192 x 65536      87.1    88.3    87.7    86.4   86.2    95.1
+//   32768 x 32768    162     158     162       -    186     178
+//   131072 x 131072 2483    2408    2460       -   2524    2536
 // A grid holds fewer than 2^32 threads: databases of more rows than the choice
 // covers so take the tile of the most rows per thread.
+constexpr uint64_t kGemvEven = 3ull << 24, kGemvBig = 3ull << 26, kGemvHuge = 1ull << 28;
+
 uint32_t gemv_by_size(const pir_db_t* db) {
-    if (db->rows >= 32768u && db->cols >= 32768u) return kGemvLong;
-    if (db->rows * db->cols >= (1ull << 28)) return kGemvLarge;
-    return db->rows >= 16384u ? kGemvMid : kGemvSmall;
+    const uint64_t R = db->rows, C = db->cols, bytes = R * C;
+    if (R <= 1024) return kGemvSmall;
+    if (R >= 12000) {
+        if (C < 1280) return kGemvShort;
+        if (bytes < kGemvHuge || C <= 2048) return kGemvMid;
+        return R >= 32768 && C >= 32768 ? kGemvLong : kGemvLarge;
+    }
+    if (bytes >= kGemvBig) return kGemvLarge;
+    const uint64_t wgs = row_blocks(db, kGemv[kGemvSmall].rows_per_block) *
+                         answer1_plan(db, kGemv[kGemvSmall].rows_per_block).splits;
+    const uint64_t even = (wgs + 255) / 256 * 256;   // what as many rounds could hold
+    return bytes >= kGemvEven && 20 * even > 21 * wgs ? kGemvLarge : kGemvSmall;
 }
 
 uint32_t gemv_auto(const pir_db_t* db) {

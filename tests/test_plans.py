@@ -78,3 +78,15 @@ def test_single_query_grid_fits(probe):
              for C in (1, 2, 16, 100, 256, 1 << 10)]
     for c, r in zip(calls, probe(calls)):
         assert int(r[1]) * int(r[3]) < 1 << 32, (c, r)
+
+
+def test_single_query_fills_the_chip(probe):
+    """Large databases of any shape run in about as many workgroups as
+    CUs (the last round at most an eighth empty): few rows by splitting
+    their columns."""
+    calls = [("answer", R, C, C, int(C % 16 == 0), 0)
+             for R, C in [(64, 1 << 22), (1, 1 << 28), (16, 1 << 25), (300, 10 ** 6), (500, 600000),
+                          (1000, 300000), (1100, 300000), (2000, 131072), (4352, 42752),
+                          (3072, 1 << 18), (6320, 24320)]]
+    for c, r in zip(calls, probe(calls)):
+        assert int(r[1]) * int(r[2]) >= 224, (c, r)
