@@ -536,20 +536,39 @@ uint32_t few_nq(uint32_t B) { return B <= 1 ? 1u : (B <= 2 ? 2u : 4u); }
 
 // Rows per workgroup and column splits.  The limb planes of NQ queries are
 // staged for a workgroup's rows, so it takes 64 (four waves of 16) and splits
-// to three workgroups per CU.  Below 32 MiB that leaves too few, and for one
-// or two queries the second launch of a split costs more than the staging: 16
-// rows (four waves of 4).  us for one / two / four queries, 64 and 16 rows:
-// 2048 x 3001 11.6 / 11.6 / 16.6 and 7.9 / 9.3 / 12.6; 4096 x 4096 8.5 / 9.8
-// / 13.3 and 9.0 / 11.3 / 17.5 (one launch, not two); 8192 x 8192 15.8 / 19.7
-// / 29.4 and 20 / 28 / 46; 3072 x 2^18 131 / 155 / 248 and 183 / 286 / 472.
+// to three workgroups per CU; 256 blocks of short rows stay whole.  Small
+// databases of few rows leave too few such workgroups, and take 16 rows (four
+// waves of 4), whole up to one slice of columns: a split's second launch costs
+// more than the staging.  Two queries stage twice as much, so they take 64
+// rows from half the size, except on a thousand rows or fewer, which would be
+// cut into too many pieces.  GPU us for one / two / four queries, best splits:
+//                  16 rows            64 rows
+//   1024 x 1024     3.5  4.5   6.4     4.5   5.7   9.2
+//   2048 x 3001     7.2  9.0  12.4    10.4  13.0  18.7
+//   4096 x 4096     8.9 10.7  16.9     7.9   9.3  12.7  (four splits)
+//   3072 x 8192    10.4 15.4  21.5    10.0  12.1  17.5
+//   3000 x 11008   13.1 19.5  28.5    12.2  14.1  21.0
+//   200 x 100000   17.0 22.3  29.4    19.9 24.0  30.3
+//   16384 x 1500    8.9 13.6  19.6     8.0  10.1  15.1  (whole)
+//   100000 x 160   17.1 24.4  43.4    14.2  18.7  36.9  (whole)
+//   8192 x 8192    18.1 29.1  44.9    15.9  18.9  27.9
 uint32_t few_rows(const pir_db_t* db, uint32_t B) {
-    return B <= 2u && db->rows * db->cols < (1ull << 25) ? 16u : 64u;
+    const uint64_t bytes = db->rows * db->cols;
+    const bool small = db->rows < 16384u && (B == 1u || db->rows <= 1024u ? bytes < (1ull << 25)
+                                                                          : bytes <= (1ull << 24));
+    return B <= 2u && small ? 16u : 64u;
 }
 
 SplitPlan few_plan(const pir_db_t* db, uint32_t B) {
     const uint32_t rows = few_rows(db, B);
     const uint64_t blocks = row_blocks(db, rows);
-    return rows == 16u ? plan_splits(db, 512 / blocks, kSlice) : plan_splits(db, 768 / blocks, kChunk);
+    if (db->cols <= (uint64_t)kSlice && (rows == 16u || blocks >= 256u)) return plan_splits(db, 1, kChunk);
+    if (rows == 64u) return plan_splits(db, 768 / blocks, kChunk);
+    // Up to eight pieces of half a slice, beyond only of whole slices (200 x
+    // 100000, one query: 25 pieces 17 us, 49 pieces 21).
+    const SplitPlan half = plan_splits(db, std::min<uint64_t>(768 / blocks, 8), kSlice / 2);
+    const SplitPlan whole = plan_splits(db, 512 / blocks, kSlice);
+    return half.splits > whole.splits ? half : whole;
 }
 
 // Whether a call's answers and queries share memory.  An unsplit launch
@@ -589,6 +608,10 @@ pir_status launch_few(const pir_db_t* db, const BatchIO& io, uint32_t B, uint32_
 }
 
 }  // namespace
+
+FewPlan few_batch_plan(const pir_db_t* db, uint32_t B) {
+    return {few_rows(db, B), few_plan(db, B).splits};
+}
 
 size_t few_workspace_bytes(const pir_db_t* db, uint32_t B) {
     if (B == 0 || B > kFewMax) return 0;

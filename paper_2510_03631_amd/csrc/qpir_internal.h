@@ -103,6 +103,11 @@ pir_status gemv_answer(const pir_db_t* db, const uint32_t* q, uint32_t* a, void*
 // Batches of at most kFewMax queries streamed with dot4 instead of the
 // matrix cores (answer_gemv.hip); modulus 0 = mod 2^32, else the field form.
 constexpr uint32_t kFewMax = 4;
+// Rows per workgroup and column splits of such a batch.
+struct FewPlan {
+    uint32_t rows_per_block, splits;
+};
+FewPlan few_batch_plan(const pir_db_t* db, uint32_t B);
 size_t few_workspace_bytes(const pir_db_t* db, uint32_t B);
 pir_status few_answer_batch(const pir_db_t* db, const BatchIO& io, uint32_t B, uint32_t modulus,
                             void* ws, size_t ws_bytes, hipStream_t s);

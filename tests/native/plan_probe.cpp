@@ -5,6 +5,7 @@
 // m > 0: the call gathers m rows; variant: pinned for B's bucket (0: none).
 //   noalloc R C pitch aligned B  ->  status name splits kts need, of the allocation-free call
 //   answer R C pitch aligned 0  ->  name row_blocks splits threads, of the single query
+//   few R C pitch aligned B  ->  rows_per_block splits, of the dot4 stream
 #include <cstdio>
 #include <cstring>
 #include <memory>
@@ -48,6 +49,9 @@ int main() {
         } else if (strcmp(op, "answer") == 0) {
             const GemvPlan p = gemv_plan(db.get());
             printf("%s %u %u %u\n", gemv_variant_name(p.variant), p.row_blocks, p.splits, p.threads);
+        } else if (strcmp(op, "few") == 0) {
+            const FewPlan p = few_batch_plan(db.get(), B);
+            printf("%u %u\n", p.rows_per_block, p.splits);
         } else {
             return 2;
         }

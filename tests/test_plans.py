@@ -90,3 +90,15 @@ def test_single_query_fills_the_chip(probe):
                           (3072, 1 << 18), (6320, 24320)]]
     for c, r in zip(calls, probe(calls)):
         assert int(r[1]) * int(r[2]) >= 224, (c, r)
+
+
+@pytest.mark.parametrize("R,C,B,rows,whole", [
+    (1024, 1024, 1, 16, True), (2048, 3001, 2, 16, True), (4096, 4096, 2, 16, True),
+    (3072, 8192, 1, 16, False), (3072, 8192, 2, 64, False), (3000, 11008, 2, 64, False),
+    (16384, 1500, 1, 64, True), (16384, 1500, 2, 64, True), (100000, 160, 1, 64, True),
+    (100000, 160, 2, 64, True), (8192, 8192, 1, 64, False), (8192, 8192, 4, 64, False)])
+def test_small_batch_stream_tiles(probe, R, C, B, rows, whole):
+    """The measured faster of 16 and 64 rows a workgroup, and one launch where
+    a split costs more than it gives."""
+    r = probe([("few", R, C, C, int(C % 16 == 0), B)])[0]
+    assert int(r[0]) == rows and (int(r[1]) == 1) == whole, r
