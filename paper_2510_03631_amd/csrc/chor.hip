@@ -10,8 +10,9 @@
 // * One query (k_chor_stream) reads only the rows it selects, about half of
 //   the database, and is bound by HBM: the selector words of a whole slab are
 //   fetched up front, set bits are taken with a wave-uniform bit scan, and up
-//   to 32 rows per wave are in flight (non-temporal loads).
-// * Two or more queries (k_chor_parity) run on the matrix cores.  XOR is
+//   to 32 rows per wave are in flight (non-temporal loads).  So do two queries
+//   on large databases (stream_two).
+// * Other batches (k_chor_parity) run on the matrix cores.  XOR is
 //   addition modulo 2, so every output bit is the parity of an integer count,
 //
 //       out[b] bit c of word n = (sum_r sel[b][r] * bit_c(DB[r][n])) mod 2,
@@ -63,19 +64,21 @@ __device__ inline uint32_t xcd_remap(uint32_t bid, uint32_t nblk) {
     return bid < per * 8u ? (bid % 8u) * per + bid / 8u : bid;
 }
 
-// One query.  Workgroup = one slab of rows [r0, r1), all columns in chunks
-// of 1024 words (lane t: words 4t..4t+3).  One load per lane fetches the
-// selector words of 64 consecutive 32-row blocks, taken in pairs: the 64-bit
-// mask names the rows to read, up to kDepth of them in flight per wave.
+// One or two queries (G).  Workgroup = one slab of rows [r0, r1), all columns
+// in chunks of 1024 words (lane t: words 4t..4t+3).  One load per lane fetches
+// the selector words of 64 / G consecutive 32-row blocks (lane l: query l G /
+// 64), taken in pairs: the queries' 64-bit masks together name the rows to
+// read, up to kDepth of them in flight per wave.
 constexpr int kDepth = 32;
 
-template <bool VEC>
+template <int G, bool VEC>
 __global__ __launch_bounds__(kThreads) void k_chor_stream(const uint32_t* __restrict__ DB,
                                                           uint64_t pitch, uint32_t rows,
                                                           uint32_t W,
                                                           const uint32_t* __restrict__ Q,
-                                                          uint32_t slab_rows,
+                                                          uint32_t qwords, uint32_t slab_rows,
                                                           uint32_t* __restrict__ out) {
+    constexpr int kBlocks = 64 / G;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t slab = xcd_remap(blockIdx.x, gridDim.x);
@@ -86,45 +89,62 @@ __global__ __launch_bounds__(kThreads) void k_chor_stream(const uint32_t* __rest
         if (c0 + 256u * (uint32_t)wave >= W) continue;   // no lane of this wave has words here
         const uint32_t w = c0 + 4u * threadIdx.x;
         const bool active = w < W;
-        u32x4 acc = u32x4{0, 0, 0, 0};
-        for (uint32_t base = r0; base < r1; base += 32u * 64u) {
+        u32x4 acc[G];
+#pragma unroll
+        for (int g = 0; g < G; ++g) acc[g] = u32x4{0, 0, 0, 0};
+        for (uint32_t base = r0; base < r1; base += 32u * kBlocks) {
             uint32_t qv = 0;
-            const uint32_t rb = base + 32u * (uint32_t)lane;
+            const uint32_t rb = base + 32u * (uint32_t)(lane % kBlocks);
             if (rb < r1) {
-                qv = Q[rb / 32u];
+                qv = Q[(uint64_t)(lane / kBlocks) * qwords + rb / 32u];
                 const uint32_t nrow = min(32u, r1 - rb);
                 if (nrow < 32u) qv &= (1u << nrow) - 1u;
             }
-            for (int jb = 0; jb < 64; jb += 2) {
+            for (int jb = 0; jb < kBlocks; jb += 2) {
                 const uint32_t rblk = base + 32u * (uint32_t)jb;
                 if (rblk >= r1) break;                    // uniform
-                const uint32_t lo = __builtin_amdgcn_readlane(qv, jb);
-                const uint32_t hi = __builtin_amdgcn_readlane(qv, jb + 1);
-                uint64_t any = (uint64_t)lo | ((uint64_t)hi << 32);
+                uint64_t sel[G], any = 0;
+#pragma unroll
+                for (int g = 0; g < G; ++g) {
+                    const uint32_t lo = __builtin_amdgcn_readlane(qv, g * kBlocks + jb);
+                    const uint32_t hi = __builtin_amdgcn_readlane(qv, g * kBlocks + jb + 1);
+                    sel[g] = (uint64_t)lo | ((uint64_t)hi << 32);
+                    any |= sel[g];
+                }
                 while (any) {
                     u32x4 d[kDepth];
+                    uint32_t idx[kDepth];
 #pragma unroll
                     for (int k = 0; k < kDepth; ++k) {
                         d[k] = u32x4{0, 0, 0, 0};
+                        idx[k] = 0;
                         if (any) {                        // uniform
-                            const uint32_t idx = (uint32_t)__builtin_ctzll(any);
+                            idx[k] = (uint32_t)__builtin_ctzll(any);
                             any &= any - 1u;
                             if (active)
-                                d[k] = load_words_nt<VEC>(DB + (uint64_t)(rblk + idx) * pitch, w,
+                                d[k] = load_words_nt<VEC>(DB + (uint64_t)(rblk + idx[k]) * pitch, w,
                                                           W);
                         }
                     }
 #pragma unroll
-                    for (int k = 0; k < kDepth; ++k) acc ^= d[k];
+                    for (int g = 0; g < G; ++g)
+#pragma unroll
+                        for (int k = 0; k < kDepth; ++k) {
+                            const uint32_t m = G == 1 ? ~0u : 0u - (uint32_t)((sel[g] >> idx[k]) & 1u);
+                            acc[g] ^= d[k] & u32x4{m, m, m, m};
+                        }
                 }
             }
         }
         if (active) {
-            uint32_t* o = out + w;
-            if (acc.x) atomicXor(o, acc.x);
-            if (w + 1 < W && acc.y) atomicXor(o + 1, acc.y);
-            if (w + 2 < W && acc.z) atomicXor(o + 2, acc.z);
-            if (w + 3 < W && acc.w) atomicXor(o + 3, acc.w);
+#pragma unroll
+            for (int g = 0; g < G; ++g) {
+                uint32_t* o = out + (uint64_t)g * W + w;
+                if (acc[g].x) atomicXor(o, acc[g].x);
+                if (w + 1 < W && acc[g].y) atomicXor(o + 1, acc[g].y);
+                if (w + 2 < W && acc[g].z) atomicXor(o + 2, acc[g].z);
+                if (w + 3 < W && acc[g].w) atomicXor(o + 3, acc[g].w);
+            }
         }
     }
 }
@@ -634,26 +654,41 @@ pir_status launch_parity(const uint32_t* d_DB, uint32_t rows, uint32_t words, ui
     return PIR_OK;
 }
 
+// Two queries select three quarters of the rows.  Where a database is long
+// enough to be bound by HBM, reading only those beats the matrix cores, which
+// read all (us, matrix cores / stream: 2^18 blocks of 3 KB 141 / 127, 2^19 271 /
+// 221, 800 MB of 2 KB blocks 151 / 135; 600 MB of 8 KB blocks 107 / 115, 2^17
+// blocks of 3 KB 79 / 87); short rows leave most of its waves idle (800 MB of 1
+// KB blocks 156 / 179), and few rows too few slabs (800 MB of 16 KB blocks 146 /
+// 149, 400 MB 77 / 124).
+bool stream_two(uint32_t rows, uint32_t words) {
+    return words >= 480u && rows >= 65536u && (uint64_t)rows * words >= (700ull << 18);
+}
+
+template <int G>
 pir_status launch_stream(const uint32_t* d_DB, uint32_t rows, uint32_t words, uint64_t pitch,
                          const uint32_t* d_Q, uint32_t* d_out, hipStream_t s) {
     // Enough rows in flight to stream HBM (32 per wave), few enough slabs to
     // keep the output atomics (slabs x words, all onto the same words) down:
-    // at most one workgroup per CU, and at least 256 rows per slab.
+    // at most one workgroup per CU (two for two queries), and at least 256
+    // rows per slab.
     // (Measured on 2^18 and 2^16 rows of 3 KB: fewer workgroups starve the
     // stream on the large database, more slabs spend the small one's time in
     // atomics.)
-    uint64_t slab = (rows + 255) / 256;
+    constexpr uint32_t kTarget = 256u * G;
+    uint64_t slab = ((uint64_t)rows + kTarget - 1) / kTarget;
     slab = (slab + 31) / 32 * 32;
     if (slab < 256) slab = 256;
     const uint64_t blocks = (rows + slab - 1) / slab;
     if (blocks > 0x7FFFFFFFull) return PIR_ERR_SHAPE;
     const bool vec = ((uintptr_t)d_DB % 16 == 0) && (words % 4 == 0) && (pitch % 4 == 0);
+    const uint32_t qwords = (rows + 31) / 32;
     if (vec)
-        k_chor_stream<true><<<(uint32_t)blocks, kThreads, 0, s>>>(d_DB, pitch, rows, words, d_Q,
-                                                                  (uint32_t)slab, d_out);
+        k_chor_stream<G, true><<<(uint32_t)blocks, kThreads, 0, s>>>(d_DB, pitch, rows, words, d_Q,
+                                                                     qwords, (uint32_t)slab, d_out);
     else
-        k_chor_stream<false><<<(uint32_t)blocks, kThreads, 0, s>>>(d_DB, pitch, rows, words, d_Q,
-                                                                   (uint32_t)slab, d_out);
+        k_chor_stream<G, false><<<(uint32_t)blocks, kThreads, 0, s>>>(d_DB, pitch, rows, words, d_Q,
+                                                                      qwords, (uint32_t)slab, d_out);
     PIR_LAUNCH_CHECK();
     return PIR_OK;
 }
@@ -679,10 +714,11 @@ pir_status chor_init(uint32_t* d_out, const uint32_t* d_init, uint64_t n, hipStr
 pir_status chor_xor(const uint32_t* d_DB, uint32_t rows, uint32_t words, uint64_t pitch,
                     const uint32_t* d_Q, uint32_t B, const uint32_t* d_init, uint32_t* d_out,
                     hipStream_t s) {
-    if (B == 1) {
-        const pir_status st = chor_init(d_out, d_init, words, s);
+    if (B == 1 || (B == 2 && stream_two(rows, words))) {
+        const pir_status st = chor_init(d_out, d_init, (uint64_t)B * words, s);
         if (st != PIR_OK) return st;
-        return launch_stream(d_DB, rows, words, pitch, d_Q, d_out, s);
+        if (B == 1) return launch_stream<1>(d_DB, rows, words, pitch, d_Q, d_out, s);
+        return launch_stream<2>(d_DB, rows, words, pitch, d_Q, d_out, s);
     }
     // Up to 32 queries one 32-query tile with two workgroup halves; above,
     // 64 queries per workgroup, which halves the masks and the transposes
