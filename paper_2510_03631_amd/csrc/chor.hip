@@ -262,7 +262,7 @@ template <int TM, int NH, bool DMA, bool NT>
 __global__ __launch_bounds__(256 * NH, TM == 1 ? 2 : 1) void k_chor_parity(
     const uint32_t* __restrict__ DB, uint64_t pitch, uint32_t rows, uint32_t W,
     const uint32_t* __restrict__ Q, uint32_t qwords, uint32_t B, uint32_t slab_rows,
-    uint32_t n_qg, uint32_t n_cs, bool first, const uint32_t* init, uint32_t* out) {
+    uint32_t n_qg, uint32_t cs0, uint32_t n_cs, bool first, const uint32_t* init, uint32_t* out) {
     constexpr int NW = kParWords;
     constexpr int kWgWords = NW * NH;
     constexpr int kTile = 4 * 8 * NW;                 // 16-byte entries of a transposed chunk
@@ -279,7 +279,7 @@ __global__ __launch_bounds__(256 * NH, TM == 1 ? 2 : 1) void k_chor_parity(
     // groups that read the same rows run on one XCD and share its L2.
     const uint32_t bid = xcd_remap(blockIdx.x, gridDim.x);
     const uint32_t qg = bid % n_qg;
-    const uint32_t cs = (bid / n_qg) % n_cs;
+    const uint32_t cs = cs0 + (bid / n_qg) % n_cs;
     const uint32_t slab = bid / (n_qg * n_cs);
     const uint32_t r0 = slab * slab_rows;
     const uint32_t r1 = min(rows, r0 + slab_rows);
@@ -624,8 +624,10 @@ pir_status launch_parity(const uint32_t* d_DB, uint32_t rows, uint32_t words, ui
     const uint32_t n_cs = (words + kParWords * NH - 1) / (kParWords * NH);
     const uint64_t per_slab = (uint64_t)n_qg * n_cs;
     const Slabs sl = parity_slabs(rows, per_slab);
-    const uint64_t blocks = per_slab * sl.count;
-    if (blocks > 0x7FFFFFFFull) return PIR_ERR_SHAPE;
+    // A grid holds fewer than 2^32 threads; very wide blocks take several
+    // launches of `most` column slices each.
+    const uint64_t most = ((1ull << 32) - 1) / (256 * NH) / ((uint64_t)n_qg * sl.count);
+    if (most == 0) return PIR_ERR_SHAPE;
     const bool first = sl.count == 1;
     if (!first) {
         const pir_status st = chor_init(d_out, d_init, (uint64_t)B * words, s);
@@ -637,20 +639,24 @@ pir_status launch_parity(const uint32_t* d_DB, uint32_t rows, uint32_t words, ui
     // loads, 142 us non-temporal; 2^16 blocks 40 and 46 us).
     const bool nt = n_qg == 1 && (uint64_t)rows * words * 4u > (256ull << 20);
     const bool dma = TM == 2 && (uintptr_t)d_DB % 16 == 0 && words % 4 == 0 && pitch % 4 == 0;
-#define PIR_PARITY(DMA, X)                                                                \
-    k_chor_parity<TM, NH, DMA, X><<<(uint32_t)blocks, 256 * NH, 0, s>>>(                  \
-        d_DB, pitch, rows, words, d_Q, (rows + 31) / 32, B, sl.rows, n_qg, n_cs, first, d_init, \
-        d_out)
-    if constexpr (TM == 2) {
-        if (dma) {
-            if (nt) PIR_PARITY(true, true); else PIR_PARITY(true, false);
-            PIR_LAUNCH_CHECK();
-            return PIR_OK;
+    for (uint64_t cs0 = 0; cs0 < n_cs; cs0 += most) {
+        const uint32_t cs = (uint32_t)std::min(most, n_cs - cs0);
+        const uint32_t blocks = n_qg * cs * sl.count;
+#define PIR_PARITY(DMA, X)                                                                   \
+    k_chor_parity<TM, NH, DMA, X><<<blocks, 256 * NH, 0, s>>>(                               \
+        d_DB, pitch, rows, words, d_Q, (rows + 31) / 32, B, sl.rows, n_qg, (uint32_t)cs0, cs, first, \
+        d_init, d_out)
+        if constexpr (TM == 2) {
+            if (dma) {
+                if (nt) PIR_PARITY(true, true); else PIR_PARITY(true, false);
+                PIR_LAUNCH_CHECK();
+                continue;
+            }
         }
-    }
-    if (nt) PIR_PARITY(false, true); else PIR_PARITY(false, false);
+        if (nt) PIR_PARITY(false, true); else PIR_PARITY(false, false);
 #undef PIR_PARITY
-    PIR_LAUNCH_CHECK();
+        PIR_LAUNCH_CHECK();
+    }
     return PIR_OK;
 }
 
