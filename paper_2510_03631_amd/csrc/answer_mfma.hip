@@ -1715,6 +1715,11 @@ constexpr double kFillTiles = 3, kFinishUs = 3, kPieceUs = 0.3, kPartialBytesPer
 // fill one or two well.
 constexpr uint64_t max_rounds(uint64_t tiles, uint64_t slots) { return 2 * tiles > slots ? 4 : 2; }
 
+// Writing and reading the partials of one piece of `rows` rows and N limb rows.
+double part_us(uint32_t rows, uint32_t N, bool exact) {
+    return 2.0 * (exact ? 8 : 4) * (double)rows * (N / 4) / kPartialBytesPerUs;
+}
+
 SplitPlan plan_splits(uint32_t M, uint32_t N, uint32_t C, const VariantInfo& vi, bool exact,
                       bool reg) {
     const uint32_t ktiles = ceil_div(C, vi.bk);
@@ -1722,8 +1727,7 @@ SplitPlan plan_splits(uint32_t M, uint32_t N, uint32_t C, const VariantInfo& vi,
     const uint64_t slots = (uint64_t)g_cus * std::max(1u, vi.per_cu);
     const double tk = ktile_us(vi);
     // Per piece, from whole tiles: one bound for every M of as many tiles.
-    const double part =
-        kPieceUs + 2.0 * (exact ? 8 : 4) * (double)(mt * vi.bm) * (N / 4) / kPartialBytesPerUs;
+    const double part = kPieceUs + (double)mt * part_us(vi.bm, N, exact);
     SplitPlan best{1u, ktiles, 1e30};
     auto consider = [&](uint64_t want) {
         const uint32_t kts = ceil_div(ktiles, (uint32_t)want);
@@ -1820,48 +1824,90 @@ struct BatchLayout {
     size_t colsum_off, part_off, total;
 };
 
-// At least (splits x output rows) of any split-K plan for the batches whose
-// wide layout has N limb columns: every ring variant valid for them (narrow
-// variants, one column tile, for N = 128: batches of at most 32), every
-// output row count up to R (gathered calls have fewer rows, and so may split
-// more), both forms.  A plan's pieces fill at most max_rounds rounds of tiles
-// and number at most kMaxSplits, or are the exact form's fewest.  On a
-// database the ring does not serve, every register-staged variant instead.
-uint64_t worst_split_rows(const pir_db_t* db, uint32_t N_wide) {
-    const uint64_t R = db->rows, C = db->cols;
-    const bool exact_ok = C <= kMaxExactCols && ring_ok(db);
-    const bool reg = !ring_serves(db);
-    uint64_t worst = 0;   // splits x rows
-    for (uint32_t v = 1; v < kNumVariants; ++v) {
-        const VariantInfo& vi = kVariants[v];
-        if (vi.kind != (reg ? kReg : kRing)) continue;
-        if (vi.narrow ? N_wide != 128u : N_wide % vi.bn != 0) continue;
-        const uint64_t nt = vi.narrow ? 1u : N_wide / vi.bn;
-        const uint64_t slots = (uint64_t)g_cus * std::max(1u, vi.per_cu);
-        const uint32_t ktiles = ceil_div(C, vi.bk);
-        const uint64_t hi = std::min(kMaxSplits, ktiles / 2);
-        const uint64_t rounds = max_rounds(nt * ceil_div(R, vi.bm), slots);
-        if (hi > 1) worst = std::max(worst, std::min(hi * R, rounds * slots / nt * vi.bm));
-        const uint64_t lo = exact_ok ? ceil_div(ktiles, kExactSpan / vi.bk) : 1u;
-        if (lo > 1) worst = std::max(worst, lo * R);
+// At least the partial words of a query, splits x output rows, of any plan
+// that cuts `vi`'s tiles into pieces for occupancy, on up to R rows (gathered
+// calls have fewer rows, and so may split more).  The loops follow
+// plan_splits: S pieces of mt row tiles in `r` rounds are only chosen where
+// they take less time than whole tiles in u rounds, which bounds mt.
+uint64_t worst_pieces(uint64_t R, uint32_t C, const VariantInfo& vi, uint32_t nt, bool exact) {
+    const uint32_t ktiles = ceil_div(C, vi.bk);
+    const uint64_t slots = (uint64_t)g_cus * std::max(1u, vi.per_cu);
+    const uint64_t mt_all = ceil_div(R, vi.bm), hi = std::min(kMaxSplits, ktiles / 2);
+    const double tk = ktile_us(vi);
+    const double part_mt = part_us(vi.bm, nt * vi.bn, exact);   // per piece and row tile
+    uint64_t worst = 0;
+    for (uint64_t S = 2; S <= hi; ++S) {
+        const uint32_t kts = ceil_div(ktiles, (uint32_t)S);
+        if (ceil_div(ktiles, kts) != S) continue;
+        for (uint64_t u = 1; u <= 2; ++u) {
+            for (uint64_t r = 1; r <= 4; ++r) {
+                const double room = (u * (ktiles + kFillTiles) - r * (kts + kFillTiles)) * tk -
+                                    kFinishUs - S * kPieceUs + 1e-3;
+                if (room <= 0) break;
+                const uint64_t mt = std::min({mt_all, r * slots / (S * nt), u * slots / nt,
+                                              (uint64_t)std::min(room / (S * part_mt), 1e9)});
+                if (mt == 0 || (u == 2 && mt * nt <= slots)) continue;
+                if (r > max_rounds(mt * nt, slots)) continue;
+                worst = std::max(worst, S * std::min<uint64_t>(R, mt * vi.bm));
+            }
+        }
     }
     return worst;
 }
 
-// Split-K partial bytes the workspace reserves for batch B (8 bytes per
-// partial).  The bound is kept in the handle per padded-batch bucket (racing
+// At least the partial words of a query of any split-K plan for the batches
+// whose wide layout has N limb columns (exact partials count two words): every
+// ring variant valid for them (narrow variants, one column tile, for N = 128:
+// batches of at most 32), and the exact form's fewest pieces.  On a database
+// the ring does not serve, every register-staged variant instead.
+uint64_t worst_split_words(const pir_db_t* db, uint32_t N_wide) {
+    const uint64_t R = db->rows;
+    const uint32_t C = (uint32_t)db->cols;
+    const bool exact_ok = C <= kMaxExactCols && ring_ok(db);
+    const bool reg = !ring_serves(db);
+    uint64_t worst = 0;
+    for (uint32_t v = 1; v < kNumVariants; ++v) {
+        const VariantInfo& vi = kVariants[v];
+        if (vi.kind != (reg ? kReg : kRing)) continue;
+        if (vi.narrow ? N_wide != 128u : N_wide % vi.bn != 0) continue;
+        bool seen = false;   // the same tile under another pipeline
+        for (uint32_t w = 1; w < v && !seen; ++w) {
+            const VariantInfo& o = kVariants[w];
+            seen = o.kind == vi.kind && o.bm == vi.bm && o.bn == vi.bn && o.bk == vi.bk &&
+                   std::max(1u, o.per_cu) == std::max(1u, vi.per_cu);
+        }
+        if (seen) continue;
+        const uint32_t nt = vi.narrow ? 1u : N_wide / vi.bn;
+        worst = std::max(worst, worst_pieces(R, C, vi, nt, false));
+        if (!exact_ok) continue;
+        const uint32_t ktiles = ceil_div(C, vi.bk);
+        const uint64_t lo = ceil_div(ktiles, kExactSpan / vi.bk);
+        if (lo <= 1) {
+            worst = std::max(worst, 2 * worst_pieces(R, C, vi, nt, true));
+        } else {   // the pieces fill at most max_rounds rounds, or are the fewest
+            const uint64_t slots = (uint64_t)g_cus * std::max(1u, vi.per_cu);
+            const uint64_t rounds = max_rounds((uint64_t)nt * ceil_div(R, vi.bm), slots);
+            const uint64_t hi = std::min(kMaxSplits, ktiles / 2);
+            worst = std::max({worst, 2 * lo * R, 2 * std::min(hi * R, rounds * slots / nt * vi.bm)});
+        }
+    }
+    return worst;
+}
+
+// Split-K partial bytes the workspace reserves for batch B.  The bound takes
+// some microseconds and is kept in the handle per padded-batch bucket (racing
 // writers store the same value).
 size_t partial_bound(const pir_db_t* db, uint32_t B, uint32_t N) {
-    std::atomic<uint64_t>& slot = db->split_rows[batch_bucket(N / 4)];
+    std::atomic<uint64_t>& slot = db->split_words[batch_bucket(N / 4)];
     uint64_t cached = slot.load(std::memory_order_relaxed);
     uint64_t worst;
     if (cached != 0 && (cached >> 40) == N) {
         worst = cached & ((1ull << 40) - 1);
     } else {
-        worst = worst_split_rows(db, N);
+        worst = worst_split_words(db, N);
         slot.store(((uint64_t)N << 40) | worst, std::memory_order_relaxed);
     }
-    return worst ? round_up((size_t)worst * B * 8, kWsAlign) : 0;
+    return worst ? round_up((size_t)worst * B * 4, kWsAlign) : 0;
 }
 
 // Workspace: limb planes, exact column sums, split-K partials.  The
@@ -1991,7 +2037,7 @@ pir_status mfma_plan_batch(const pir_db_t* db, uint32_t B, const uint32_t* rows,
     if (sp.splits > 1) {
         const uint64_t n = (uint64_t)P.M * B;
         if ((n + 255) / 256 > 0x7FFFFFFFull) return PIR_ERR_SHAPE;   // k_finish grid
-        P.need += (size_t)sp.splits * P.M * B * 8;
+        P.need += (size_t)sp.splits * P.M * B * (exact ? 8 : 4);
         if (P.need > L.total) return PIR_ERR_WORKSPACE;   // cannot happen: the layout bounds every plan
     }
     *plan = P;
@@ -2004,7 +2050,7 @@ pir_status mfma_plan_batch(const pir_db_t* db, uint32_t B, const uint32_t* rows,
 void mfma_plan_fit(const pir_db_t* db, uint32_t B, size_t scratch_bytes, BatchPlan* plan) {
     if (plan->few || plan->splits <= 1 || plan->need <= scratch_bytes) return;
     const uint32_t ktiles = ceil_div(db->cols, kVariants[plan->variant].bk);
-    const size_t piece = (size_t)plan->M * B * 8;
+    const size_t piece = (size_t)plan->M * B * 4;
     const size_t room = scratch_bytes > plan->part_off ? (scratch_bytes - plan->part_off) / piece : 0;
     plan->kts = ceil_div(ktiles, std::max<size_t>(room, 1));
     plan->splits = ceil_div(ktiles, plan->kts);

@@ -25,9 +25,9 @@ struct pir_db {
     bool aligned;          // D and pitch are multiples of 16
     uint8_t variant[kBuckets];        // kernel variant per batch bucket (0 = built-in choice)
     uint8_t variant_rows[kBuckets];   // the same for row-gathered products
-    // Cached split-K bound per padded-batch bucket: (N << 40) | (splits x rows),
+    // Cached split-K bound per padded-batch bucket: (N << 40) | (partial words of a query),
     // 0 when not yet computed (see answer_mfma.hip).
-    mutable std::atomic<uint64_t> split_rows[kBuckets];
+    mutable std::atomic<uint64_t> split_words[kBuckets];
 };
 
 constexpr uint32_t kDbMagic = 0x51504952u;   // "QPIR"

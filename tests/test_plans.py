@@ -102,3 +102,34 @@ def test_small_batch_stream_tiles(probe, R, C, B, rows, whole):
     a split costs more than it gives."""
     r = probe([("few", R, C, C, int(C % 16 == 0), B)])[0]
     assert int(r[0]) == rows and (int(r[1]) == 1) == whole, r
+
+
+def test_workspace_holds_every_plan(probe):
+    """No call needs more than the workspace reported for its batch, whatever
+    its rows, form and pinned kernel, and the whole database's largest call
+    and the gathered ones of every tile count come near it."""
+    rng = random.Random(3)
+    calls = []
+    for _ in range(4000):
+        R = max(1, round(2 ** rng.uniform(0, 18)))
+        C = max(1, round(2 ** rng.uniform(4, 18)))
+        C = max(16, C // 16 * 16) if rng.random() < 0.5 else C
+        aligned = int(rng.random() < 0.7)
+        B = rng.choice((rng.randint(3, 16), rng.randint(17, 64), rng.randint(65, 300)))
+        mod = P if rng.random() < 0.3 else 0
+        for m in (0, 1, R, rng.randint(1, R), min(R, 128 * rng.randint(1, 40)),
+                  min(R, 256 * rng.randint(1, 600))):
+            calls.append(("batch", R, C, pitch16(C) if aligned else C, aligned, B, 0 if m else mod, m,
+                          rng.choice((0, 0, rng.randint(1, 25)))))
+    for c, r in zip(calls, probe(calls)):
+        assert int(r[0]) in (OK, UNSUPPORTED) and int(r[4]) <= int(r[5]), (c, r)
+
+
+def test_workspace_is_no_larger_than_plans_need(probe):
+    """Short rows: splitting them gains little, so little is reserved for it
+    (megabytes; without the product's times in the bound these took 134, 80
+    and 107)."""
+    calls = [("batch", 194870, 482, 482, 0, 128, 0, 0, 0), ("batch", 122601, 207, 207, 0, 41, 0, 0, 0),
+             ("batch", 96382, 511, 512, 1, 51, 0, 0, 0)]
+    for c, r in zip(calls, probe(calls)):
+        assert int(r[5]) < 8 << 20, (c, r)
