@@ -2028,6 +2028,7 @@ pir_status mfma_plan_batch(const pir_db_t* db, uint32_t B, const uint32_t* rows,
     P.part_off = L.part_off;
     if ((uint64_t)L.Cp / kIngJ > g_max_grid_y) return PIR_ERR_SHAPE;   // ingest grid
     P.M = M;
+    P.exact = exact;
     const SplitPlan sp = plan_splits(P.M, L.N, C, vi, exact, !ring_serves(db));
     P.splits = sp.splits;
     P.kts = sp.kts;
@@ -2046,9 +2047,9 @@ pir_status mfma_plan_batch(const pir_db_t* db, uint32_t B, const uint32_t* rows,
 
 // Fewer pieces, or one, where a fixed scratch cannot hold the partials of
 // the plan: the allocation-free entry point serves every batch whose limb planes
-// fit.
+// fit.  The field form's pieces also keep its sums exact and are left alone.
 void mfma_plan_fit(const pir_db_t* db, uint32_t B, size_t scratch_bytes, BatchPlan* plan) {
-    if (plan->few || plan->splits <= 1 || plan->need <= scratch_bytes) return;
+    if (plan->few || plan->exact || plan->splits <= 1 || plan->need <= scratch_bytes) return;
     const uint32_t ktiles = ceil_div(db->cols, kVariants[plan->variant].bk);
     const size_t piece = (size_t)plan->M * B * 4;
     const size_t room = scratch_bytes > plan->part_off ? (scratch_bytes - plan->part_off) / piece : 0;

@@ -129,6 +129,7 @@ size_t mfma_workspace_bytes(const pir_db_t* db, uint32_t B);
 struct BatchPlan {
     uint32_t variant;
     bool few;                    // dot4 stream (answer_gemv.hip)
+    bool exact;                  // field form
     uint32_t Bp, N, Cp;          // queries in the limb layout, limb rows, padded columns
     size_t colsum_off, part_off;
     uint32_t M, splits, kts;     // output rows, split-K pieces, k-tiles per piece
@@ -139,8 +140,9 @@ struct BatchPlan {
 // `planes`: the call will read pre-ingested wide-layout limb planes.
 pir_status mfma_plan_batch(const pir_db_t* db, uint32_t B, const uint32_t* rows, uint32_t m,
                            uint32_t modulus, bool planes, BatchPlan* plan);
-// Drop the split-K of a plan whose partials do not fit `scratch_bytes`, where
-// the whole product does not need it.
+// Cut a plan mod 2^32 whose partials do not fit `scratch_bytes` to the pieces
+// that do, or one; field-form plans stay as they are.  plan->need may still
+// pass the scratch (limb planes, or the field form): the caller checks it.
 void mfma_plan_fit(const pir_db_t* db, uint32_t B, size_t scratch_bytes, BatchPlan* plan);
 // Enqueue a planned call; `ws` must hold plan.need bytes, 256-byte aligned;
 // `planes` (or null) as written by mfma_ingest_planes for these queries.

@@ -4,6 +4,7 @@
 //   batch R C pitch aligned B modulus m variant  ->  status name splits kts need workspace
 // m > 0: the call gathers m rows; variant: pinned for B's bucket (0: none).
 //   noalloc R C pitch aligned B  ->  status name splits kts need, of the allocation-free call
+//   fit R C pitch aligned B modulus scratch  ->  name splits kts need, cut to a scratch
 //   answer R C pitch aligned 0  ->  name row_blocks splits threads, of the single query
 //   few R C pitch aligned B  ->  rows_per_block splits, of the dot4 stream
 #include <cstdio>
@@ -46,6 +47,13 @@ int main() {
                 if (p.need > PIR_NOALLOC_SCRATCH_BYTES) st = PIR_ERR_SHAPE;
             }
             printf("%d %s %u %u %zu\n", (int)st, mfma_variant_name(p.variant), p.splits, p.kts, p.need);
+        } else if (strcmp(op, "fit") == 0) {
+            unsigned long long scratch;
+            if (scanf("%u %llu", &mod, &scratch) != 2) return 2;
+            BatchPlan p{};
+            if (mfma_plan_batch(db.get(), B, nullptr, 0, mod, false, &p) != PIR_OK) return 3;
+            mfma_plan_fit(db.get(), B, scratch, &p);
+            printf("%s %u %u %zu\n", mfma_variant_name(p.variant), p.splits, p.kts, p.need);
         } else if (strcmp(op, "answer") == 0) {
             const GemvPlan p = gemv_plan(db.get());
             printf("%s %u %u %u\n", gemv_variant_name(p.variant), p.row_blocks, p.splits, p.threads);

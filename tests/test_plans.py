@@ -133,3 +133,45 @@ def test_workspace_is_no_larger_than_plans_need(probe):
              ("batch", 96382, 511, 512, 1, 51, 0, 0, 0)]
     for c, r in zip(calls, probe(calls)):
         assert int(r[5]) < 8 << 20, (c, r)
+
+
+def ktile(name):
+    return 128 if "_k128" in name or name.startswith("reg") else 64
+
+
+def test_fitting_keeps_the_field_forms_pieces(probe):
+    """The field form's accumulators cover at most 2^17 columns a piece: a
+    plan cut to a scratch keeps that (and then passes the scratch)."""
+    calls = [("fit", R, C, C, 1, B, P, scratch)
+             for R, C in ((3072, 1 << 18), (500, 1 << 20), (40000, 1 << 18), (3072, 1 << 15))
+             for B in (5, 40, 200) for scratch in (1 << 16, 1 << 24, 1 << 28)]
+    for c, r in zip(calls, probe(calls)):
+        assert int(r[2]) * ktile(r[0]) <= 1 << 17, (c, r)
+
+
+def test_fitting_cuts_to_what_the_scratch_holds(probe):
+    """Plans whose partials pass the scratch get the pieces that fit, down to
+    one, and are left alone where they fit."""
+    rng = random.Random(4)
+    calls, cut, whole = [], 0, 0
+    for _ in range(6000):
+        R, C = round(2 ** rng.uniform(4, 16)), round(2 ** rng.uniform(8, 18))
+        B, aligned = rng.randint(5, 200), rng.randint(0, 1)
+        base = ("fit", R, C, pitch16(C) if aligned else C, aligned, B, 0)
+        calls += [base + (1 << 60,), base + (round(2 ** rng.uniform(14, 29)),)]
+    out = probe(calls)
+    for c, full, r in zip(calls[1::2], out[0::2], out[1::2]):
+        splits, kts, need = (int(x) for x in r[1:])
+        part, ktiles = 4 * c[1] * c[5], -(-c[2] // ktile(r[0]))
+        planes = int(full[3]) - (part * int(full[1]) if int(full[1]) > 1 else 0)
+        assert splits * kts >= ktiles and (splits - 1) * kts < ktiles, (c, r)
+        assert need == planes + (part * splits if splits > 1 else 0), (c, full, r)
+        if int(full[3]) <= c[7]:
+            assert r == full
+        else:
+            assert need <= max(c[7], planes), (c, full, r)
+            if int(full[1]) > 1:
+                assert splits < int(full[1]), (c, full, r)
+                cut += splits > 1
+                whole += splits == 1
+    assert cut > 50 and whole > 50
