@@ -175,3 +175,16 @@ def test_fitting_cuts_to_what_the_scratch_holds(probe):
                 cut += splits > 1
                 whole += splits == 1
     assert cut > 50 and whole > 50
+
+
+@pytest.mark.parametrize("R,C,pad,B,pieces", [
+    (168, 85906, 0, 130, "some"), (355, 86016, 0, 183, "some"), (234, 130684, 0, 78, "one"),
+    (624, 64400, 0, 224, "one"), (556, 65098, 6, 243, "one")])
+def test_noalloc_calls_that_are_cut(probe, R, C, pad, B, pieces):
+    """The calls that tests/test_gpu_noalloc_shapes.py runs do pass the scratch
+    uncut, and are cut to fewer pieces or to one."""
+    pitch = C + pad
+    full, r = probe([("fit", R, C, pitch, int(pitch % 16 == 0), B, 0, 1 << 60),
+                     ("noalloc", R, C, pitch, int(pitch % 16 == 0), B)])
+    assert int(full[3]) > 64 << 20 and int(r[0]) == OK and int(r[4]) <= 64 << 20
+    assert int(r[2]) == 1 if pieces == "one" else 1 < int(r[2]) < int(full[1])
