@@ -272,8 +272,7 @@ SplitPlan answer1_plan(const pir_db_t* db, uint32_t rows_per_block) {
     return SplitPlan{(uint32_t)((chunks + best - 1) / best), (uint32_t)(best * kChunk)};
 }
 
-size_t split_bytes(const pir_db_t* db, uint32_t rows_per_block) {
-    const SplitPlan p = answer1_plan(db, rows_per_block);
+size_t split_bytes(const pir_db_t* db, const SplitPlan& p) {
     return p.splits > 1 ? round_up((size_t)p.splits * db->rows * 4, kWsAlign) : 0;
 }
 
@@ -285,7 +284,7 @@ pir_status launch_answer1(const pir_db_t* db, const uint32_t* q, uint32_t* a, vo
     const uint32_t R = (uint32_t)db->rows, C = (uint32_t)db->cols;
     uint32_t* dst = a;
     if (p.splits > 1) {
-        if (!ws || ws_bytes < split_bytes(db, kRows) || ((uintptr_t)ws % kWsAlign))
+        if (!ws || ws_bytes < split_bytes(db, p) || ((uintptr_t)ws % kWsAlign))
             return PIR_ERR_WORKSPACE;
         dst = static_cast<uint32_t*>(ws);
     }
@@ -640,19 +639,21 @@ uint32_t gemv_variant_count() { return kNumGemv; }
 
 const char* gemv_variant_name(uint32_t v) { return v < kNumGemv ? kGemv[v].name : nullptr; }
 
-// Enough for every variant, so a workspace sized once serves any tuning.
-size_t gemv_workspace_bytes(const pir_db_t* db) {
-    size_t m = 0;
-    for (uint32_t v = 1; v < kNumGemv; ++v) {
-        const size_t b = split_bytes(db, kGemv[v].rows_per_block);
-        m = b > m ? b : m;
-    }
-    return m;
+// Both depend on the shape only; choosing and sizing them on every call took
+// up to 3 us of a call's host time.  The workspace is enough for every
+// variant, so one sized once serves any tuning.
+void gemv_open(pir_db_t* db) {
+    db->answer_variant = gemv_auto(db);
+    db->answer_ws = 0;
+    for (uint32_t v = 1; v < kNumGemv; ++v)
+        db->answer_ws = std::max(db->answer_ws, split_bytes(db, answer1_plan(db, kGemv[v].rows_per_block)));
 }
+
+size_t gemv_workspace_bytes(const pir_db_t* db) { return db->answer_ws; }
 
 static uint32_t gemv_choice(const pir_db_t* db) {
     const uint32_t v = db->variant[0];
-    return v == 0 || v >= kNumGemv ? gemv_auto(db) : v;
+    return v == 0 || v >= kNumGemv ? db->answer_variant : v;
 }
 
 GemvPlan gemv_plan(const pir_db_t* db) {

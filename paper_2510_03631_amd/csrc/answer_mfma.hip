@@ -1768,7 +1768,7 @@ SplitPlan plan_splits(uint32_t M, uint32_t N, uint32_t C, const VariantInfo& vi,
 //   60000 x 12000     186    119    288   195    489   371    732   718
 // `wide`: the limb planes are laid out already, or rows gathered: no narrow
 // tile.
-uint32_t default_gemm(const pir_db_t* db, uint32_t B, uint32_t M, bool exact, bool wide) {
+uint32_t priced_gemm(const pir_db_t* db, uint32_t B, uint32_t M, bool exact, bool wide) {
     static constexpr uint32_t ring[] = {kVarNarrow128, kVarNarrow256, kVarRing128,
                                         kVarRing128x2, kVarRing256,   kVarRing4wD3};
     static constexpr uint32_t reg[] = {kVarReg128, kVarReg128x256, kVarReg256};
@@ -1788,6 +1788,18 @@ uint32_t default_gemm(const pir_db_t* db, uint32_t B, uint32_t M, bool exact, bo
         }
     }
     return best;
+}
+
+// Pricing takes up to 0.3 us; the choice for whole-database products is kept
+// in the handle (racing writers store the same value).
+uint32_t default_gemm(const pir_db_t* db, uint32_t B, uint32_t M, bool exact, bool wide) {
+    if (wide || M != db->rows) return priced_gemm(db, B, M, exact, wide);
+    std::atomic<uint32_t>& slot = db->tile[exact][batch_bucket(B)];
+    const uint32_t kept = slot.load(std::memory_order_relaxed);
+    if (kept >> 8 == B) return kept & 0xFFu;
+    const uint32_t v = priced_gemm(db, B, M, exact, false);
+    slot.store((B << 8) | v, std::memory_order_relaxed);
+    return v;
 }
 
 // The dot4 stream beats the padded matrix-core tile up to two queries; at

@@ -69,6 +69,9 @@ pir_status pir_db_open(uint8_t* d_D, uint64_t rows, uint64_t cols, uint64_t row_
     db->device = dev;
     db->aligned = ((uintptr_t)d_D % 16 == 0) && (row_pitch % 16 == 0);
     for (auto& slot : db->split_words) slot.store(0, std::memory_order_relaxed);
+    for (auto& form : db->tile)
+        for (auto& slot : form) slot.store(0, std::memory_order_relaxed);
+    gemv_open(db);
     if (hipMalloc(&db->rowsum, rows * sizeof(uint32_t)) != hipSuccess) {
         delete db;
         return PIR_ERR_NO_MEMORY;

@@ -28,6 +28,12 @@ struct pir_db {
     // Cached split-K bound per padded-batch bucket: (N << 40) | (partial words of a query),
     // 0 when not yet computed (see answer_mfma.hip).
     mutable std::atomic<uint64_t> split_words[kBuckets];
+    // The built-in tile of a whole-database product, (B << 8) | variant, per
+    // batch bucket and form (mod 2^32, field); 0 when not yet chosen.
+    mutable std::atomic<uint32_t> tile[2][kBuckets];
+    // Single query: the built-in kernel and the workspace of the largest one.
+    uint32_t answer_variant;
+    size_t answer_ws;
 };
 
 constexpr uint32_t kDbMagic = 0x51504952u;   // "QPIR"
@@ -90,6 +96,8 @@ __device__ inline uint32_t ql_col(uint32_t k) { return (k >> 7) * 4096u + (k & 1
 // ---- single-query path (answer_gemv.hip)
 uint32_t gemv_variant_count();
 const char* gemv_variant_name(uint32_t v);
+// Fill in the handle's single-query fields, from its shape.
+void gemv_open(pir_db_t* db);
 size_t gemv_workspace_bytes(const pir_db_t* db);
 // Kernel and grid of a single-query call: row blocks x column splits
 // workgroups of `threads` threads.

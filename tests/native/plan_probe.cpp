@@ -5,6 +5,8 @@
 // m > 0: the call gathers m rows; variant: pinned for B's bucket (0: none).
 //   noalloc R C pitch aligned B  ->  status name splits kts need, of the allocation-free call
 //   fit R C pitch aligned B modulus scratch  ->  name splits kts need, cut to a scratch
+//   kept R C pitch aligned B modulus other  ->  names of the plans of B, of B mod
+//                           p, of `other` and of the first two again, on one handle
 //   answer R C pitch aligned 0  ->  name row_blocks splits threads, of the single query
 //   few R C pitch aligned B  ->  rows_per_block splits, of the dot4 stream
 #include <cstdio>
@@ -21,6 +23,7 @@ static std::unique_ptr<pir_db> handle(uint64_t R, uint64_t C, uint64_t pitch, in
     db->cols = C;
     db->pitch = pitch;
     db->aligned = aligned != 0;
+    gemv_open(db.get());
     return db;
 }
 
@@ -54,6 +57,16 @@ int main() {
             if (mfma_plan_batch(db.get(), B, nullptr, 0, mod, false, &p) != PIR_OK) return 3;
             mfma_plan_fit(db.get(), B, scratch, &p);
             printf("%s %u %u %zu\n", mfma_variant_name(p.variant), p.splits, p.kts, p.need);
+        } else if (strcmp(op, "kept") == 0) {
+            unsigned other;
+            if (scanf("%u %u", &mod, &other) != 2) return 2;
+            const unsigned Bs[] = {B, B, other, B, B}, ms[] = {0, mod, 0, 0, mod};
+            for (int i = 0; i < 5; ++i) {
+                BatchPlan p{};
+                const pir_status st = mfma_plan_batch(db.get(), Bs[i], nullptr, 0, ms[i], false, &p);
+                printf("%d:%s ", (int)st, mfma_variant_name(p.variant));
+            }
+            printf("\n");
         } else if (strcmp(op, "answer") == 0) {
             const GemvPlan p = gemv_plan(db.get());
             printf("%s %u %u %u\n", gemv_variant_name(p.variant), p.row_blocks, p.splits, p.threads);

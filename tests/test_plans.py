@@ -188,3 +188,20 @@ def test_noalloc_calls_that_are_cut(probe, R, C, pad, B, pieces):
                      ("noalloc", R, C, pitch, int(pitch % 16 == 0), B)])
     assert int(full[3]) > 64 << 20 and int(r[0]) == OK and int(r[4]) <= 64 << 20
     assert int(r[2]) == 1 if pieces == "one" else 1 < int(r[2]) < int(full[1])
+
+
+def test_kept_tile_choice(probe):
+    """A handle's kept choice is the choice of a fresh handle, for each batch
+    size and form, in any order."""
+    rng = random.Random(5)
+    kept, fresh = [], []
+    for _ in range(500):
+        R, C = round(2 ** rng.uniform(4, 16)), round(2 ** rng.uniform(4, 16)) // 16 * 16
+        k = rng.randint(2, 8)
+        B, other = rng.randint(2 ** (k - 1) + 1, 2 ** k), rng.randint(2 ** (k - 1) + 1, 2 ** k)
+        kept.append(("kept", R, C, C, 1, B, P, other))
+        fresh += [("batch", R, C, C, 1, b, m, 0, 0) for b, m in ((B, 0), (B, P), (other, 0))]
+    out = probe(fresh)
+    for i, r in enumerate(probe(kept)):
+        a, b, c = (f"{x[0]}:{x[1]}" for x in out[3 * i:3 * i + 3])
+        assert r == [a, b, c, a, b], (kept[i], r)
