@@ -1841,20 +1841,28 @@ struct BatchLayout {
 // calls have fewer rows, and so may split more).  The loops follow
 // plan_splits: S pieces of mt row tiles in `r` rounds are only chosen where
 // they take less time than whole tiles in u rounds, which bounds mt.
-uint64_t worst_pieces(uint64_t R, uint32_t C, const VariantInfo& vi, uint32_t nt, bool exact) {
+// What fills those rounds bounds them all, and the search ends near it, or
+// where it cannot pass `least`.
+uint64_t worst_pieces(uint64_t R, uint32_t C, const VariantInfo& vi, uint32_t nt, bool exact,
+                      uint64_t least) {
     const uint32_t ktiles = ceil_div(C, vi.bk);
     const uint64_t slots = (uint64_t)g_cus * std::max(1u, vi.per_cu);
     const uint64_t mt_all = ceil_div(R, vi.bm), hi = std::min(kMaxSplits, ktiles / 2);
+    const uint64_t most = std::min(hi * R, max_rounds(mt_all * nt, slots) * slots / nt * vi.bm);
+    if (hi < 2 || most <= least) return least;
     const double tk = ktile_us(vi);
     const double part_mt = part_us(vi.bm, nt * vi.bn, exact);   // per piece and row tile
-    uint64_t worst = 0;
+    uint64_t worst = least;
+    uint32_t kts_before = 0;
     for (uint64_t S = 2; S <= hi; ++S) {
         const uint32_t kts = ceil_div(ktiles, (uint32_t)S);
-        if (ceil_div(ktiles, kts) != S) continue;
+        if (kts == kts_before) continue;   // fewer pieces than S: the same plan
+        kts_before = kts;
+        const double gain1 = (ktiles + kFillTiles) * tk, piece = (kts + kFillTiles) * tk;
+        const double fixed = kFinishUs + S * kPieceUs - 1e-3;
         for (uint64_t u = 1; u <= 2; ++u) {
             for (uint64_t r = 1; r <= 4; ++r) {
-                const double room = (u * (ktiles + kFillTiles) - r * (kts + kFillTiles)) * tk -
-                                    kFinishUs - S * kPieceUs + 1e-3;
+                const double room = u * gain1 - r * piece - fixed;
                 if (room <= 0) break;
                 const uint64_t mt = std::min({mt_all, r * slots / (S * nt), u * slots / nt,
                                               (uint64_t)std::min(room / (S * part_mt), 1e9)});
@@ -1863,6 +1871,7 @@ uint64_t worst_pieces(uint64_t R, uint32_t C, const VariantInfo& vi, uint32_t nt
                 worst = std::max(worst, S * std::min<uint64_t>(R, mt * vi.bm));
             }
         }
+        if (worst + worst / 32 >= most) return most;
     }
     return worst;
 }
@@ -1890,12 +1899,12 @@ uint64_t worst_split_words(const pir_db_t* db, uint32_t N_wide) {
         }
         if (seen) continue;
         const uint32_t nt = vi.narrow ? 1u : N_wide / vi.bn;
-        worst = std::max(worst, worst_pieces(R, C, vi, nt, false));
+        worst = worst_pieces(R, C, vi, nt, false, worst);
         if (!exact_ok) continue;
         const uint32_t ktiles = ceil_div(C, vi.bk);
         const uint64_t lo = ceil_div(ktiles, kExactSpan / vi.bk);
         if (lo <= 1) {
-            worst = std::max(worst, 2 * worst_pieces(R, C, vi, nt, true));
+            worst = std::max(worst, 2 * worst_pieces(R, C, vi, nt, true, worst / 2));
         } else {   // the pieces fill at most max_rounds rounds, or are the fewest
             const uint64_t slots = (uint64_t)g_cus * std::max(1u, vi.per_cu);
             const uint64_t rounds = max_rounds((uint64_t)nt * ceil_div(R, vi.bm), slots);
