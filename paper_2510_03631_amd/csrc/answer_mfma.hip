@@ -1808,16 +1808,18 @@ uint32_t default_gemm(const pir_db_t* db, uint32_t B, uint32_t M, bool exact, bo
 // databases of up to kFewSmall bytes, bound by launches, do not notice (one
 // launch or two instead of three; four queries: 1024 x 1024 12-14 vs 16-18
 // us, 5000 x 2001 16 vs 17-21, 4096 x 4096 16 vs 17; 30000 x 3000 38 vs 31).
-// Rows shorter than a wave's load leave lanes idle, and the tile leads again
-// (GPU time, four queries: 65536 x 256 22.8 vs 14.2 us, 2^18 x 64 81 vs 33,
-// 2^20 x 16 320 vs 112); their partials would also outgrow a fixed scratch.
+// Rows shorter than a wave's load leave its lanes idle and count as whole
+// ones: few of them still run best in the stream (3277 x 1017 11.9 vs 21 us,
+// 13312 x 72 11.5 vs 14.7), many in the tile (GPU time 65536 x 256 22.8 vs 14.2,
+// 2^18 x 64 81 vs 33, 2^20 x 16 320 vs 112), where the stream's partials would
+// also outgrow a fixed scratch.
 constexpr uint32_t kFewDefault = 2;
 constexpr uint64_t kFewSmall = 1ull << 24;
-constexpr uint32_t kFewCols = 1024;
+constexpr uint64_t kFewCols = 1024;
 
 bool few_default(const pir_db_t* db, uint32_t B) {
     return B <= kFewDefault ||
-           (B <= kFewMax && db->cols >= kFewCols && db->rows * db->cols <= kFewSmall);
+           (B <= kFewMax && db->rows * std::max(db->cols, kFewCols) <= kFewSmall);
 }
 
 // Gathered rows (the incremental hint): scattered row addresses add

@@ -205,3 +205,13 @@ def test_kept_tile_choice(probe):
     for i, r in enumerate(probe(kept)):
         a, b, c = (f"{x[0]}:{x[1]}" for x in out[3 * i:3 * i + 3])
         assert r == [a, b, c, a, b], (kept[i], r)
+
+
+@pytest.mark.parametrize("R,C,few", [
+    (1024, 1024, True), (4096, 4096, True), (3277, 1017, True), (13312, 72, True), (16384, 1, True),
+    (16385, 64, False), (65536, 256, False), (1 << 20, 16, False), (30000, 3000, False)])
+@pytest.mark.parametrize("B", [3, 4])
+def test_stream_or_tile_for_three_and_four_queries(probe, R, C, few, B):
+    """The dot4 stream up to 16 MiB, rows below 1024 bytes counted as 1024."""
+    r = probe([("batch", R, C, pitch16(C), 1, B, 0, 0, 0)])[0]
+    assert (r[1] == "few") == few
