@@ -321,7 +321,7 @@ constexpr uint32_t kGemvShort = 2, kGemvLong = 3, kGemvLarge = 4, kGemvMid = 5, 
 // they do not (one workgroup in four rounds for a CU, three for most), and on
 // larger databases, eight waves of 8 rows with split columns come out even.
 // Short rows pay a wave's start and end per row, so they take more rows a
-// wave; databases of at most 1024 rows only fill the chip by splitting their
+// wave; databases of at most 512 rows only fill the chip by splitting their
 // columns, where few rows a wave leave most pieces to split.  GPU us with the
 // splits of answer1_plan (200 random shapes, 2^22 to 2^30 bytes: 1.3% over the
 // fastest kernel of each in the geometric mean):
@@ -345,7 +345,7 @@ constexpr uint64_t kGemvEven = 3ull << 24, kGemvBig = 3ull << 26, kGemvHuge = 1u
 
 uint32_t gemv_by_size(const pir_db_t* db) {
     const uint64_t R = db->rows, C = db->cols, bytes = R * C;
-    if (R <= 1024) return kGemvSmall;
+    if (R <= 512) return kGemvSmall;
     if (R >= 12000) {
         if (C < 1280) return kGemvShort;
         if (bytes < kGemvHuge || C <= 2048) return kGemvMid;
@@ -561,11 +561,17 @@ uint32_t few_rows(const pir_db_t* db, uint32_t B) {
 SplitPlan few_plan(const pir_db_t* db, uint32_t B) {
     const uint32_t rows = few_rows(db, B);
     const uint64_t blocks = row_blocks(db, rows);
-    if (db->cols <= (uint64_t)kSlice && (rows == 16u || blocks >= 256u)) return plan_splits(db, 1, kChunk);
+    // Short rows stay whole: of one slice in blocks of 16 rows, of two chunks in
+    // 256 and more blocks of 64 (17784 x 2343, two field queries: two pieces
+    // 24.8 us, whole 28.2).
+    if (db->cols <= (rows == 16u ? (uint64_t)kSlice : blocks >= 256u ? 2u * kChunk : 0u))
+        return plan_splits(db, 1, kChunk);
     if (rows == 64u) return plan_splits(db, 768 / blocks, kChunk);
-    // Up to eight pieces of half a slice, beyond only of whole slices (200 x
-    // 100000, one query: 25 pieces 17 us, 49 pieces 21).
-    const SplitPlan half = plan_splits(db, std::min<uint64_t>(768 / blocks, 8), kSlice / 2);
+    // Up to eight pieces of half a slice for at most a block per CU, beyond only
+    // of whole slices (200 x 100000, one query: 25 pieces 17 us, 49 pieces 21;
+    // 6144 x 4352, 384 blocks: whole 13.4, two pieces 14.9).
+    const uint64_t halves = blocks <= 256u ? std::min<uint64_t>(768 / blocks, 8) : 1;
+    const SplitPlan half = plan_splits(db, halves, kSlice / 2);
     const SplitPlan whole = plan_splits(db, 512 / blocks, kSlice);
     return half.splits > whole.splits ? half : whole;
 }

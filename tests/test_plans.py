@@ -215,3 +215,9 @@ def test_stream_or_tile_for_three_and_four_queries(probe, R, C, few, B):
     """The dot4 stream up to 16 MiB, rows below 1024 bytes counted as 1024."""
     r = probe([("batch", R, C, pitch16(C), 1, B, 0, 0, 0)])[0]
     assert (r[1] == "few") == few
+
+
+@pytest.mark.parametrize("R,C,B,splits", [(17784, 2343, 2, 2), (16384, 2048, 2, 1),
+                                          (6144, 4352, 1, 1), (3072, 8192, 1, 4), (200, 100000, 1, 25)])
+def test_small_batch_stream_pieces(probe, R, C, B, splits):
+    assert int(probe([("few", R, C, C, int(C % 16 == 0), B)])[0][1]) == splits
