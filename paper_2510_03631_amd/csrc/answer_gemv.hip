@@ -72,7 +72,7 @@ __device__ inline void load_chunk(u32x4 (&d)[RW], const uint8_t* const (&rp)[RW]
 
 // In a row's ragged last chunk, move the bytes of the one lane whose 16
 // bytes cross the end into place.  (Lanes past the end hold anything: they
-// meet zero limbs.)
+// meet zero limbs.)  Rows of whole 16-byte pieces have no such lane.
 template <int RW>
 __device__ inline void align_tail(u32x4 (&d)[RW], uint32_t c, uint32_t C) {
     const uint32_t sh = 8u * min(c - min(c, C - 16u), 15u);
@@ -193,7 +193,7 @@ __global__ __launch_bounds__(64 * WV) void k_answer1(const uint8_t* __restrict__
                 asm volatile("");   // keep the two branches' products apart
             } else {
                 if (!kAhead || c0 != s0) load_chunk<RW>(d, rp, c, C);
-                if (c0 + kChunk > C) align_tail<RW>(d, c, C);
+                if (C % 16u != 0u && c0 + kChunk > C) align_tail<RW>(d, c, C);
 #pragma unroll
                 for (int i = 0; i < RW; ++i) acc[i] += dot16(d[i], L);
             }
@@ -456,7 +456,7 @@ __global__ __launch_bounds__(64 * WV) void k_answer_few(
         for (uint32_t c0 = s0; c0 < se; c0 += kChunk) {
             const uint32_t li = (c0 - s0) / 16 + lane;
             if (RW > 8 || c0 != s0) load_chunk<RW>(d, rp, c0 + 16u * lane, C);
-            if (c0 + kChunk > C) align_tail<RW>(d, c0 + 16u * lane, C);
+            if (C % 16u != 0u && c0 + kChunk > C) align_tail<RW>(d, c0 + 16u * lane, C);
 #pragma unroll
             for (int b = 0; b < NQ; ++b) {
                 u32x4 L[4];
