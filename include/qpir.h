@@ -88,7 +88,11 @@ uint32_t pir_version(void);
  *   row_pitch  bytes between row starts, >= cols.  The fast paths need
  *              d_D and row_pitch to be multiples of 16; other values are
  *              served exactly too (streams at the same rate, batches by
- *              register-staged tiles).
+ *              register-staged tiles).  Where both are, the batched kernels
+ *              read rows in whole 16-byte pieces: with C no multiple of 16
+ *              also the bytes up to the next multiple of 16 after a row's
+ *              end (after the last row's too; never used, never written),
+ *              which share the 16-byte granule of the row's last byte.
  *   stream     stream for the metadata pass (per-row byte sums, R words of
  *              device memory allocated and owned by the handle).  The call
  *              synchronizes this stream before returning.
@@ -161,8 +165,9 @@ pir_status pir_answer_batch(pir_db_t* db, const uint32_t* d_Q, uint32_t B, uint3
  * Errors: as pir_answer_batch, and PIR_ERR_SHAPE (nothing enqueued) when
  * the call needs more than PIR_NOALLOC_SCRATCH_BYTES of scratch (about
  * 4 * B * C bytes of limb planes; the product is split along C only as far
- * as its partials fit beside them; 64 queries fit a 32768 x 32768 database), PIR_ERR_DEVICE when the array's address could
- * not be resolved on this device.
+ * as its partials fit beside them; 64 queries fit a 32768 x 32768 database),
+ * PIR_ERR_DEVICE when the array's address could not be resolved on this
+ * device.
  */
 #define PIR_NOALLOC_SCRATCH_BYTES (64u << 20)
 pir_status pir_answer_batch_noalloc(pir_db_t* db, const uint32_t* d_Q, uint32_t B,
@@ -308,7 +313,8 @@ pir_status pir_client_decode(const uint32_t* d_H, uint32_t R, uint32_t n, const 
  * pir_client_query / pir_client_decode.
  *
  * pir_client_mat_open: prepare M (rows x n words, row-major, device; read
- *   during the call only).  Allocates rows x 4n bytes of device memory and a
+ *   during the call only).  Allocates rows x 4n bytes of device memory (4n
+ *   rounded up to 16, and two words per row) and a
  *   database handle over them, owned by the returned object; synchronizes
  *   `stream`.  Errors: PIR_ERR_INVALID_ARG, PIR_ERR_SHAPE,
  *   PIR_ERR_UNSUPPORTED, PIR_ERR_NO_MEMORY, PIR_ERR_DEVICE.

@@ -451,8 +451,8 @@ def client_decode(H: torch.Tensor, S: torch.Tensor, answers: torch.Tensor,
 class ClientMatrix:
     """A word matrix prepared for the matrix-core client steps
     (``pir_client_mat_*``): the public matrix A for :meth:`query`, the hint H
-    for :meth:`decode`.  Holds rows x 4n bytes of device memory until
-    :meth:`close`."""
+    for :meth:`decode`.  Holds rows x 4n bytes of device memory (4n
+    rounded up to 16) and two words per row until :meth:`close`."""
 
     def __init__(self, M: torch.Tensor, stream=None):
         if M.dim() != 2:

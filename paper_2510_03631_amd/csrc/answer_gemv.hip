@@ -20,9 +20,10 @@
 //   slice's first chunk before the slice's query words are staged.  The
 //   stream is read with non-temporal loads.
 // * Rows may start at any address and have any length: loads of 16 bytes
-//   need no alignment on gfx950.  (Reading unaligned rows byte by byte took
-//   450 us for 20000 x 10007 bytes; 16-byte loads take 43 us, and 35 us when
-//   the same rows are padded to an aligned pitch.)
+//   need no alignment on gfx950.  (20000 x 10007 unaligned bytes, the same
+//   buffers on every call: 452 us byte by byte, 41.2 us so, and 33.6 us when
+//   the rows are padded to an aligned pitch; with other inputs on every call
+//   531 and 41.7 us.)
 // * After the column loop each lane holds RW partial sums; they are
 //   transposed through LDS and finished with lane shuffles, so one lane per
 //   row writes the result.

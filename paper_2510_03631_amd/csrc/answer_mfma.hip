@@ -689,9 +689,10 @@ struct Tile {
 // loads of tile u+1 are issued one after each of the first MFMAs of tile u
 // and written to the other buffer after its last.  Bound by that staging: the
 // loads have one tile's MFMAs to land, and every byte passes the register
-// file.  37 and 200 queries on 20000 rows of 10007 bytes, whole calls: byte
-// loads, no split-K 900 and 1885 us; 16-byte loads and split-K, one buffer and
-// two barriers 115 and 417 us; now 84 and 278 us.
+// file.  37 and 200 queries on 20000 rows of 10007 bytes, whole calls on the
+// same buffers: byte loads, no split-K 698 and 1887 us; 16-byte loads and
+// split-K, one buffer and two barriers 115 and 417 us; now 88 and 282 us (37
+// queries with other inputs on every call: 900 and 90 us).
 template <class T, bool GATHER, int MODE>
 __global__ __launch_bounds__(T::THREADS) void k_gemm(const uint8_t* __restrict__ D, uint64_t pitch,
                                                      const int8_t* __restrict__ QL, uint32_t Cp,
@@ -1650,7 +1651,7 @@ bool ring_ok(const pir_db_t* db) { return db->aligned && (db->cols % 16 == 0); }
 
 // Databases the ring serves: aligned rows of any length (a row's last 16-byte
 // segment lies inside its pitch).  37 and 200 queries on 20000 rows of 10007
-// bytes, pitch 10240: 74 and 228 us, against 166 and 454 us while rows whose
+// bytes, pitch 10240: 75 and 225 us, against 166 and 454 us while rows whose
 // length is not a multiple of 16 went through registers.
 bool ring_serves(const pir_db_t* db) { return db->aligned; }
 

@@ -189,10 +189,11 @@ __global__ __launch_bounds__(kThreads) void k_chor_stream(const uint32_t* __rest
 // instructions beside them (about six per matrix instruction; a loop of bare
 // 0/1 matrix instructions reaches 7.6 POP/s in the power budget, 7.3 with
 // four vector instructions beside each).  Against lookups in 16-entry XOR
-// tables in LDS, which this replaces, whole calls on 2^18 blocks of 3 KB: 8
-// queries 230 -> 137 us (5.9 TB/s), 32 252 -> 143 us, 64 350 -> 192 us, 128
-// 617 -> 339 us, 1024 2.88 -> 2.30 ms (5.7 POP/s); on 2^13 blocks: 16 queries
-// 52 -> 14 us, 128 148 -> 22 us, 1024 249 -> 100 us.
+// tables in LDS, which this replaces, whole calls on one machine: 2^18 blocks of
+// 3 KB, 8 queries 230 -> 146 us (5.5 TB/s), 32 252 -> 145 us, 64 353 -> 201 us,
+// 128 618 -> 353 us, 1024 2.88 -> 2.36 ms (5.6 POP/s); 2^13 blocks, 16 queries 53
+// -> 16 us, 128 151 -> 22 us, 1024 250 -> 97 us.  Other machines differ by up to
+// 5%.
 template <int N>
 using I = std::integral_constant<int, N>;
 
@@ -593,8 +594,9 @@ __global__ __launch_bounds__(256 * NH, TM == 1 ? 2 : 1) void k_chor_parity(
 // Row slabs of a launch.  One workgroup runs per CU, so a launch takes
 // ceil(workgroups / 256) rounds, each of a slab's pairs of chunks plus the
 // pipeline fill and the epilogue, worth about three pairs; take the count with
-// the least total (128 queries on 2^18 blocks of 3 KB, 48 workgroups per slab:
-// 5 or 16 slabs 375 us, 8 slabs 388 us, 21 slabs 410 us).
+// the least total (2^18 blocks of 3 KB: 128 queries, 48 workgroups per slab, 5
+// slabs 359 us, 8 410, 16 (taken) 363, 21 370; 64 queries 10 slabs 193, 16 227, 21
+// (taken) 196; 32 queries 10 slabs 226, 21 (taken) 140, 32 173).
 struct Slabs {
     uint32_t count, rows;
 };
@@ -728,8 +730,9 @@ pir_status chor_xor(const uint32_t* d_DB, uint32_t rows, uint32_t words, uint64_
     }
     // Up to 32 queries one 32-query tile with two workgroup halves; above,
     // 64 queries per workgroup, which halves the masks and the transposes
-    // per matrix instruction (64 queries on 2^18 blocks: 205 us against 284
-    // us as two 32-query groups).
+    // per matrix instruction (2^18 blocks of 3 KB: 64 queries 196 us against
+    // 255 as two 32-query groups, 40 queries 192 against 249; 32 queries 197
+    // against 141 as one).
     if (B <= 32) return launch_parity<1, 2>(d_DB, rows, words, pitch, d_Q, B, d_init, d_out, s);
     return launch_parity<2, 1>(d_DB, rows, words, pitch, d_Q, B, d_init, d_out, s);
 }
