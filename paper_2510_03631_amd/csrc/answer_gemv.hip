@@ -609,8 +609,10 @@ pir_status launch_few_t(const pir_db_t* db, const BatchIO& io, uint32_t B, uint3
 template <int NQ, bool EXACT>
 pir_status launch_few(const pir_db_t* db, const BatchIO& io, uint32_t B, uint32_t modulus,
                       void* ws, hipStream_t s) {
-    if (few_rows(db, B) == 64u) return launch_few_t<NQ, 16, 4, EXACT>(db, io, B, modulus, ws, s);
-    return launch_few_t<NQ, 4, 4, EXACT>(db, io, B, modulus, ws, s);
+    if constexpr (NQ <= 2) {
+        if (few_rows(db, B) == 16u) return launch_few_t<NQ, 4, 4, EXACT>(db, io, B, modulus, ws, s);
+    }
+    return launch_few_t<NQ, 16, 4, EXACT>(db, io, B, modulus, ws, s);
 }
 
 }  // namespace
